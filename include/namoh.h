@@ -411,8 +411,9 @@ namoh_status namoh_shared_prefill_cache(const void* k, const void* v, int dtype,
  * Supported: bf16 x and weights, d_head in {64, 128}, d_model a multiple
  * of 128 (else NAMOH_ERR_UNSUPPORTED).  fp32 accumulation on the matrix
  * cores; q/k/v rounded to bf16.  The output projection takes one of two
- * forms, chosen from H, K and d (the dense form when H * d <= 384 * K and
- * H <= 64):
+ * forms, chosen from the sizes (the dense form when H * d <= 384 * K and
+ * H <= 64, and up to 512 * K, with d = 128 up to 1024 * K, where B * T and
+ * d_model give enough output tiles; finite weights assumed in both):
  *   per-pair: every routed pair's row h W_O^(i) is formed (rounded to bf16)
  *     and the K rows of a token are summed with their gates in k order;
  *   dense:    each token's gated head rows g h (rounded to bf16) enter one

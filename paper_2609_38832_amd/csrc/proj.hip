@@ -5,13 +5,14 @@
 // (batch b, head i) segment the packed rows r < n_{b,i} are the tokens of the
 // ordered index set I_i, and only those pairs are projected.
 //
-//   k_proj_big<QKV>   [q|k|v]_{t,i} = x_t W_QKV[i]^T for the segment's rows:
-//                     a grouped GEMM (M = n_{b,i}, N = 3d, K = d_model) whose
-//                     data rows are gathered by token; the 4-column runs of
-//                     each result row go straight to the dense q, k, v rows
-//                     of the pair (other rows are never written).
-//   k_out_map +       dense output projection (H d <= 384 K): the tokens'
-//   k_proj_big<OUT>   gated head rows against the stacked W_O over all heads.
+//   k_proj_tile<QKV>  [q|k|v]_{t,i} = x_t W_QKV[i]^T for the segment's rows:
+//                     a grouped GEMM (M = sum over b of n_{b,i}, N = 3d,
+//                     K = d_model) whose data rows are gathered by token;
+//                     the 8-column runs of each result row go straight to
+//                     the dense q, k, v rows of the pair (other rows are
+//                     never written).
+//   k_out_map +       dense output projection (out_dense): the tokens'
+//   k_proj_tile<OUT>  gated head rows against the stacked W_O over all heads.
 //   k_proj_gemm +     per-pair output projection (otherwise): Y_r = h_r
 //   k_combine         W_O[i]^T for every packed head-output row r (bf16 rows
 //                     in packed order), then o_t = sum_k g_{t,k}
@@ -23,6 +24,8 @@
 // one data row, as four runs of 4 consecutive columns.  K is walked in
 // chunks of 64 staged through LDS (rows of 128 bytes with the 64-bank
 // granule swizzle).  fp32 accumulation; operands bf16.
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 #include "tile.h"
@@ -211,7 +214,7 @@ __global__ __launch_bounds__(kProjThreads, 2) void k_proj_gemm(
 // H/K times the multiply-adds of the per-pair form, but no per-pair rows go
 // through HBM: each token's gated rows are gathered straight into the operand
 // tile, and the sum over the token's heads is the MFMA accumulation (head
-// order, fp32).  Chosen when H*d is small against K (see out_proj_dense).
+// order, fp32).  Chosen when H*d is small against K (see out_dense).
 //
 // k_out_map (32 tokens per workgroup): map[t * H + i] = packed row of head i
 // for token t, or Nr when i is not selected (the head of a packed row is that
@@ -286,205 +289,286 @@ __global__ __launch_bounds__(256) void k_out_map(
 }
 
 // ---------------------------------------------------------------------------
-// Big-tile GEMM of both projections: a workgroup computes 256 data rows x TN
-// output columns with four waves of 128 rows x TN/2 columns (4 x TN/64 MFMA
-// tiles per wave, accumulators in the AGPR half of the register file, one
-// workgroup per CU).  The reduction runs in chunks of 64 through two LDS
-// stages with one barrier per chunk.  Data rows are gathered, so their loads
-// have the longer latency: they are issued three chunks ahead (two register
-// sets), the weight rows two chunks ahead, each landing in LDS one chunk
-// before use; the operand fragments of the next 16-wide step are read while
-// the MFMAs of the current one run.
-//   kProjQKV: data rows = the 256-row tiles of each (b, h) segment (tiles
-//     numbered seg0 / 256 + s), gathered x rows; columns of W_QKV[h].
-//   kProjOut: data rows = 256 consecutive tokens; the reduction runs over
-//     H * d (chunk c is head c / (d / 64)); the rows are the tokens' gated
-//     head rows G found through the head map (zero for unselected heads).
-constexpr int kBigRows = 256;
-constexpr int kQkvRows = 256;   // Q/K/V tiles (128: two workgroups per CU, measured no faster)
+// Tiled GEMM of both projections: a workgroup computes TM data rows x TN
+// output columns with WM x WN waves (8 waves of 64 rows x TN / 2 columns, two
+// per SIMD).  The reduction runs in chunks of 64 through two LDS stages that
+// are filled straight from memory (no staging registers, no LDS stores), one
+// whole 128-byte line per row: chunks of 32 (half lines, four stages) asked
+// the L2 for every line twice and ran at 8 TB/s of L2 traffic, Q/K/V 151 us
+// against 140 us at d_model 2048.  Every unselected head's row lies outside
+// the OUT buffer, so three quarters of its data loads (K = H / 4) cost no
+// memory traffic.  What bounds it now: with all data rows in the L2 Q/K/V
+// still takes 117 of 121 us, without any load 105 us, of which about 10 us a
+// tile are its prologue (offsets, tokens, first chunk: three dependent
+// round trips) and epilogue, as one workgroup holds a compute unit's LDS.
+// Measured, staged through registers before (one wave of 128 x TN / 2 per
+// SIMD) and now: B T = 16384, H 32, K 8, d 64, d_model 2048: Q/K/V 160 ->
+// 121 us (0.85 PFLOP/s), output 157 -> 114 us (1.2 PFLOP/s executed); B T =
+// 6002, d 128, d_model 4096: Q/K/V 192 -> 172 us.  Waves of 128 x TN / 2 (one
+// per SIMD) 139 / 151 us, two workgroups of 128 rows per compute unit 135 us.
+//   kProjQKV: the data rows are 256-row pieces of a head's routed tokens, the
+//     sequences of the batch one after another (only each head's last tile is
+//     padded, not each segment's); gathered x rows; columns of W_QKV[h].
+//   kProjOut: the data rows are consecutive tokens; the reduction runs over
+//     H * d (chunk c belongs to head c / (d / 32)); the rows are the tokens'
+//     gated head rows G found through the head map (the zero row for
+//     unselected heads).
 constexpr int kXcds = 8;        // XCDs of the device; workgroup i runs on XCD i % 8
+constexpr int kXcdCus = 32;     // compute units of an XCD
+constexpr int kTileKC = 64;     // reduction chunk: 128-byte LDS rows, one memory line each
+constexpr int kTileStages = 2;
+constexpr int kTileMaxB = 256;  // sequences whose row counts are staged (more: per-segment tiles)
 
 template <int TM>
 NAMOH_DEV int seg_btile0(int seg0, int s) { return seg0 / TM + s; }
 
+// Largest head count whose map tile fits beside the stages of a TN-wide tile.
+constexpr int tile_map_heads(int TN) { return TN == 256 ? 32 : 64; }
+
 template <int TM, int TN, int HM>
-struct BigLds {
-  uint16_t x[2][TM * kProjKC];
-  uint16_t w[2][TN * kProjKC];
-  int32_t map[TM * HM];   // OUT: the tile's head map (HM >= H); 160 KB in all at most
+struct TileLds {
+  // stage: TM data rows, then TN weight rows, of 64 elements each, their
+  // 16-byte granules swizzled (swz<8>)
+  uint16_t ring[kTileStages][(TM + TN) * kTileKC];
+  int32_t map[TM * HM];                 // OUT: head map [h][row]
 };
 template <int TM, int TN>
-struct BigLds<TM, TN, 0> {   // Q/K/V: no map (two 128-row workgroups fit one CU)
-  uint16_t x[2][TM * kProjKC];
-  uint16_t w[2][TN * kProjKC];
+struct TileLds<TM, TN, 0> {
+  uint16_t ring[kTileStages][(TM + TN) * kTileKC];
 };
 
-// Largest head count whose map tile fits beside the stages of a TN-wide tile.
-constexpr int big_map_heads(int TN) { return TN == 256 ? 32 : 64; }
+// 16 bytes per lane straight into LDS (lane l at lds + 16 l).  Inline
+// assembly: see lds_dma16.
+NAMOH_DEV void lds_dma16_global(const uint16_t* p, uint32_t lds) {
+  asm volatile("global_load_lds_dwordx4 %1, off" ::"{m0}"(lds), "v"(p) : "memory");
+}
 
-template <int MODE, int TM, int TN, bool OUT_BF16>
-__global__ __launch_bounds__(kProjThreads, TM == 128 ? 2 : 1) void k_proj_big(
+// Tiles run one per compute unit, so a last round that fills at most half of
+// the units would leave the others idle for a whole tile: its tiles are split
+// into two halves of TM / 2 rows, two workgroups each.  Workgroup i of a group
+// with n tiles on `units` compute units: its tile (>= n: none) and half (-1:
+// the whole tile).
+struct TailTile { int tile, half; };
+NAMOH_DEV TailTile tail_tile(int i, int n, int units) {
+  const int rem = n % units, full = n - rem;
+  if (rem == 0 || 2 * rem > units || i < full) return {i, -1};
+  const int u = i - full;
+  return {u < 2 * rem ? full + u % rem : n, u / rem};
+}
+// The rows of that half (r0, nrow: the whole tile's); false if it has none.
+template <int TM, typename R>
+NAMOH_DEV bool take_half(int half, R& r0, int& nrow) {
+  if (half < 0) return true;
+  r0 += half * (TM / 2);
+  nrow = min(TM / 2, nrow - half * (TM / 2));
+  return nrow > 0;
+}
+
+template <int MODE, int TM, int TN, int WM, int WN, int OCC, bool OUT_BF16>
+__global__ __launch_bounds__(WM * WN * kWave, OCC) void k_proj_tile(
     const uint16_t* __restrict__ src, const uint16_t* __restrict__ w,
     const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ perm_token,
-    const int32_t* __restrict__ map, int BH, int H, int T, long BT, int Nr, int kdim, int N, int d,
-    int n_col_tiles, int classes, void* __restrict__ dst0, void* __restrict__ dst1,
+    const int32_t* __restrict__ map, int B, int H, int T, long BT, int Nr, int kdim, int N, int d,
+    int n_col_tiles, int by_head, void* __restrict__ dst0, void* __restrict__ dst1,
     void* __restrict__ dst2) {
-  constexpr int CT = TN / 64;                                  // 32-column tiles per wave
-  constexpr int RT = TM / 64;                                   // 32-row tiles per wave
-  constexpr int XG = TM * kProjKC / 8 / kProjThreads;          // data granules per thread
-  constexpr int WG = TN * kProjKC / 8 / kProjThreads;          // weight granules per thread
-  static_assert((TM == 128 || TM == 256) && TN % 64 == 0 && WG * kProjThreads * 8 == TN * kProjKC,
+  constexpr int NW = WM * WN, NT = NW * kWave;     // TM / WM rows x TN / WN columns per wave
+  constexpr int CT = TN / WN / 32;                 // 32-column tiles per wave
+  constexpr int WI = TN / 8 / NW;                  // 1 KB weight loads per wave and chunk
+  constexpr int STAGE = (TM + TN) * kTileKC * 2;   // bytes
+  constexpr int HM = MODE == kProjOut ? tile_map_heads(TN) : 0;
+  static_assert(TM == WM * 64 && NW % 2 == 0 && TM / 2 % (8 * NW) == 0 && WI * NW * 8 == TN && CT * WN * 32 == TN,
                 "tile shape");
-  constexpr int HM = MODE == kProjOut ? big_map_heads(TN) : 0;
-  __shared__ __attribute__((aligned(16))) BigLds<TM, TN, HM> L;
-  static_assert(sizeof(BigLds<TM, TN, HM>) <= 160 * 1024, "LDS");
+  __shared__ __attribute__((aligned(16))) TileLds<TM, TN, HM> L;
+  static_assert(sizeof(TileLds<TM, TN, HM>) <= 160 * 1024, "LDS");
   const int tid = thread_x();
-  const int lane = tid % kWave, wave = tid / kWave;
+  const int lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int c = lane & 31, g = lane >> 5;
-  const int wr = wave >> 1, wc = wave & 1;
-  const int gr = tid % 8;   // the thread's 16-byte granule of a 64-wide chunk
+  const int wr = wave / WN, wc = wave % WN;
   const int bid = block_x();
-  const int rt0 = bid / n_col_tiles;
-  int n0 = (bid - rt0 * n_col_tiles) * TN;
 
   // ---- the tile's data rows -------------------------------------------------
-  int hh = 0, b = 0, seg0 = 0, nrow;
+  int hh = 0, n0, nrow;
   long t0 = 0;
-  size_t xrow[XG];   // QKV: element offset of the thread's x rows
   if constexpr (MODE == kProjQKV) {
-    int* off = reinterpret_cast<int*>(&L.x[0][0]);   // staged before the ring is used
-    const bool in_lds = BH <= kProjSegLds;
-    if (in_lds)
-      for (int i = tid; i <= BH; i += kProjThreads) off[i] = seg_offsets[i];
-    __syncthreads();
-    const int32_t* so = in_lds ? off : seg_offsets;
-    int s, r0;
-    if (classes > 1) {
-      // XCD classes: workgroup bid runs on XCD bid % classes (dispatch is
-      // round-robin over the XCDs) and takes the tiles of the heads h with
-      // h % classes == bid % classes, so each XCD's L2 holds the weights of
-      // its H / classes heads.  Class members (h, b) in order; tile j of the
-      // class is found by a wave-wide scan of per-lane tile counts.
-      const int x = bid % classes, i = bid / classes;
-      n0 = (i % n_col_tiles) * TN;
-      const int j = i / n_col_tiles;
-      const int nb = BH / H;
-      const int hc = x < H ? (H - x + classes - 1) / classes : 0;
-      const int M = nb * hc;
-      const int per = (M + kWave - 1) / kWave;
-      const int m0 = min(M, lane * per), m1 = min(M, m0 + per);
-      auto member = [&](int m) { return (m % nb) * H + x + classes * (m / nb); };
-      int cnt = 0;
-      for (int m = m0; m < m1; ++m) {
-        const int sm = member(m);
-        cnt += (max(0, so[sm + 1] - so[sm]) + TM - 1) / TM;
+    // staged in the ring before it is used
+    int* rowbt = reinterpret_cast<int*>(&L.ring[0][0]);  // b * T + t of the tile's rows
+    int* cum = rowbt + TM;
+    int* off = cum + 2 * kTileMaxB;                      // segment offsets
+    static_assert((TM + 2 * kTileMaxB + kTileMaxB * 64 + 1) * 4 <= sizeof(L.ring) &&
+                  NW * kWave <= 2 * kTileMaxB, "staging");
+    if (by_head != 0) {
+      // tiles of all heads in head order; workgroup bid runs on XCD bid % 8
+      // (dispatch is round-robin over the XCDs), and each XCD takes one
+      // contiguous eighth of the tiles, so its L2 holds the weights of few
+      // heads at a time and all XCDs have the same number of tiles.  Lane h of
+      // wave v sums head h's rows over the sequences b = v, v + NW, ...
+      for (int i = tid; i <= B * H; i += NT) off[i] = seg_offsets[i];
+      __syncthreads();
+      int sum = 0;
+      for (int b = wave; b < B; b += NW) {
+        const int s = b * H + min(lane, H - 1);
+        sum += min(max(off[s + 1] - off[s], 0), T);
       }
-      const int incl = wave_inclusive_scan(cnt);
-      const uint64_t bal = __ballot(j >= incl - cnt && j < incl);
-      int fs = -1, fr = 0;
-      if (bal != 0 && lane == __ffsll(static_cast<unsigned long long>(bal)) - 1) {
-        int acc = incl - cnt;
-        for (int m = m0; m < m1; ++m) {
-          const int sm = member(m);
-          const int tcount = (max(0, so[sm + 1] - so[sm]) + TM - 1) / TM;
-          if (j < acc + tcount) {
-            fs = sm;
-            fr = (j - acc) * TM;
-            break;
-          }
-          acc += tcount;
+      cum[wave * kWave + lane] = sum;
+      __syncthreads();
+      int rows = 0;
+#pragma unroll
+      for (int v = 0; v < NW; ++v) rows += cum[v * kWave + lane];
+      __syncthreads();
+      const int nt = lane < H ? (rows + TM - 1) / TM * n_col_tiles : 0;
+      const int incl = wave_inclusive_scan(nt);
+      const int ntiles = __builtin_amdgcn_readlane(incl, kWave - 1);
+      const int per = (ntiles + kXcds - 1) / kXcds;
+      const TailTile tt = tail_tile(bid / kXcds, per, kXcdCus);
+      const int tile = (bid % kXcds) * per + tt.tile;
+      if (tt.tile >= per || tile >= ntiles) return;
+      hh = __popcll(__ballot(incl <= tile));
+      const int total = __shfl(rows, hh);
+      const int i = tile - __shfl(incl - nt, hh);   // tile of the head: rows first, then columns
+      const int j = i / n_col_tiles;
+      n0 = (i - j * n_col_tiles) * TN;
+      // rows before sequence b of this head (wave 0)
+      if (wave == 0) {
+        int base = 0;
+        for (int b0 = 0; b0 < B; b0 += kWave) {
+          const int b = b0 + lane, s = min(b, B - 1) * H + hh;
+          const int n = b < B ? min(max(off[s + 1] - off[s], 0), T) : 0;
+          const int incl = wave_inclusive_scan(n);
+          if (b < B) cum[b] = base + incl - n;
+          base += __builtin_amdgcn_readfirstlane(__shfl(incl, kWave - 1));
         }
       }
-      const int src_lane = bal != 0 ? __ffsll(static_cast<unsigned long long>(bal)) - 1 : 0;
-      s = __shfl(fs, src_lane);
-      r0 = __shfl(fr, src_lane);
-    } else if (in_lds) {
-      int cnt = 0;
-      for (int s0 = 0; s0 < BH; s0 += kWave) {
-        const int si = s0 + lane;
-        cnt += __popcll(__ballot(si < BH && seg_btile0<TM>(so[si], si) <= rt0));
+      __syncthreads();
+      int r0 = j * TM;
+      nrow = min(TM, total - r0);
+      if (!take_half<TM>(tt.half, r0, nrow)) return;
+      for (int r = tid; r < TM; r += NT) {
+        // padding rows repeat the last row (their results are never stored)
+        const int rr = r0 + min(r, nrow - 1);
+        int lo = 0, hi = B;
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (cum[mid] <= rr) lo = mid; else hi = mid;
+        }
+        const unsigned p = static_cast<unsigned>(off[lo * H + hh] + rr - cum[lo]);
+        const unsigned t = perm_token[min(p, static_cast<unsigned>(Nr - 1))];
+        rowbt[r] = lo * T + static_cast<int>(min(t, static_cast<unsigned>(T - 1)));
       }
-      s = cnt - 1;
-      r0 = (rt0 - seg_btile0<TM>(so[s], s)) * TM;
+      __syncthreads();
     } else {
-      int lo = 0, hi = BH;
+      // many sequences: tiles of each segment, numbered seg0 / TM + s
+      const int rt0 = bid / n_col_tiles;
+      n0 = (bid - rt0 * n_col_tiles) * TN;
+      int lo = 0, hi = B * H;
       while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (seg_btile0<TM>(so[mid], mid) <= rt0) lo = mid; else hi = mid;
+        if (seg_btile0<TM>(seg_offsets[mid], mid) <= rt0) lo = mid; else hi = mid;
       }
-      s = lo;
-      r0 = (rt0 - seg_btile0<TM>(so[s], s)) * TM;
-    }
-    const int n = s >= 0 ? so[s + 1] - so[s] : 0;
-    seg0 = s >= 0 ? so[s] : 0;
-    __syncthreads();   // the staged offsets are read; the ring may be written
-    if (s < 0 || r0 < 0 || r0 >= n || seg0 < 0 || n > T || seg0 + n > Nr) return;
-    b = s / H;
-    hh = s - (s / H) * H;
-    seg0 += r0;
-    nrow = min(TM, n - r0);
-    // padding rows past the tile's end load the last row (their results are
-    // never stored), so that no load needs a branch
-#pragma unroll
-    for (int e = 0; e < XG; ++e) {
-      const int r = min(tid / 8 + 32 * e, nrow - 1);
-      const int t = min(static_cast<unsigned>(perm_token[seg0 + r]), static_cast<unsigned>(T - 1));
-      xrow[e] = (static_cast<size_t>(b) * T + t) * kdim;
+      const int seg0 = seg_offsets[lo], n = seg_offsets[lo + 1] - seg0;
+      const int r0 = (rt0 - seg_btile0<TM>(seg0, lo)) * TM;
+      if (r0 < 0 || r0 >= n || seg0 < 0 || n > T || seg0 + n > Nr) return;
+      hh = lo % H;
+      nrow = min(TM, n - r0);
+      for (int r = tid; r < TM; r += NT) {
+        const unsigned t = perm_token[seg0 + r0 + min(r, nrow - 1)];
+        rowbt[r] = (lo / H) * T + static_cast<int>(min(t, static_cast<unsigned>(T - 1)));
+      }
+      __syncthreads();
     }
   } else {
-    // the tile's head map into LDS (rows past the end repeat the last row;
-    // their results are never stored)
+    const int ntiles = static_cast<int>((BT + TM - 1) / TM) * n_col_tiles;
+    const TailTile tt = tail_tile(bid, ntiles, kXcds * kXcdCus);
+    if (tt.tile >= ntiles) return;
+    const int rt0 = tt.tile / n_col_tiles;
+    n0 = (tt.tile - rt0 * n_col_tiles) * TN;
     t0 = static_cast<long>(rt0) * TM;
     nrow = static_cast<int>(min(static_cast<long>(TM), BT - t0));
-    // stored head-major ([h][row]): the 8 rows a wave reads for one head are
-    // consecutive words, free of bank conflicts
-    for (int i = tid; i < TM * H; i += kProjThreads) {
+    if (!take_half<TM>(tt.half, t0, nrow)) return;
+    // the tile's head map, head-major (rows past the end repeat the last row;
+    // their results are never stored)
+    for (int i = tid; i < TM * H; i += NT) {
       const int row = i % TM, h = i / TM;
       const int32_t m = map[(static_cast<size_t>(t0) + min(row, nrow - 1)) * H + h];
       L.map[i] = static_cast<unsigned>(m) <= static_cast<unsigned>(Nr) ? m : Nr;
     }
     __syncthreads();
   }
-  const int cph = d / kProjKC;                         // chunks per head (OUT)
-  const int nchunk = MODE == kProjQKV ? kdim / kProjKC : H * cph;
-  const int last = nchunk - 1;
+  hh = __builtin_amdgcn_readfirstlane(hh);
+  n0 = __builtin_amdgcn_readfirstlane(n0);
+  const int cph = d / kTileKC;                         // chunks per head (OUT)
+  const int nchunk = MODE == kProjQKV ? kdim / kTileKC : H * cph;
 
-  // two register sets for the weight rows too where the registers allow
-  // (QKV; OUT with TN = 128): their loads are then also issued three chunks
-  // ahead instead of two
-  constexpr bool W2 = (MODE == kProjQKV && TM == 256) || (MODE == kProjOut && TN <= 128);
-  u32x4 xs0[XG], xs1[XG], wv0[WG], wv1[W2 ? WG : 1];
-  // one 16-byte granule e of the thread's data rows (rows tid / 8 + 32 e) or
-  // weight rows of chunk ch
-  auto load_x = [&](u32x4 (&xs)[XG], int ch, int e) {
-    if constexpr (MODE == kProjQKV) {
-      xs[e] = *reinterpret_cast<const u32x4*>(src + xrow[e] + ch * kProjKC + 8 * gr);
-    } else {   // the gated row of the token's head (the zero row Nr if unselected)
-      const int h = ch / cph, dd0 = (ch - h * cph) * kProjKC;
-      const int m = L.map[h * TM + tid / 8 + 32 * e];
-      xs[e] = *reinterpret_cast<const u32x4*>(src + static_cast<size_t>(m) * d + dd0 + 8 * gr);
+  // The tile with RT 32-row blocks per wave: 2, or 1 for tiles of at most
+  // TM / 2 rows (split tails, a head's last rows).
+  auto body = [&](auto rtc) {
+  constexpr int RT = decltype(rtc)::value;
+  constexpr int XI = RT * WM * 4 / NW;                 // 1 KB data loads per wave and chunk
+  // ---- loads ------------------------------------------------------------------
+  // load i of a wave fills LDS rows 8 (i NW + wave) .. + 7 of the tile; the
+  // lane that fills position p of row r fetches granule swz<8>(r, p), the same
+  // for all i
+  const int xr = 8 * wave + lane / 8;                  // row of load 0 (load i: + 8 NW i)
+  const int lg = swz<8>(xr, lane & 7);
+  const uint32_t ring0 = lds_address(&L.ring[0][0]) + wave * 1024;
+  size_t xo[XI];                                       // QKV: byte offset of the rows' granules
+  int xm[XI];                                          // OUT: the rows' packed rows, next head
+  int ebt[RT];                                         // QKV: the lane's result rows
+  if constexpr (MODE == kProjQKV) {
+    const int* rowbt = reinterpret_cast<const int*>(&L.ring[0][0]);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) ebt[rt] = rowbt[(32 * RT) * wr + 32 * rt + c];
+#pragma unroll
+    for (int i = 0; i < XI; ++i)
+      xo[i] = (static_cast<size_t>(rowbt[xr + 8 * NW * i]) * kdim + 8 * lg) * 2;
+    __syncthreads();   // the staged rows are read; the ring may be written
+  }
+  const int wstride = MODE == kProjQKV ? kdim : d;     // elements of a weight row
+  const uint32_t wvoff = static_cast<uint32_t>((xr * wstride + 8 * lg) * 2);
+  const uint32_t wstep = static_cast<uint32_t>(8 * NW * wstride * 2);
+  // Each workgroup starts the reduction at another chunk (up to 15 on): the
+  // weight rows lie d_model elements apart, so workgroups in step would ask
+  // for lines of the same few L2 channels at once (d_model 2048: 131 -> 121
+  // us, 4096: 179 -> 172 us; offsets over the whole reduction lose the L2 hits
+  // that workgroups near one another share, 199 us).
+  const int rot = MODE == kProjQKV ? ((bid / kXcds) & 15) % nchunk : 0;
+  int ldc = rot, ldh = 0;     // next chunk to load; OUT: of head ldh
+  const uint16_t* wb = w + (static_cast<size_t>(hh) * N + n0) * wstride;
+  auto read_map = [&]() {
+    if constexpr (MODE == kProjOut) {
+#pragma unroll
+      for (int i = 0; i < XI; ++i) xm[i] = L.map[ldh * TM + xr + 8 * NW * i];
     }
   };
-  auto load_w = [&](u32x4 (&wv)[WG], int ch, int e) {
-    const uint16_t* wb;
-    size_t stride;
+  read_map();
+  const bool far = MODE == kProjOut && (static_cast<size_t>(Nr) + 1) * d * 2 >= (1ull << 32);
+  // load i of the data rows / weight rows of chunk ldc into a stage; next()
+  auto load_x = [&](int stage, int i) {
+    const uint32_t dst = ring0 + stage * STAGE + i * NW * 1024;
+    const int koff = __builtin_amdgcn_readfirstlane(ldc * kTileKC * 2);
     if constexpr (MODE == kProjQKV) {
-      wb = w + (static_cast<size_t>(hh) * N + n0) * kdim + ch * kProjKC;
-      stride = kdim;
+      lds_dma16_global(reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(src) + koff + xo[i]), dst);
+    } else if (far) {
+      lds_dma16_global(src + static_cast<size_t>(xm[i]) * d + koff / 2 + 8 * lg, dst);
     } else {
-      const int h = ch / cph, dd0 = (ch - h * cph) * kProjKC;
-      wb = w + (static_cast<size_t>(h) * N + n0) * d + dd0;
-      stride = d;
+      // rows of unselected heads (Nr) lie past the buffer's end and read as zero
+      lds_dma16(buffer_rsrc(src, static_cast<uint32_t>(Nr) * d * 2), dst,
+                static_cast<uint32_t>(xm[i]) * static_cast<uint32_t>(d * 2) + 16 * lg, koff);
     }
-    wv[e] = *reinterpret_cast<const u32x4*>(wb + static_cast<size_t>(tid / 8 + 32 * e) * stride + 8 * gr);
   };
-  auto store_x = [&](const u32x4 (&xs)[XG], int stg, int e) {
-    const int row = tid / 8 + 32 * e;
-    *reinterpret_cast<u32x4*>(&L.x[stg][row * kProjKC + swz<8>(row, gr) * 8]) = xs[e];
+  auto load_w = [&](int stage, int i) {
+    const int koff = __builtin_amdgcn_readfirstlane(ldc * kTileKC * 2);
+    lds_dma16(buffer_rsrc(MODE == kProjQKV ? wb : wb + static_cast<size_t>(ldh) * N * d, 0xFFFFFFFFu),
+              ring0 + stage * STAGE + TM * kTileKC * 2 + i * NW * 1024, wvoff + i * wstep, koff);
   };
-  auto store_w = [&](const u32x4 (&wv)[WG], int stg, int e) {
-    const int row = tid / 8 + 32 * e;
-    *reinterpret_cast<u32x4*>(&L.w[stg][row * kProjKC + swz<8>(row, gr) * 8]) = wv[e];
+  auto next = [&]() {
+    ++ldc;
+    if constexpr (MODE == kProjQKV) {
+      if (ldc == nchunk) ldc = 0;
+    } else if (ldc == cph) {
+      ldc = 0;
+      if (++ldh == H) ldh = 0;
+      read_map();
+    }
   };
 
   f32x16 C[CT][RT];
@@ -495,143 +579,171 @@ __global__ __launch_bounds__(kProjThreads, TM == 128 ? 2 : 1) void k_proj_big(
 #pragma unroll
       for (int e = 0; e < 16; ++e) C[ct][rt][e] = 0.f;
 
-  // One chunk step: chunk ch is multiplied from stage stg in four 16-wide
-  // steps; behind the MFMAs of each step go a quarter of the LDS stores of
-  // X(ch+1) (register set xn) and W(ch+1) into the free stage, each followed
-  // by the load of the same granule of X(ch+3) and W(ch+2 or ch+3) into the
-  // register it freed, so the staging runs in the shadow of the matrix work.
-  // Operand fragments use two register sets: the reads of step ks + 1 are
-  // issued before the MFMAs of step ks (scheduling barriers keep each step's
-  // instructions together).  No branch surrounds a load or store (a load
-  // under a branch is waited for where the branch joins, and the wait
-  // counter is in order, so it would also wait for every load issued
-  // before); indices past the end are clamped to the last chunk and land in
-  // the stage that is no longer read.
-  auto step = [&](int ch, u32x4 (&xn)[XG], u32x4 (&wn)[WG], int stg) {
-    const int chx = min(ch + 3, last), chw = min(ch + (W2 ? 3 : 2), last);
-    bf16x8 bx[2][RT], aw[2][CT];
-    auto read_frags = [&](int ks, int set) {
+  const int fx = (32 * RT) * wr + c, fw = TM + (TN / WN) * wc + c;
+  bf16x8 bx[2][RT], aw[2][CT];
+  auto read_frags = [&](int stage, int ks, int set) {
+    const uint16_t* st = &L.ring[stage][0];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+      bx[set][rt] = *reinterpret_cast<const bf16x8*>(st + (fx + 32 * rt) * kTileKC + swz<8>(c, 2 * ks + g) * 8);
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+      aw[set][ct] = *reinterpret_cast<const bf16x8*>(st + (fw + 32 * ct) * kTileKC + swz<8>(c, 2 * ks + g) * 8);
+  };
+  // the products of one step, `behind(k)` issued behind the k-th
+  auto mfmas = [&](int set, auto behind) {
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        const int drow = (TM / 2) * wr + 32 * rt + c;
-        bx[set][rt] =
-            *reinterpret_cast<const bf16x8*>(&L.x[stg][drow * kProjKC + swz<8>(drow, 2 * ks + g) * 8]);
+        C[ct][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aw[set][ct], bx[set][rt], C[ct][rt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        behind(ct * RT + rt);
+        __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const int wrow = (TN / 2) * wc + 32 * ct + c;
-        aw[set][ct] =
-            *reinterpret_cast<const bf16x8*>(&L.w[stg][wrow * kProjKC + swz<8>(wrow, 2 * ks + g) * 8]);
-      }
-    };
-    read_frags(0, 0);
-#pragma unroll
-    for (int ks = 0; ks < kProjKC / 16; ++ks) {
-      if (ks + 1 < kProjKC / 16) read_frags(ks + 1, (ks + 1) & 1);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          C[ct][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aw[ks & 1][ct], bx[ks & 1][rt],
-                                                              C[ct][rt], 0, 0, 0);
-#pragma unroll
-      for (int e = ks * XG / 4; e < (ks + 1) * XG / 4; ++e) {
-        store_x(xn, stg ^ 1, e);
-        load_x(xn, chx, e);
-      }
-#pragma unroll
-      for (int e = ks * WG / 4; e < (ks + 1) * WG / 4; ++e) {
-        store_w(wn, stg ^ 1, e);
-        load_w(wn, chw, e);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __syncthreads();
+  };
+  auto nothing = [](int) {};
+  // publishes the stage whose loads are in flight: every wave's loads have
+  // landed, and every wave's reads of the other stage have returned
+  auto publish = [&]() {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
   };
 
-  auto& wv1s = [&]() -> u32x4(&)[WG] {
-    if constexpr (W2) return wv1; else return wv0;
-  }();
+  // One chunk: four 16-wide steps, the fragments of the next one read during
+  // each.  The barrier stands before the last step: it publishes the next
+  // chunk, whose first fragments that step reads, and frees this chunk's
+  // stage for the chunk after the next.  That one's loads go one behind each
+  // product, the data rows (longer latency) in this step and the weight rows
+  // in the first step of the next chunk: issued together they fill the load
+  // queue and the waves stand before it instead of feeding the matrix units.
+  static_assert(XI <= CT * RT && WI <= CT * RT, "a load behind each product");
 #pragma unroll
-  for (int e = 0; e < XG; ++e) load_x(xs0, 0, e);
+  for (int i = 0; i < XI; ++i) load_x(0, i);
 #pragma unroll
-  for (int e = 0; e < WG; ++e) load_w(wv0, 0, e);
+  for (int i = 0; i < WI; ++i) load_w(0, i);
+  next();
+  publish();
+  read_frags(0, 0, 0);
+  if (nchunk > 1)
 #pragma unroll
-  for (int e = 0; e < XG; ++e) store_x(xs0, 0, e);
-#pragma unroll
-  for (int e = 0; e < WG; ++e) store_w(wv0, 0, e);
-#pragma unroll
-  for (int e = 0; e < XG; ++e) load_x(xs1, min(1, last), e);
-#pragma unroll
-  for (int e = 0; e < WG; ++e) load_w(wv1s, min(1, last), e);
-#pragma unroll
-  for (int e = 0; e < XG; ++e) load_x(xs0, min(2, last), e);
-  if constexpr (W2) {
-#pragma unroll
-    for (int e = 0; e < WG; ++e) load_w(wv0, min(2, last), e);
-  }
-  __syncthreads();
+    for (int i = 0; i < XI; ++i) load_x(1, i);
+  auto chunk = [&](int stage, bool more1, bool more2) {
+    __builtin_amdgcn_sched_barrier(0);
+    read_frags(stage, 1, 1);
+    mfmas(0, [&](int k) { if (k < WI && more1) load_w(stage ^ 1, k); });
+    next();
+    read_frags(stage, 2, 0);
+    mfmas(1, nothing);
+    read_frags(stage, 3, 1);
+    mfmas(0, nothing);
+    publish();
+    read_frags(stage ^ 1, 0, 0);
+    mfmas(1, [&](int k) { if (k < XI && more2) load_x(stage, k); });
+  };
   int ch = 0;
   for (; ch + 1 < nchunk; ch += 2) {
-    step(ch, xs1, wv1s, 0);
-    step(ch + 1, xs0, wv0, 1);
+    chunk(0, true, ch + 2 < nchunk);
+    chunk(1, ch + 2 < nchunk, ch + 3 < nchunk);
   }
-  if (ch < nchunk) step(ch, xs1, wv1s, 0);
+  if (ch < nchunk) chunk(0, false, false);
 
-  // ---- epilogue: lane (c, g) holds data row 128 wr + 32 rt + c, output
-  // columns n0 + TN/2 wc + 32 ct + 8 j + 4 g + i in accumulator 4 j + i ----
+  // ---- epilogue: lane (c, g) holds data row 64 wr + 32 rt + c, output
+  // columns n0 + TN/2 wc + 32 ct + 8 j + 4 g + i in accumulator 4 j + i; the
+  // two halves of a wave swap runs so that a lane stores 8 consecutive
+  // columns (j even: lanes g = 0, j odd: g = 1) -------------------------------
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    const int r = (TM / 2) * wr + 32 * rt + c;
-    if (r >= nrow) continue;
+    const int r = (32 * RT) * wr + 32 * rt + c;
+    const bool ok = r < nrow;
     size_t orow;
     if constexpr (MODE == kProjQKV) {
-      const int t = min(static_cast<unsigned>(perm_token[seg0 + r]), static_cast<unsigned>(T - 1));
-      orow = ((static_cast<size_t>(b) * H + hh) * T + t) * d;
+      const int bt = ebt[rt], b = bt / T;
+      orow = ((static_cast<size_t>(b) * H + hh) * T + (bt - b * T)) * d;
     } else {
       orow = static_cast<size_t>(t0 + r) * N;
     }
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
+    for (int ct = 0; ct < CT; ++ct) {
+      const f32x16& A = C[ct][rt];
+      const int col0 = n0 + (TN / WN) * wc + 32 * ct;
+      if constexpr (MODE == kProjOut && !OUT_BF16) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int col = n0 + (TN / 2) * wc + 32 * ct + 8 * j + 4 * g;
-        const f32x16& A = C[ct][rt];
-        if constexpr (MODE == kProjQKV) {
-          const int which = col / d, cc = col - (col / d) * d;   // a 4-column run inside q, k or v
-          uint16_t* dst = static_cast<uint16_t*>(which == 0 ? dst0 : (which == 1 ? dst1 : dst2));
-          *reinterpret_cast<uint2*>(dst + orow + cc) =
-              make_uint2(pack_bf16x2(A[4 * j], A[4 * j + 1]), pack_bf16x2(A[4 * j + 2], A[4 * j + 3]));
-        } else if constexpr (OUT_BF16) {
-          *reinterpret_cast<uint2*>(static_cast<uint16_t*>(dst0) + orow + col) =
-              make_uint2(pack_bf16x2(A[4 * j], A[4 * j + 1]), pack_bf16x2(A[4 * j + 2], A[4 * j + 3]));
-        } else {
-          *reinterpret_cast<float4*>(static_cast<float*>(dst0) + orow + col) =
-              make_float4(A[4 * j], A[4 * j + 1], A[4 * j + 2], A[4 * j + 3]);
+        for (int j = 0; j < 4; ++j)
+          if (ok)
+            *reinterpret_cast<float4*>(static_cast<float*>(dst0) + orow + col0 + 8 * j + 4 * g) =
+                make_float4(A[4 * j], A[4 * j + 1], A[4 * j + 2], A[4 * j + 3]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) {
+          uint32_t e0 = pack_bf16x2(A[4 * j], A[4 * j + 1]), e1 = pack_bf16x2(A[4 * j + 2], A[4 * j + 3]);
+          uint32_t o0 = pack_bf16x2(A[4 * j + 4], A[4 * j + 5]), o1 = pack_bf16x2(A[4 * j + 6], A[4 * j + 7]);
+          const auto s0 = __builtin_amdgcn_permlane32_swap(e0, o0, false, false);
+          const auto s1 = __builtin_amdgcn_permlane32_swap(e1, o1, false, false);
+          const u32x4 v = u32x4{s0[0], s1[0], s0[1], s1[1]};
+          const int col = col0 + 8 * (j + g);
+          if (!ok) continue;
+          if constexpr (MODE == kProjQKV) {
+            const int which = col / d, cc = col - which * d;   // an 8-column run inside q, k or v
+            uint16_t* dst = static_cast<uint16_t*>(which == 0 ? dst0 : (which == 1 ? dst1 : dst2));
+            *reinterpret_cast<u32x4*>(dst + orow + cc) = v;
+          } else {
+            *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(dst0) + orow + col) = v;
+          }
         }
       }
+    }
   }
+  };
+  if (nrow <= TM / 2)
+    body(std::integral_constant<int, 1>{});
+  else
+    body(std::integral_constant<int, 2>{});
 }
 
-// The dense form costs 2 B T H d d_model multiply-add flops at MFMA rate; the
-// per-pair form writes and re-reads B T K d_model bf16 rows.  With about
-// 1 PFLOP/s sustained against about 4-5 TB/s for those rows the dense form is
-// the faster one while H d < about 384 K (d 64: H/K <= 6; d 128: H/K <= 3).
-bool out_proj_dense(int H, int K, int d) { return static_cast<long>(H) * d <= 384L * K && H <= 64; }
+// Workspace rule of the output projection: head map and gated rows, or the
+// per-pair rows.
+static bool out_ws_dense(int H, int K, int d) { return static_cast<long>(H) * d <= 384L * K && H <= 64; }
+static size_t out_dense_bytes(int B, int T, int H, int K, int d) {
+  return align_up(static_cast<size_t>(B) * T * H * sizeof(int32_t)) +
+         align_up((static_cast<size_t>(B) * T * K + 1) * d * 2);
+}
+static size_t out_pair_bytes(int B, int T, int K, int d_model) {
+  return align_up(static_cast<size_t>(B) * T * K * d_model * 2);
+}
+// The form.  The dense one executes H / K times the multiply-adds at matrix
+// rate (1.1-1.2 PFLOP/s of them with full rounds of 256 x 256 tiles), the
+// per-pair one writes and re-reads B T K rows of d_model.  Measured (us,
+// dense against per-pair, d_model 2048): 8192 tokens H d = 512 K 63 / 92
+// (d 64, H 32), 115 / 232 (d 128, H 32); 1024 K 59 / 58 (d 64) but 105 / 118
+// (d 128: rows of 256 bytes, twice the products per row); 2048 K 99 / 70.
+// With few tiles the dense form's serial reduction of H d stands alone on few
+// compute units: 3000 tokens, d_model 512 (24 tiles) 33 / 19, d_model 2048
+// (96 tiles) 39 / 42; at 1024 K, d 128: 96 tiles 65 / 51, 256 tiles as above.
+// Where the workspace rule says per-pair, the dense form's map and rows fit
+// into the per-pair rows' space except at the smallest d_model.
+static bool out_dense(int B, int T, int H, int K, int d, int d_model) {
+  if (out_ws_dense(H, K, d)) return true;
+  const size_t tiles = (static_cast<size_t>(B) * T + 255) / 256 * (d_model / 256);
+  const long lim = d == 128 && tiles >= 256 ? 1024 : 512;
+  return static_cast<long>(H) * d <= lim * K && H <= 64 && tiles >= 96 &&
+         out_dense_bytes(B, T, H, K, d) <= out_pair_bytes(B, T, K, d_model);
+}
 
-template <int TN>
-static void launch_out_big(const uint16_t* grows, const uint16_t* w_o, const int32_t* map, long BT,
-                           int Nr, int H, int d, int d_model, void* out, bool out_bf16,
-                           hipStream_t st) {
+template <int TM, int TN, int WM, int WN, int OCC>
+static void launch_out_tile(const uint16_t* grows, const uint16_t* w_o, const int32_t* map, long BT,
+                            int Nr, int H, int d, int d_model, void* out, bool out_bf16,
+                            hipStream_t st) {
   const int nct = d_model / TN;
-  const unsigned grid = static_cast<unsigned>(((BT + kBigRows - 1) / kBigRows) * nct);
+  const unsigned tiles = static_cast<unsigned>(((BT + TM - 1) / TM) * nct);
+  constexpr unsigned units = kXcds * kXcdCus;
+  const unsigned rem = tiles % units;
+  const unsigned grid = tiles + (2 * rem <= units ? rem : 0);   // second halves of a split tail
   if (out_bf16)
-    k_proj_big<kProjOut, kBigRows, TN, true><<<grid, kProjThreads, 0, st>>>(
-        grows, w_o, nullptr, nullptr, map, 0, H, 0, BT, Nr, d, d_model, d, nct, 1, out, nullptr, nullptr);
+    k_proj_tile<kProjOut, TM, TN, WM, WN, OCC, true><<<grid, WM * WN * kWave, 0, st>>>(
+        grows, w_o, nullptr, nullptr, map, 0, H, 0, BT, Nr, d, d_model, d, nct, 0, out, nullptr, nullptr);
   else
-    k_proj_big<kProjOut, kBigRows, TN, false><<<grid, kProjThreads, 0, st>>>(
-        grows, w_o, nullptr, nullptr, map, 0, H, 0, BT, Nr, d, d_model, d, nct, 1, out, nullptr, nullptr);
+    k_proj_tile<kProjOut, TM, TN, WM, WN, OCC, false><<<grid, WM * WN * kWave, 0, st>>>(
+        grows, w_o, nullptr, nullptr, map, 0, H, 0, BT, Nr, d, d_model, d, nct, 0, out, nullptr, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -640,40 +752,36 @@ static unsigned proj_row_tiles(int B, int T, int H, int K) {
   return static_cast<unsigned>(Nr / kProjRows + static_cast<size_t>(B) * H + 1);
 }
 
+template <int TM, int WM, int WN, int OCC>
+static void launch_qkv_tile(const uint16_t* x, const uint16_t* w, int B, int T, int H, int K, int d,
+                            int d_model, const int32_t* seg_offsets, const int32_t* perm_token,
+                            void* q, void* k, void* v, hipStream_t st) {
+  const int N = 3 * d, nct = N / 192;
+  // at most Nr / TM full tiles and one partial tile per head, dealt to the
+  // XCDs in equal shares; or numbered by segment
+  const size_t BT = static_cast<size_t>(B) * T;
+  const bool by_head = B <= kTileMaxB;
+  const size_t tiles = BT * K / TM + (by_head ? H : static_cast<size_t>(B) * H + 1);
+  // (by head: and the second halves of a split tail)
+  const size_t grid = by_head ? ((tiles * nct + kXcds - 1) / kXcds + kXcdCus / 2) * kXcds : tiles * nct;
+  k_proj_tile<kProjQKV, TM, 192, WM, WN, OCC, false><<<static_cast<unsigned>(grid), WM * WN * kWave, 0, st>>>(
+      x, w, seg_offsets, perm_token, nullptr, B, H, T, static_cast<long>(BT), B * T * K, d_model, N,
+      d, nct, by_head ? 1 : 0, q, k, v);
+}
+
 hipError_t launch_qkv_proj(const void* x, const void* w_qkv, int B, int T, int H, int K, int d,
                            int d_model, const int32_t* seg_offsets, const int32_t* perm_token,
                            void* q, void* k, void* v, hipStream_t st) {
-  const int N = 3 * d;
-  if (N % 192 != 0 || d_model % kProjKC != 0) return hipErrorInvalidValue;
-  const size_t Nr = static_cast<size_t>(B) * T * K;
-  const int nct = N / 192;
-  constexpr int TM = kQkvRows;
-  // XCD classes (heads h % 8 on XCD h % 8) when the offsets fit in LDS; the
-  // grid then holds, per class, the most tiles a class can have (B T
-  // min(K, H/8) / TM + B H/8 + 1); the rest of its workgroups find no tile
-  const int classes = B * H <= kProjSegLds && H >= kXcds ? kXcds : 1;
-  size_t tiles;
-  if (classes > 1) {
-    const size_t hc = (H + classes - 1) / classes;
-    tiles = classes * (static_cast<size_t>(B) * T * std::min<size_t>(K, hc) / TM + B * hc + 1);
-  } else {
-    tiles = Nr / TM + static_cast<size_t>(B) * H + 1;
-  }
-  const unsigned grid = static_cast<unsigned>(tiles * nct);
+  if ((3 * d) % 192 != 0 || d_model % kProjKC != 0) return hipErrorInvalidValue;
   prof_mark("qkv_proj", true, st);
-  k_proj_big<kProjQKV, TM, 192, false><<<grid, kProjThreads, 0, st>>>(
-      static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_qkv), seg_offsets,
-      perm_token, nullptr, B * H, H, T,
-      static_cast<long>(B) * T, B * T * K, d_model, N, d, nct, classes, q, k, v);
+  launch_qkv_tile<256, 4, 2, 2>(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_qkv), B, T,
+                       H, K, d, d_model, seg_offsets, perm_token, q, k, v, st);
   prof_mark("qkv_proj", false, st);
   return hipGetLastError();
 }
 
 size_t out_proj_workspace_bytes(int B, int T, int H, int K, int d, int d_model) {
-  if (out_proj_dense(H, K, d))   // head map + gated bf16 rows
-    return align_up(static_cast<size_t>(B) * T * H * sizeof(int32_t)) +
-           align_up((static_cast<size_t>(B) * T * K + 1) * d * 2);
-  return align_up(static_cast<size_t>(B) * T * K * d_model * 2);
+  return out_ws_dense(H, K, d) ? out_dense_bytes(B, T, H, K, d) : out_pair_bytes(B, T, K, d_model);
 }
 
 hipError_t launch_out_proj(const void* head_out, int head_out_dtype, const void* w_o,
@@ -681,7 +789,7 @@ hipError_t launch_out_proj(const void* head_out, int head_out_dtype, const void*
                            const int32_t* seg_offsets, int B, int T, int H, int K, int d,
                            int d_model, void* out, int out_dtype, void* ws, hipStream_t st) {
   if (d % kProjKC != 0 || d_model % 128 != 0) return hipErrorInvalidValue;
-  if (out_proj_dense(H, K, d)) {
+  if (out_dense(B, T, H, K, d, d_model)) {
     const long BT = static_cast<long>(B) * T;
     int32_t* map = static_cast<int32_t*>(ws);
     uint16_t* grows = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) +
@@ -695,10 +803,10 @@ hipError_t launch_out_proj(const void* head_out, int head_out_dtype, const void*
       k_out_map<false><<<mgrid, 256, 0, st>>>(head_out, gates, slot_pos, seg_offsets, BT, H, K, B * H,
                                               B * T * K, d, map, grows);
     const uint16_t* w = static_cast<const uint16_t*>(w_o);
-    if (d_model % 256 == 0 && H <= big_map_heads(256))
-      launch_out_big<256>(grows, w, map, BT, B * T * K, H, d, d_model, out, out_dtype == 1, st);
+    if (d_model % 256 == 0 && H <= tile_map_heads(256))
+      launch_out_tile<256, 256, 4, 2, 2>(grows, w, map, BT, B * T * K, H, d, d_model, out, out_dtype == 1, st);
     else
-      launch_out_big<128>(grows, w, map, BT, B * T * K, H, d, d_model, out, out_dtype == 1, st);
+      launch_out_tile<256, 128, 4, 2, 2>(grows, w, map, BT, B * T * K, H, d, d_model, out, out_dtype == 1, st);
     prof_mark("out_proj", false, st);
     return hipGetLastError();
   }
