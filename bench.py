@@ -176,7 +176,7 @@ def bench_prefill(w, args, torch, L, DI):
     mfma = w.dtype == "bf16" and d in (64, 128)
     peak = PEAK_BF16_TFLOPS if mfma else PEAK_FP32_TFLOPS
     achieved = flops / (attn_ms * 1e-3) / 1e12
-    roof = {"kernel": "k_attn_mfma" if mfma else "k_attn_generic",
+    roof = {"kernel": "k_attn_mfma" if mfma else "k_f32_attn",
             "bound": "mfma" if mfma else "alu", "achieved": round(achieved, 2), "peak": peak,
             "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
             "traffic": traffic_entry("k_attn_mfma", w.name, None),
@@ -574,7 +574,7 @@ def bench_backward(w, args, torch, L, DI):
                       "forward_state": "saved by the training forward" if mfma else "recomputed",
                       "rope": "head-relative",
                       "rope_base": w.rope_base, "gates": "softmax over selected"},
-           "roofline": {"kernel": "k_bwd_dq + k_bwd_dkdv" if mfma else "k_bwd_q + k_bwd_kv",
+           "roofline": {"kernel": "k_bwd_dq + k_bwd_dkdv" if mfma else "k_f32_bwd_q + k_f32_bwd_kv",
                         "bound": "mfma" if mfma else "alu", "achieved": round(achieved, 2),
                         "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                         "traffic": None,

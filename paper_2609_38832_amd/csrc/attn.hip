@@ -26,10 +26,8 @@
 //                 through a ring of LDS stages; S^T = K Q^T and O^T += V^T P^T
 //                 run on v_mfma_f32_32x32x16_bf16 with fp32 accumulation and
 //                 an fp32 online softmax (exp2).
-//   other dtype / width:
-//     k_attn_schedule  the work list alone.
-//     k_attn_generic  fp32 arithmetic, one lane per query, keys gathered and
-//                 rotated while staging each tile.
+//   other dtype / width: k_f32_attn (f32.hip), keys gathered and rotated by
+//     the table while staging each tile.
 //   k_combine     o_t = sum_k gate(t,k) * h[slot_pos(t,k)] in k order.
 #include <cmath>
 
@@ -59,7 +57,7 @@ template <> struct MfmaShape<128> {
 // 2^kLazyLog2 and the final normalisation is exact), so the output
 // accumulator is rarely rescaled.
 constexpr float kLazyLog2 = 8.f;
-constexpr int kGenericBM = 64;
+constexpr int kGenericBM = 64;   // (the float32 path's share of the workspace)
 
 constexpr int kPackThreads = 256;
 
@@ -87,15 +85,6 @@ __global__ __launch_bounds__(kTableThreads) void k_rope_table(int T, int d, doub
       table[i] = rope_cos_sin(static_cast<double>(p) * s_theta[j]);
     }
   }
-}
-
-// The schedule on its own (paths without the packing kernel, which otherwise
-// builds it in its workgroup 0).
-__global__ __launch_bounds__(kPackThreads) void k_attn_schedule(
-    const int32_t* __restrict__ seg_offsets, int BH, int T, int BM, int Nr, int max_items,
-    int period, WorkItem* __restrict__ items, int32_t* __restrict__ meta) {
-  __shared__ SchedLds L;
-  attn_schedule<kPackThreads>(seg_offsets, BH, T, BM, Nr, max_items, period, 1, items, meta, L);
 }
 
 // ---------------------------------------------------------------------------
@@ -912,113 +901,6 @@ __global__ __launch_bounds__(kMergeThreads) void k_attn_merge(
 }
 
 // ---------------------------------------------------------------------------
-// fp32-arithmetic attention for every other dtype / head width: one lane per
-// query, keys gathered by perm_token and rotated while each tile is staged.
-template <int D, bool BF16>
-NAMOH_DEV void load_row(const void* base, size_t row, float* out) {
-  if constexpr (BF16) {
-    const uint4* p = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(base) + row * D);
-#pragma unroll
-    for (int i = 0; i < D / 8; ++i) unpack8(p[i], out + 8 * i);
-  } else {
-    const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(base) + row * D);
-#pragma unroll
-    for (int i = 0; i < D / 4; ++i) {
-      const float4 x = p[i];
-      out[4 * i] = x.x; out[4 * i + 1] = x.y; out[4 * i + 2] = x.z; out[4 * i + 3] = x.w;
-    }
-  }
-}
-
-template <int D>
-NAMOH_DEV void rope_row(float* x, const float2* __restrict__ cs) {
-#pragma unroll
-  for (int j = 0; j < D / 2; ++j) {
-    const float2 w = cs[j];
-    const float a = x[j], bb = x[j + D / 2];
-    x[j] = a * w.x - bb * w.y;
-    x[j + D / 2] = bb * w.x + a * w.y;
-  }
-}
-
-template <int D, bool BF16>
-__global__ __launch_bounds__(64) void k_attn_generic(
-    const void* __restrict__ q, const void* __restrict__ k,
-    const void* __restrict__ v, const float2* __restrict__ table,
-    const int32_t* __restrict__ perm_token, const WorkItem* __restrict__ items,
-    const int32_t* __restrict__ meta, int T, int H, int rope_mode, float scale,
-    float* __restrict__ hout) {
-  __shared__ float sK[kBN][D + 1];
-  __shared__ float sV[kBN][D + 1];
-  WorkItem it;
-  if (!my_item(items, meta, it)) return;
-  const int s = it.s;
-  const int q0 = it.qb * kGenericBM;
-  const int b = s / H, h = s - (s / H) * H;
-  const int seg0 = it.seg0;
-  const int n = it.n;
-  const size_t head_base = (static_cast<size_t>(b) * H + h) * T;
-  const int lane = thread_x();
-  const int r = q0 + lane;
-
-  float qv[D], acc[D], row[D];
-  {
-    const int rr = r < n ? r : n - 1;
-    const int t = min(static_cast<unsigned>(perm_token[seg0 + rr]), static_cast<unsigned>(T - 1));
-    load_row<D, BF16>(q, head_base + t, qv);
-    if (rope_mode != 2)
-      rope_row<D>(qv, table + static_cast<size_t>(rope_mode == 0 ? rr : t) * (D / 2));
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      qv[d] *= scale;
-      acc[d] = 0.f;
-    }
-  }
-  float m = -INFINITY, l = 0.f;
-  const int ntiles = (n + kBN - 1) / kBN;
-  const int kt_end = min(ntiles, (q0 + kGenericBM - 1) / kBN + 1);
-  for (int kt = 0; kt < kt_end; ++kt) {
-    const int key = kt * kBN + lane;
-    if (key < n) {
-      const int t = min(static_cast<unsigned>(perm_token[seg0 + key]), static_cast<unsigned>(T - 1));
-      load_row<D, BF16>(k, head_base + t, row);
-      if (rope_mode != 2)
-        rope_row<D>(row, table + static_cast<size_t>(rope_mode == 0 ? key : t) * (D / 2));
-#pragma unroll
-      for (int d = 0; d < D; ++d) sK[lane][d] = row[d];
-      load_row<D, BF16>(v, head_base + t, row);
-#pragma unroll
-      for (int d = 0; d < D; ++d) sV[lane][d] = row[d];
-    }
-    __syncthreads();
-    const int jmax = min(min(kBN, n - kt * kBN), r - kt * kBN + 1);
-    for (int j = 0; j < kBN; ++j) {
-      float sc = 0.f;
-#pragma unroll
-      for (int d = 0; d < D; ++d) sc = fmaf(qv[d], sK[j][d], sc);
-      if (j < jmax) {
-        const float mn = fmaxf(m, sc);
-        const float corr = expf(m - mn);
-        const float p = expf(sc - mn);
-        l = l * corr + p;
-#pragma unroll
-        for (int d = 0; d < D; ++d) acc[d] = fmaf(p, sV[j][d], acc[d] * corr);
-        m = mn;
-      }
-    }
-    __syncthreads();
-  }
-  if (r < n) {
-    const float inv = 1.f / l;
-    float* orow = hout + static_cast<size_t>(seg0 + r) * D;
-#pragma unroll
-    for (int d = 0; d < D; d += 4)
-      *reinterpret_cast<float4*>(orow + d) =
-          make_float4(acc[d] * inv, acc[d + 1] * inv, acc[d + 2] * inv, acc[d + 3] * inv);
-  }
-}
-
-// ---------------------------------------------------------------------------
 // One thread per (token, 8 output elements).  The K slots are gathered eight
 // at a time (all loads of a batch issued before their products) and summed
 // in k order.  GC = 1 fixes G = 1 at compile time (no per-row division,
@@ -1325,15 +1207,6 @@ static void launch_mfma(const AttnWs& w, const void* q, const void* k, const voi
   }
 }
 
-template <int D, bool BF16>
-static void launch_generic(const AttnWs& w, const void* q, const void* k, const void* v,
-                           int T, int H, int rope_mode, float scale,
-                           const int32_t* seg_offsets, const int32_t* perm_token,
-                           float* hout, hipStream_t st) {
-  launch_k("attn", k_attn_generic<D, BF16>, dim3(static_cast<unsigned>(w.max_items)), dim3(64),
-           st, q, k, v, w.table, perm_token, w.items, w.meta, T, H, rope_mode, scale, hout);
-}
-
 hipError_t launch_attn(const void* q, const void* k, const void* v, int dtype,
                        int B, int T, int H, int K, int d, float rope_base,
                        int rope_mode, float scale, const float* gates,
@@ -1370,18 +1243,9 @@ hipError_t launch_attn(const void* q, const void* k, const void* v, int dtype,
                        perm_token, hout, hb, nullptr, st, 0, true, fuse);
   } else {
     if (G != 1) return hipErrorInvalidValue;   // key/value groups run on the MFMA path only
-    k_attn_schedule<<<1, kPackThreads, 0, st>>>(seg_offsets, B * H, T, BM, Nr,
-                                                static_cast<int>(w.max_items), device_cu_count(),
-                                                w.items, w.meta);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const bool bf = dtype == 1;
-#define NAMOH_GEN(DD)                                                                        \
-  (bf ? launch_generic<DD, true>(w, q, k, v, T, H, rope_mode, scale, seg_offsets, perm_token, static_cast<float*>(hout), st) \
-      : launch_generic<DD, false>(w, q, k, v, T, H, rope_mode, scale, seg_offsets, perm_token, static_cast<float*>(hout), st))
-    if (d == 32) NAMOH_GEN(32);
-    else if (d == 64) NAMOH_GEN(64);
-    else NAMOH_GEN(128);
-#undef NAMOH_GEN
+    e = launch_f32_attn(q, k, v, dtype, d, w.table, seg_offsets, perm_token, B * H, T, Nr,
+                        rope_mode, scale, static_cast<float*>(hout), st);
+    if (e != hipSuccess) return e;
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (out == nullptr) return hipSuccess;   // head outputs only

@@ -13,17 +13,12 @@
 // recomputed here, so the gradients do not depend on how the forward ran.
 //   k_bwd_zero     clears the dense gradients (rows of tokens a head does
 //                  not see get none).
-//   k_bwd_gather   one thread per (packed row, 8-pair group): rotated q, k,
+//   k_bwd_gather   one thread per (packed row, 4-pair group): rotated q, k,
 //                  the value row and dO = g dout, packed fp32; the row's
 //                  segment (binary search over the offsets, staged in LDS)
 //                  and its k slot.
-//   k_bwd_q        one lane per query of a 64-query block of a segment:
-//                  pass 1 over the block's keys (64-key tiles in LDS) for the
-//                  log-sum-exp and O, then D = <dO, O> and the gate gradient;
-//                  pass 2 for dQ~.
-//   k_bwd_kv       one lane per key of a 64-key block: pass 1 over the later
-//                  queries (tiles of Q~, dO, lse, D in LDS) for dV, pass 2
-//                  for dK~.
+//   k_f32_bwd_q,   (f32.hip) statistics, D = <dO, O>, the gate gradient and
+//   k_f32_bwd_kv   dQ~ by query block; dV and dK~ by key block.
 //   k_bwd_scatter  un-rotates dQ~, dK~ and writes dq, dk, dv at the token
 //                  rows; dgates at the (t, k) slots.
 #include <algorithm>
@@ -36,13 +31,27 @@
 
 namespace namoh {
 
-constexpr int kBwdBlock = 64;       // rows per LDS tile
+constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kBwdSegLds = 2048;    // segment offsets staged in LDS up to this many
 
 template <bool BF16>
-NAMOH_DEV float ldx(const void* p, size_t i) {
-  if constexpr (BF16) return bf16_to_f32(static_cast<const uint16_t*>(p)[i]);
-  else return static_cast<const float*>(p)[i];
+NAMOH_DEV float4 ldx4(const void* p, size_t i) {
+  if constexpr (BF16) {
+    const uint2 w = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p) + i);
+    return make_float4(lo_bf16(w.x), hi_bf16(w.x), lo_bf16(w.y), hi_bf16(w.y));
+  } else {
+    return *reinterpret_cast<const float4*>(static_cast<const float*>(p) + i);
+  }
+}
+
+// (x1, x2) = elements j0 .. j0 + 3 and their partners, rotated by the angles
+// whose (cos, sin) are cs[0 .. 3]
+NAMOH_DEV void rotate4(float4& x1, float4& x2, const float2 (&cs)[4]) {
+  const float4 a = x1, b = x2;
+  x1 = make_float4(a.x * cs[0].x - b.x * cs[0].y, a.y * cs[1].x - b.y * cs[1].y,
+                   a.z * cs[2].x - b.z * cs[2].y, a.w * cs[3].x - b.w * cs[3].y);
+  x2 = make_float4(b.x * cs[0].x + a.x * cs[0].y, b.y * cs[1].x + a.y * cs[1].y,
+                   b.z * cs[2].x + a.z * cs[2].y, b.w * cs[3].x + a.w * cs[3].y);
 }
 
 // ---------------------------------------------------------------------------
@@ -66,7 +75,7 @@ __global__ __launch_bounds__(256) void k_bwd_gather(
     const int32_t* __restrict__ perm_token, int BH, int H, int T, int K, int Nr, int rope_mode,
     double log_base, float* __restrict__ Qr, float* __restrict__ Kr, float* __restrict__ Vp,
     float* __restrict__ dOp, int32_t* __restrict__ seg_of, int32_t* __restrict__ kslot) {
-  constexpr int G = D / 16;               // 8-pair groups per row
+  constexpr int G = D / 8;                // 4-pair groups per row
   constexpr int RW = 256 / G;             // rows per workgroup
   __shared__ double s_theta[D / 2];
   __shared__ int s_off[kBwdSegLds + 1];
@@ -78,7 +87,7 @@ __global__ __launch_bounds__(256) void k_bwd_gather(
   __syncthreads();
   const int32_t* off = in_lds ? s_off : seg_offsets;
   const int r = block_x() * RW + tid / G;
-  const int j0 = (tid % G) * 8;
+  const int j0 = (tid % G) * 4;
   if (r >= Nr) return;
   int lo = 0, hi = BH;   // the last segment starting at or before r
   while (hi - lo > 1) {
@@ -111,286 +120,31 @@ __global__ __launch_bounds__(256) void k_bwd_gather(
     seg_of[r] = s;
     kslot[r] = ks;
   }
-  const size_t src = (static_cast<size_t>(s) * T + t) * D;
-  const size_t dst = static_cast<size_t>(r) * D;
-  const double pos = rope_mode == 0 ? rank : t;
+  const size_t src = (static_cast<size_t>(s) * T + t) * D + j0;
+  const size_t dst = static_cast<size_t>(r) * D + j0;
+  const size_t drow = (static_cast<size_t>(b) * T + t) * D + j0;
+  float4 q1 = ldx4<BF16>(q, src), q2 = ldx4<BF16>(q, src + D / 2);
+  float4 k1 = ldx4<BF16>(k, src), k2 = ldx4<BF16>(k, src + D / 2);
+  const float4 v1 = ldx4<BF16>(v, src), v2 = ldx4<BF16>(v, src + D / 2);
+  const float4 d1 = *reinterpret_cast<const float4*>(dout + drow);
+  const float4 d2 = *reinterpret_cast<const float4*>(dout + drow + D / 2);
+  if (rope_mode != 2) {
+    const double pos = rope_mode == 0 ? rank : t;
+    float2 cs[4];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int j = j0 + e;
-    float cs = 1.f, sn = 0.f;
-    if (rope_mode != 2) {
-      const float2 w = rope_cos_sin(pos * s_theta[j]);
-      cs = w.x;
-      sn = w.y;
-    }
-    const float q1 = ldx<BF16>(q, src + j), q2 = ldx<BF16>(q, src + j + D / 2);
-    const float k1 = ldx<BF16>(k, src + j), k2 = ldx<BF16>(k, src + j + D / 2);
-    Qr[dst + j] = q1 * cs - q2 * sn;
-    Qr[dst + j + D / 2] = q2 * cs + q1 * sn;
-    Kr[dst + j] = k1 * cs - k2 * sn;
-    Kr[dst + j + D / 2] = k2 * cs + k1 * sn;
-    Vp[dst + j] = ldx<BF16>(v, src + j);
-    Vp[dst + j + D / 2] = ldx<BF16>(v, src + j + D / 2);
-    const size_t drow = (static_cast<size_t>(b) * T + t) * D;
-    dOp[dst + j] = g * dout[drow + j];
-    dOp[dst + j + D / 2] = g * dout[drow + j + D / 2];
+    for (int e = 0; e < 4; ++e) cs[e] = rope_cos_sin(pos * s_theta[j0 + e]);
+    rotate4(q1, q2, cs);
+    rotate4(k1, k2, cs);
   }
-}
-
-// ---------------------------------------------------------------------------
-// Row split: a row of D values is held by LPR = D / 64 lanes (one for d <= 64,
-// two at d = 128), each with DH = D / LPR of its values; dot products add the
-// lanes' partial sums with one exchange.  A wave holds 64 / LPR rows and a
-// workgroup of kBwdWaves waves shares every 64-row tile staged in LDS (rows
-// padded to D + 4 floats, so 16-byte reads stay aligned).
-constexpr int kBwdWaves = 4;
-constexpr int kBwdWgThreads = kBwdWaves * kWave;
-template <int D> struct BwdShape {
-  static constexpr int LPR = D > 64 ? D / 64 : 1;
-  static constexpr int DH = D / LPR;
-  static constexpr int RW = kWave / LPR;          // rows per wave
-  static constexpr int RB = kBwdWaves * RW;       // rows per workgroup
-  static constexpr int LD = D + 4;                // LDS row stride (floats)
-};
-
-template <int LPR>
-NAMOH_DEV float row_sum(float x) {
-  if constexpr (LPR == 2) x = group_sum<2>(x);
-  return x;
-}
-
-// rows [r0, r0 + 64) of a packed fp32 array (rows past n as zeros) into an
-// LDS tile, 16-byte loads all issued before the stores
-template <int D>
-NAMOH_DEV void stage_tile(float* tile, const float* __restrict__ src, size_t a, int r0, int n,
-                          int tid) {
-  constexpr int LD = BwdShape<D>::LD;
-  constexpr int C4 = D / 4;                               // float4 per row
-  constexpr int PER = kBwdBlock * C4 / kBwdWgThreads;     // float4 per thread
-  float4 x[PER];
-#pragma unroll
-  for (int m = 0; m < PER; ++m) {
-    const int u = tid + m * kBwdWgThreads;
-    const int rr = u / C4, c4 = u - rr * C4;
-    x[m] = r0 + rr < n ? *reinterpret_cast<const float4*>(src + (a + r0 + rr) * D + 4 * c4)
-                       : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-#pragma unroll
-  for (int m = 0; m < PER; ++m) {
-    const int u = tid + m * kBwdWgThreads;
-    const int rr = u / C4, c4 = u - rr * C4;
-    *reinterpret_cast<float4*>(tile + rr * LD + 4 * c4) = x[m];
-  }
-}
-
-template <int DH>
-NAMOH_DEV float dot_lds(const float* v, const float* row) {
-  float s = 0.f;
-#pragma unroll
-  for (int e = 0; e < DH; e += 4) {
-    const float4 r = *reinterpret_cast<const float4*>(row + e);
-    s = fmaf(v[e], r.x, s);
-    s = fmaf(v[e + 1], r.y, s);
-    s = fmaf(v[e + 2], r.z, s);
-    s = fmaf(v[e + 3], r.w, s);
-  }
-  return s;
-}
-
-template <int DH>
-NAMOH_DEV void axpy_lds(float* acc, float a, const float* row) {
-#pragma unroll
-  for (int e = 0; e < DH; e += 4) {
-    const float4 r = *reinterpret_cast<const float4*>(row + e);
-    acc[e] = fmaf(a, r.x, acc[e]);
-    acc[e + 1] = fmaf(a, r.y, acc[e + 1]);
-    acc[e + 2] = fmaf(a, r.z, acc[e + 2]);
-    acc[e + 3] = fmaf(a, r.w, acc[e + 3]);
-  }
-}
-
-constexpr float kLog2e = 1.4426950408889634f;
-
-// Query side.  Workgroup qb of segment s (grid y = segment, x = block;
-// blocks past the segment's end exit); lanes (row i, part).  Scores are kept
-// in log2 units (q scaled by scale log2 e), so exp2 applies directly.
-template <int D>
-__global__ __launch_bounds__(kBwdWgThreads, 1) void k_bwd_q(
-    const float* __restrict__ Qr, const float* __restrict__ Kr, const float* __restrict__ Vp,
-    const float* __restrict__ dOp, const float* __restrict__ dout,
-    const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ perm_token, int H, int T,
-    int Nr, float scale, float* __restrict__ lse, float* __restrict__ Dr, float* __restrict__ dgp,
-    float* __restrict__ dQr) {
-  using S = BwdShape<D>;
-  constexpr int DH = S::DH, RB = S::RB, LD = S::LD;
-  __shared__ __attribute__((aligned(16))) float sk[kBwdBlock * LD];
-  __shared__ __attribute__((aligned(16))) float sv[kBwdBlock * LD];
-  const int s = static_cast<int>(__builtin_amdgcn_workgroup_id_y());
-  const int qb = block_x();
-  const int a = seg_offsets[s], n = seg_offsets[s + 1] - a;
-  const int i0 = qb * RB;
-  if (i0 >= n || a < 0 || n > T || a + n > Nr) return;   // past the end, or not a packing
-  const int tid = thread_x();
-  const int wave = tid / kWave, lane = tid % kWave;
-  const int i = i0 + wave * S::RW + lane / S::LPR, c0 = (lane % S::LPR) * DH;
-  const bool valid = i < n;
-  const size_t row = static_cast<size_t>(a) + (valid ? i : n - 1);
-  const float sl2 = scale * kLog2e;
-  float qv[DH], acc[DH];
-#pragma unroll
-  for (int e = 0; e < DH; ++e) {
-    qv[e] = Qr[row * D + c0 + e] * sl2;
-    acc[e] = 0.f;
-  }
-  const int ntile = (min(n, i0 + RB) + kBwdBlock - 1) / kBwdBlock;
-  auto stage = [&](int kt) {
-    __syncthreads();
-    stage_tile<D>(sk, Kr, a, kt * kBwdBlock, n, tid);
-    stage_tile<D>(sv, Vp, a, kt * kBwdBlock, n, tid);
-    __syncthreads();
-  };
-  float m = -INFINITY, l = 0.f;
-  // pass 1: log-sum-exp and O (the accumulator is rescaled only when the
-  // running maximum rises)
-  for (int kt = 0; kt < ntile; ++kt) {
-    stage(kt);
-    const int j0 = kt * kBwdBlock;
-    const int jn = min(kBwdBlock, i + 1 - j0);   // keys j0 .. i (the same for a row's lanes)
-    for (int jj = 0; jj < jn; ++jj) {
-      const float sc = row_sum<S::LPR>(dot_lds<DH>(qv, sk + jj * LD + c0));
-      if (sc > m) {
-        const float corr = exp2f(m - sc);
-        l *= corr;
-#pragma unroll
-        for (int e = 0; e < DH; ++e) acc[e] *= corr;
-        m = sc;
-      }
-      const float p = exp2f(sc - m);
-      l += p;
-      axpy_lds<DH>(acc, p, sv + jj * LD + c0);
-    }
-  }
-  // D = <dO, O>, gate gradient <O, dout_t>
-  const float inv = 1.f / l;
-  const int t = min(static_cast<unsigned>(perm_token[row]), static_cast<unsigned>(T - 1));
-  const int b = s / H;
-  float dsum = 0.f, gsum = 0.f;
-  float dov[DH];
-#pragma unroll
-  for (int e = 0; e < DH; ++e) {
-    const float o = acc[e] * inv;
-    dov[e] = dOp[row * D + c0 + e];
-    dsum = fmaf(dov[e], o, dsum);
-    gsum = fmaf(dout[(static_cast<size_t>(b) * T + t) * D + c0 + e], o, gsum);
-    acc[e] = 0.f;
-  }
-  dsum = row_sum<S::LPR>(dsum);
-  gsum = row_sum<S::LPR>(gsum);
-  const float lse2 = m + log2f(l);   // log2 units
-  if (valid && c0 == 0) {
-    lse[row] = lse2;
-    Dr[row] = dsum;
-    dgp[row] = gsum;
-  }
-  // pass 2: dQ~ = scale * sum_j P_ij (dO_i . v_j - D_i) k~_j
-  for (int kt = 0; kt < ntile; ++kt) {
-    stage(kt);
-    const int j0 = kt * kBwdBlock;
-    const int jn = min(kBwdBlock, i + 1 - j0);
-    for (int jj = 0; jj < jn; ++jj) {
-      const float sc = row_sum<S::LPR>(dot_lds<DH>(qv, sk + jj * LD + c0));
-      const float dp = row_sum<S::LPR>(dot_lds<DH>(dov, sv + jj * LD + c0));
-      const float ds = exp2f(sc - lse2) * (dp - dsum) * scale;
-      axpy_lds<DH>(acc, ds, sk + jj * LD + c0);
-    }
-  }
-  if (valid) {
-#pragma unroll
-    for (int e = 0; e < DH; ++e) dQr[row * D + c0 + e] = acc[e];
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Key side.  Workgroup kb of segment s; lanes (key row j, part); queries
-// i >= j, their tiles (Q~, dO, log-sum-exp in log2 units, D) staged in LDS.
-template <int D>
-__global__ __launch_bounds__(kBwdWgThreads, 1) void k_bwd_kv(
-    const float* __restrict__ Qr, const float* __restrict__ Kr, const float* __restrict__ Vp,
-    const float* __restrict__ dOp, const float* __restrict__ lse, const float* __restrict__ Dr,
-    const int32_t* __restrict__ seg_offsets, int T, int Nr, float scale, float* __restrict__ dKr,
-    float* __restrict__ dVp) {
-  using S = BwdShape<D>;
-  constexpr int DH = S::DH, RB = S::RB, LD = S::LD;
-  __shared__ __attribute__((aligned(16))) float sq[kBwdBlock * LD];
-  __shared__ __attribute__((aligned(16))) float sdo[kBwdBlock * LD];
-  __shared__ float sl[kBwdBlock], sd[kBwdBlock];
-  const int s = static_cast<int>(__builtin_amdgcn_workgroup_id_y());
-  const int kb = block_x();
-  const int a = seg_offsets[s], n = seg_offsets[s + 1] - a;
-  const int j0 = kb * RB;
-  if (j0 >= n || a < 0 || n > T || a + n > Nr) return;   // past the end, or not a packing
-  const int tid = thread_x();
-  const int wave = tid / kWave, lane = tid % kWave;
-  const int j = j0 + wave * S::RW + lane / S::LPR, c0 = (lane % S::LPR) * DH;
-  const bool valid = j < n;
-  const size_t row = static_cast<size_t>(a) + (valid ? j : n - 1);
-  const float sl2 = scale * kLog2e;
-  float kv[DH], acc[DH];
-#pragma unroll
-  for (int e = 0; e < DH; ++e) {
-    kv[e] = Kr[row * D + c0 + e] * sl2;
-    acc[e] = 0.f;
-  }
-  const int nqt = (n + kBwdBlock - 1) / kBwdBlock;
-  const int qt0 = j0 / kBwdBlock;
-  auto stage = [&](int qt) {
-    const int i0 = qt * kBwdBlock;
-    __syncthreads();
-    stage_tile<D>(sq, Qr, a, i0, n, tid);
-    stage_tile<D>(sdo, dOp, a, i0, n, tid);
-    if (tid < kBwdBlock) {
-      const bool in = i0 + tid < n;
-      sl[tid] = in ? lse[static_cast<size_t>(a) + i0 + tid] : 0.f;
-      sd[tid] = in ? Dr[static_cast<size_t>(a) + i0 + tid] : 0.f;
-    }
-    __syncthreads();
-  };
-  // pass 1: dV_j = sum_{i >= j} P_ij dO_i
-  for (int qt = qt0; qt < nqt; ++qt) {
-    stage(qt);
-    const int i0 = qt * kBwdBlock;
-    const int ib = max(0, j - i0), ie = min(kBwdBlock, n - i0);
-    for (int ii = ib; ii < ie; ++ii) {
-      const float sc = row_sum<S::LPR>(dot_lds<DH>(kv, sq + ii * LD + c0));
-      axpy_lds<DH>(acc, exp2f(sc - sl[ii]), sdo + ii * LD + c0);
-    }
-  }
-  if (valid) {
-#pragma unroll
-    for (int e = 0; e < DH; ++e) dVp[row * D + c0 + e] = acc[e];
-  }
-  // pass 2: dK~_j = scale * sum_{i >= j} P_ij (dO_i . v_j - D_i) q~_i
-  float vv[DH];
-#pragma unroll
-  for (int e = 0; e < DH; ++e) {
-    vv[e] = Vp[row * D + c0 + e];
-    acc[e] = 0.f;
-  }
-  for (int qt = qt0; qt < nqt; ++qt) {
-    stage(qt);
-    const int i0 = qt * kBwdBlock;
-    const int ib = max(0, j - i0), ie = min(kBwdBlock, n - i0);
-    for (int ii = ib; ii < ie; ++ii) {
-      const float sc = row_sum<S::LPR>(dot_lds<DH>(kv, sq + ii * LD + c0));
-      const float dp = row_sum<S::LPR>(dot_lds<DH>(vv, sdo + ii * LD + c0));
-      const float ds = exp2f(sc - sl[ii]) * (dp - sd[ii]) * scale;
-      axpy_lds<DH>(acc, ds, sq + ii * LD + c0);
-    }
-  }
-  if (valid) {
-#pragma unroll
-    for (int e = 0; e < DH; ++e) dKr[row * D + c0 + e] = acc[e];
-  }
+  auto put = [&](float* p, size_t i, const float4 x) { *reinterpret_cast<float4*>(p + i) = x; };
+  put(Qr, dst, q1);
+  put(Qr, dst + D / 2, q2);
+  put(Kr, dst, k1);
+  put(Kr, dst + D / 2, k2);
+  put(Vp, dst, v1);
+  put(Vp, dst + D / 2, v2);
+  put(dOp, dst, make_float4(g * d1.x, g * d1.y, g * d1.z, g * d1.w));
+  put(dOp, dst + D / 2, make_float4(g * d2.x, g * d2.y, g * d2.z, g * d2.w));
 }
 
 // ---------------------------------------------------------------------------
@@ -402,14 +156,14 @@ __global__ __launch_bounds__(256) void k_bwd_scatter(
     const int32_t* __restrict__ perm_token, int BH, int H, int T, int K, int Nr, int rope_mode,
     double log_base, float* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv,
     float* __restrict__ dgates, int packed) {
-  constexpr int G = D / 16;
+  constexpr int G = D / 8;
   constexpr int RW = 256 / G;
   __shared__ double s_theta[D / 2];
   const int tid = thread_x();
   if (tid < D / 2) s_theta[tid] = exp(-(2.0 * tid / D) * log_base);
   __syncthreads();
   const int r = block_x() * RW + tid / G;
-  const int j0 = (tid % G) * 8;
+  const int j0 = (tid % G) * 4;
   if (r >= Nr) return;
   const int t = perm_token[r];
   const int s = seg_of[r];
@@ -418,29 +172,32 @@ __global__ __launch_bounds__(256) void k_bwd_scatter(
   const int b = s / H;
   const int ks = kslot[r];
   if (j0 == 0 && ks >= 0 && ks < K) dgates[(static_cast<size_t>(b) * T + t) * K + ks] = dgp[r];
-  const size_t src = static_cast<size_t>(r) * D;
+  const size_t src = static_cast<size_t>(r) * D + j0;
   // dense [B, H, T, d] rows, or (packed) the routed row's own packed row
-  const size_t dst = packed ? static_cast<size_t>(r) * D : (static_cast<size_t>(s) * T + t) * D;
-  const double pos = rope_mode == 0 ? rank : t;
+  const size_t dst = (packed ? static_cast<size_t>(r) * D : (static_cast<size_t>(s) * T + t) * D) + j0;
+  auto get = [&](const float* p, size_t i) { return *reinterpret_cast<const float4*>(p + i); };
+  auto put = [&](float* p, size_t i, const float4 x) { *reinterpret_cast<float4*>(p + i) = x; };
+  float4 q1 = get(dQr, src), q2 = get(dQr, src + D / 2);
+  float4 k1 = get(dKr, src), k2 = get(dKr, src + D / 2);
+  const float4 v1 = get(dVp, src), v2 = get(dVp, src + D / 2);
+  if (rope_mode != 2) {
+    // gradient through the rotation: the rotation by minus the angle
+    const double pos = rope_mode == 0 ? rank : t;
+    float2 cs[4];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int j = j0 + e;
-    float cs = 1.f, sn = 0.f;
-    if (rope_mode != 2) {
-      const float2 w = rope_cos_sin(pos * s_theta[j]);
-      cs = w.x;
-      sn = w.y;
+    for (int e = 0; e < 4; ++e) {
+      cs[e] = rope_cos_sin(pos * s_theta[j0 + e]);
+      cs[e].y = -cs[e].y;
     }
-    // gradient through x' = (x1 c - x2 s, x2 c + x1 s): (d1 c + d2 s, d2 c - d1 s)
-    const float q1 = dQr[src + j], q2 = dQr[src + j + D / 2];
-    const float k1 = dKr[src + j], k2 = dKr[src + j + D / 2];
-    dq[dst + j] = q1 * cs + q2 * sn;
-    dq[dst + j + D / 2] = q2 * cs - q1 * sn;
-    dk[dst + j] = k1 * cs + k2 * sn;
-    dk[dst + j + D / 2] = k2 * cs - k1 * sn;
-    dv[dst + j] = dVp[src + j];
-    dv[dst + j + D / 2] = dVp[src + j + D / 2];
+    rotate4(q1, q2, cs);
+    rotate4(k1, k2, cs);
   }
+  put(dq, dst, q1);
+  put(dq, dst + D / 2, q2);
+  put(dk, dst, k1);
+  put(dk, dst + D / 2, k2);
+  put(dv, dst, v1);
+  put(dv, dst + D / 2, v2);
 }
 
 // ===========================================================================
@@ -1550,21 +1307,15 @@ static hipError_t run_bwd(const void* q, const void* k, const void* v, int B, in
         reinterpret_cast<float4*>(dv), n4);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  constexpr int RW = 256 / (D / 16);
+  constexpr int RW = 256 / (D / 8);
   const unsigned rgrid = static_cast<unsigned>((Nr + RW - 1) / RW);
   k_bwd_gather<D, BF16><<<rgrid, 256, 0, st>>>(q, k, v, topk_idx, gates, dout, seg_offsets,
                                                perm_token, BH, H, T, K, Nr, rope_mode, log_base,
                                                w.Qr, w.Kr, w.Vp, w.dOp, w.seg_of, w.kslot);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  constexpr int RB = BwdShape<D>::RB;
-  const dim3 sgrid(static_cast<unsigned>((T + RB - 1) / RB), static_cast<unsigned>(BH));
-  k_bwd_q<D><<<sgrid, kBwdWgThreads, 0, st>>>(w.Qr, w.Kr, w.Vp, w.dOp, dout, seg_offsets,
-                                            perm_token, H, T, Nr, scale, w.lse, w.Dr, w.dgp,
-                                            w.dQr);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_bwd_kv<D><<<sgrid, kBwdWgThreads, 0, st>>>(w.Qr, w.Kr, w.Vp, w.dOp, w.lse, w.Dr, seg_offsets,
-                                             T, Nr, scale, w.dKr, w.dVp);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const F32BwdRows rows{w.Qr, w.Kr, w.Vp, w.dOp, w.dQr, w.dKr, w.dVp, w.lse, w.Dr, w.dgp};
+  e = launch_f32_bwd(rows, dout, D, seg_offsets, perm_token, BH, H, T, Nr, scale, st);
+  if (e != hipSuccess) return e;
   k_bwd_scatter<D><<<rgrid, 256, 0, st>>>(w.dQr, w.dKr, w.dVp, w.dgp, w.seg_of, w.kslot,
                                           seg_offsets, perm_token, BH, H, T, K, Nr, rope_mode,
                                           log_base, dq, dk, dv, dgates, packed ? 1 : 0);

@@ -94,6 +94,20 @@ hipError_t launch_combine_rows(const uint16_t* rows, const float* gates, const i
                                long BT, int K, int D, int Nr, void* out, int out_dtype,
                                hipStream_t st);
 
+// ---- float32 path (f32.hip) -------------------------------------------------
+hipError_t launch_f32_attn(const void* q, const void* k, const void* v, int dtype, int d,
+                           const float2* table, const int32_t* seg_offsets,
+                           const int32_t* perm_token, int BH, int T, int Nr, int rope_mode,
+                           float scale, float* hout, hipStream_t st);
+// The backward's packed rows [Nr, d] (rotated q and k, v, g dout), statistics
+// [Nr] and packed gradients.
+struct F32BwdRows {
+  float *Qr, *Kr, *Vp, *dOp, *dQr, *dKr, *dVp, *lse, *Dr, *dgp;
+};
+hipError_t launch_f32_bwd(const F32BwdRows& w, const float* dout, int d, const int32_t* seg_offsets,
+                          const int32_t* perm_token, int BH, int H, int T, int Nr, float scale,
+                          hipStream_t st);
+
 // ---- routed projections (proj.hip) ---------------------------------------
 hipError_t launch_qkv_proj(const void* x, const void* w_qkv, int B, int T, int H, int K, int d,
                            int d_model, const int32_t* seg_offsets, const int32_t* perm_token,

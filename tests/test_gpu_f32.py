@@ -1,0 +1,143 @@
+"""The float32 path (f32.hip) at the edges of its 32-row tiles, against plain
+causal attention in float64 on the host.
+
+Tolerance: relative L2 error 4e-6.  Every product and sum is float32 (2^-24
+relative each, accumulated over d + n terms of random sign: about
+2^-24 sqrt(d + n) = 2e-6 at the sizes below), the exponentials and the
+rotation factors are good to a few units in the last place.
+"""
+import math
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2609_38832_amd import _lib as L  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    L.lib()
+
+
+from gpu_util import DEV, say  # noqa: E402
+
+REL = 4e-6
+BASE = 1e4
+
+
+def _rope(x, base):
+    n, d = x.shape[-2:]
+    th = base ** (-2.0 * torch.arange(d // 2, dtype=torch.float64) / d)
+    a = torch.arange(n, dtype=torch.float64)[:, None] * th
+    c, s = a.cos(), a.sin()
+    x1, x2 = x[..., :d // 2], x[..., d // 2:]
+    return torch.cat([x1 * c - x2 * s, x2 * c + x1 * s], -1)
+
+
+def _reference(q, k, v, dout):
+    """out and gradients of one head that holds every token (gate 1)."""
+    q, k, v = (x.cpu().double().requires_grad_(True) for x in (q, k, v))
+    n, d = q.shape[-2:]
+    s = _rope(q, BASE) @ _rope(k, BASE).transpose(-1, -2) / math.sqrt(d)
+    p = torch.softmax(s.masked_fill(torch.ones(n, n).triu(1).bool(), float("-inf")), -1)
+    o = p @ v
+    g = torch.autograd.grad((o * dout.cpu().double()).sum(), (q, k, v))
+    return o.detach(), g
+
+
+def _rel(got, ref):
+    return float((got.cpu().double() - ref).norm() / ref.norm())
+
+
+def _one_head(B, n, d, dtype, seed=1):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    q, k, v = (torch.randn(B, 1, n, d, generator=g, device=DEV).to(dtype) for _ in range(3))
+    dout = torch.randn(B, n, d, generator=g, device=DEV)
+    r = L.route(torch.zeros(B, n, 1, device=DEV), 1)
+    return q, k, v, dout, r
+
+
+# rows of a segment around the tiles, the four-tile rounds and the two-tile ones
+SIZES = [1, 2, 31, 32, 33, 63, 65, 96, 127, 128, 129, 160, 257, 513]
+
+
+@pytest.mark.parametrize("d,dtype", [(32, torch.float32), (32, torch.bfloat16),
+                                     (64, torch.float32), (128, torch.float32)])
+@pytest.mark.parametrize("n", SIZES)
+def test_edges(n, d, dtype):
+    say(f"float32 path n {n} d {d} {dtype}")
+    B = 2
+    q, k, v, dout, r = _one_head(B, n, d, dtype)
+    out = L.attn_fwd(q, k, v, r, 1, BASE, out_dtype=torch.float32,
+                     out=torch.full((B, n, d), float("nan"), device=DEV))
+    ref, grads = _reference(q[:, 0], k[:, 0], v[:, 0], dout)
+    assert _rel(out, ref) <= REL
+    for packed in (False, True):
+        res = L.attn_bwd(q, k, v, r, 1, BASE, dout, packed=packed)
+        for name, g in zip(("dq", "dk", "dv"), grads):
+            if n == 1 and name != "dv":   # one key: the probabilities are constant
+                assert float(res[name].abs().max()) <= 1e-5
+            else:
+                assert _rel(res[name].reshape(B, n, d), g) <= REL, name
+        gates = (ref * dout.cpu().double()).sum(-1)
+        err = (res["dgates"].reshape(B, n).cpu().double() - gates).norm() / gates.norm()
+        assert float(err) <= REL
+
+
+def test_many_segments():
+    # more than 1024 (sequence, head) segments: offsets searched in global memory
+    B, T, H, K, d = 300, 5, 4, 2, 64
+    g = torch.Generator(device=DEV).manual_seed(2)
+    q, k, v = (torch.randn(B, H, T, d, generator=g, device=DEV) for _ in range(3))
+    dout = torch.randn(B, T, d, generator=g, device=DEV)
+    r = L.route(torch.randn(B, T, H, generator=g, device=DEV), K)
+    out, res = L.attn_fwd(q, k, v, r, K, BASE), L.attn_bwd(q, k, v, r, K, BASE, dout)
+    ref = torch.zeros(B, T, d, dtype=torch.float64)
+    refs = [torch.zeros(B, H, T, d, dtype=torch.float64) for _ in range(3)]
+    topk, gates = r["topk_idx"].cpu(), r["gates"].cpu().double()
+    for b in range(B):
+        for h in range(H):
+            t, slot = torch.nonzero(topk[b] == h, as_tuple=True)
+            if len(t) == 0:
+                continue
+            gt = gates[b, t, slot][:, None]
+            o, gr = _reference(q[b, h, t.to(DEV)], k[b, h, t.to(DEV)], v[b, h, t.to(DEV)],
+                               gt * dout.cpu().double()[b, t])
+            ref[b, t] += gt * o
+            for x, y in zip(refs, gr):
+                x[b, h, t] = y
+    assert _rel(out, ref) <= REL
+    for name, x in zip(("dq", "dk", "dv"), refs):
+        assert _rel(res[name], x) <= REL, name
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_non_finite_rows_stay_where_they_are_seen(bad, d):
+    # a key, value or query of token t reaches no earlier token's output, and
+    # a gradient of token t's output no later token's
+    n, t = 140, 101
+    q, k, v, dout, r = _one_head(1, n, d, torch.float32, 3)
+    ref, (gq, gk, gv) = _reference(q[:, 0], k[:, 0], v[:, 0], dout)
+    for which in range(3):
+        x = [y.clone() for y in (q, k, v)]
+        x[which][0, 0, t, 5] = bad
+        out = L.attn_fwd(*x, r, 1, BASE)
+        res = L.attn_bwd(*x, r, 1, BASE, dout)
+        assert _rel(out[:, :t], ref[:, :t]) <= REL
+        assert _rel(res["dq"][0, :, :t], gq[:, :t]) <= REL
+        if which == 2:   # (an infinite key may score minus infinity: weight zero)
+            assert not torch.isfinite(out[:, t]).all()
+        if which == 0:   # the query is its own row's alone
+            assert _rel(out[:, t + 1:], ref[:, t + 1:]) <= REL
+    do = dout.clone()
+    do[0, t, 5] = bad
+    res = L.attn_bwd(q, k, v, r, 1, BASE, do)
+    assert _rel(res["dk"][0, :, t + 1:], gk[:, t + 1:]) <= REL
+    assert _rel(res["dv"][0, :, t + 1:], gv[:, t + 1:]) <= REL
+    assert _rel(res["dq"][0, :, t + 1:], gq[:, t + 1:]) <= REL
