@@ -227,11 +227,26 @@ constexpr float kLn2 = 0.6931471805599453f;
 // The key side's own work list (built by the packing kernel's workgroup 0):
 // where it goes, its capacity, and the placement (period: compute units;
 // resident: the key-side kernel's resident workgroups).
+// split_slots / splits: query-range parts of blocks heavier than a fair share
+// of that many workgroups (0: whole blocks only).
 struct KeyList {
   WorkItem* items;
   int32_t* meta;
-  int max_items, period, resident;
+  int max_items, period, resident, split_slots;
+  SplitItem* splits;
 };
+
+// Query-range parts of the key side.  A key block's work is one serial chain
+// over the query tiles after it, about 2 us each at d = 128; a block of a long
+// segment outlasts the rest of the kernel (one head with 9.7k of 12k tokens:
+// 152 tiles against a fair share of 81, key side 373 us with most of the chip
+// idle at the end).  Blocks with more than a fair share are cut as the forward
+// cuts its query blocks; a part writes its dK, dV sums to the block's partial
+// rows, which k_bwd_kv_merge adds in part order.  Only blocks of at least
+// kKeySplitTiles query tiles: then no block is cut at T <= 4096, and the
+// merge launch (about 4 us, also when nothing was cut) is left out there.
+constexpr int kKeySplitTiles = 65;
+static bool key_split(int T) { return T > (kKeySplitTiles - 1) * kBN; }
 
 template <int D>
 struct BwdPackLds {
@@ -256,10 +271,12 @@ __global__ __launch_bounds__(kBwdPackThreads) void k_bwd_pack(
   } U;
   BwdPackLds<D>& L = U.pack;
   if (block_x() == 0) {
-    // the key side's work list: whole blocks, heaviest first, placed for the
-    // key-side kernel's resident workgroups (it runs alongside the packing)
+    // the key side's work list: blocks or their parts, heaviest first, placed
+    // for the key-side kernel's resident workgroups (it runs alongside the
+    // packing)
     attn_schedule<kBwdPackThreads>(seg_offsets, BH, T, kBwdMfmaBlock, Nr, kl.max_items, kl.period,
-                                   1, kl.items, kl.meta, U.sched, 0, nullptr, kl.resident);
+                                   1, kl.items, kl.meta, U.sched, kl.split_slots, kl.splits,
+                                   kl.resident, kKeySplitTiles, false);
     return;
   }
   const int gt = block_x() - 1;   // the tile this workgroup packs
@@ -608,12 +625,31 @@ NAMOH_DEV bool bwd_item_ok(const WorkItem& it, int BH, int T, int Nr, int max_ti
          it.tile0 <= max_tiles - nt && it.kt_lo >= 0 && it.kt_lo < it.kt_hi && it.kt_hi <= nt;
 }
 
-// The key side runs its own list of whole blocks, where every item passes
-// this test.  It guards that list: were the key side given a list with
-// key-range parts, it would take a split block once, whole, at its part 1
-// and skip the other parts, so no block's dK, dV would be written twice.
-NAMOH_DEV bool bwd_key_side_item(const WorkItem& it) {
-  return item_parts(it.qh) <= 1 || item_part(it.qh) == 1;
+// The query tiles [lo, hi) of a key-side item: key block ceil(n / 128) - 1 -
+// qb from its own tiles on.  The list numbers a block's work as the forward's
+// query block qb does (w tiles, the diagonal last); counted from the end that
+// is the key block's tiles from the diagonal on (one more than there are where
+// n has an odd tile count, cut off here: a part may be empty, its sums zero).
+struct KeyRange { int j0, lo, hi, slot; };
+NAMOH_DEV KeyRange key_range(const WorkItem& it) {
+  const int nkb = (it.n + kBwdMfmaBlock - 1) / kBwdMfmaBlock;
+  const int ntiles = (it.n + kBN - 1) / kBN;
+  const int w = min(ntiles, (it.qb + 1) * (kBwdMfmaBlock / kBN));
+  KeyRange r;
+  r.j0 = (nkb - 1 - it.qb) * kBwdMfmaBlock;
+  r.lo = r.j0 / kBN + w - it.kt_hi;
+  r.hi = min(ntiles, r.j0 / kBN + w - it.kt_lo);
+  r.slot = item_slot(it.qh);
+  return r;
+}
+
+// Where the key side's parts put their sums: [slot][dK, dV][128][D] float.
+struct KeyParts {
+  float* rows;
+  int slots;
+};
+NAMOH_DEV float* key_part_row(const KeyParts& kp, int slot, int which, int row, int D) {
+  return kp.rows + ((static_cast<size_t>(slot) * 2 + which) * kBwdMfmaBlock + row) * D;
 }
 
 // Query side: dQ~ of one (segment, 128-query block) item.
@@ -825,7 +861,7 @@ __global__ __launch_bounds__(kBwdMfmaThreads, BwdMfmaShape<D>::MINB) void k_bwd_
     const uint16_t* __restrict__ Vp, const WorkItem* __restrict__ items,
     const int32_t* __restrict__ meta, const int32_t* __restrict__ perm_token,
     const double* __restrict__ freq, int T, int rope_mode, float* __restrict__ dk,
-    float* __restrict__ dv, int packed, int BH, int Nr, int max_tiles, int n_list, DqMerge dqm) {
+    float* __restrict__ dv, int packed, int BH, int Nr, int max_tiles, int n_list, DqMerge dqm, KeyParts kp) {
   constexpr int NT = kBwdMfmaThreads, BM = kBwdMfmaBlock;
   constexpr int KS = D / 16, MT = D / 32;
   constexpr int KPT = kBN * D / 8 / NT;
@@ -843,14 +879,13 @@ __global__ __launch_bounds__(kBwdMfmaThreads, BwdMfmaShape<D>::MINB) void k_bwd_
                           perm_token, freq, T);
     return;
   }
-  if (!my_item(items, meta, it) || !bwd_item_ok(it, BH, T, Nr, max_tiles) ||
-      !bwd_key_side_item(it))
-    return;
+  if (!my_item(items, meta, it) || !bwd_item_ok(it, BH, T, Nr, max_tiles)) return;
+  const KeyRange kr = key_range(it);
+  if (kr.slot >= kp.slots) return;
   const int seg0 = it.seg0, n = it.n, tile0 = it.tile0;
-  const int nkb = (n + BM - 1) / BM;
-  const int j0 = (nkb - 1 - it.qb) * BM;
+  const int j0 = kr.j0;
   const int ntiles = (n + kBN - 1) / kBN;
-  const int qt0 = j0 / kBN;
+  const int qt0 = kr.lo, qt1 = kr.hi;   // the item's query tiles
   const int tid = thread_x();
   const int wave = tid / 64, lane = tid % 64;
   const int c = lane & 31, g = lane >> 5;
@@ -904,11 +939,11 @@ __global__ __launch_bounds__(kBwdMfmaThreads, BwdMfmaShape<D>::MINB) void k_bwd_
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) aK[mt][e] = aV[mt][e] = 0.f;
-  for (int qt = qt0; qt < ntiles; ++qt) {
+  for (int qt = qt0; qt < qt1; ++qt) {
     const int st = (qt - qt0) & 1;
     wait_vmcnt<0>();
     __syncthreads();
-    if (qt + 1 < ntiles) issue(qt + 1, st ^ 1);
+    if (qt + 1 < qt1) issue(qt + 1, st ^ 1);
     const int i0 = qt * kBN;
     // queries i0 .. i0 + 63 against the wave's keys: none visible when the
     // tile ends before the first key
@@ -955,6 +990,13 @@ __global__ __launch_bounds__(kBwdMfmaThreads, BwdMfmaShape<D>::MINB) void k_bwd_
       rows_tposed_x_c<D>(aK, lQ0 + st * TB, tro, dsB);   // dK^T += Q^T dS
     }
   }
+  if (kr.slot >= 0) {   // a part: its sums as they are
+    if (valid) {
+      store_row_unrotated<D>(key_part_row(kp, kr.slot, 0, j - j0, D), aK, 1.f, nullptr, 0.0, g);
+      store_row_unrotated<D>(key_part_row(kp, kr.slot, 1, j - j0, D), aV, 1.f, nullptr, 0.0, g);
+    }
+    return;
+  }
   if (valid) {
     // the queries were scaled by scale * log2 e: dk~ = ln 2 * sum dS Qs,
     // back through the key's rotation; dv as it is
@@ -980,7 +1022,7 @@ __global__ __launch_bounds__(2 * kBwdMfmaThreads, 1) void k_bwd_dkdv8(
     const uint16_t* __restrict__ Vp, const WorkItem* __restrict__ items,
     const int32_t* __restrict__ meta, const int32_t* __restrict__ perm_token,
     const double* __restrict__ freq, int T, int rope_mode, float* __restrict__ dk,
-    float* __restrict__ dv, int packed, int BH, int Nr, int max_tiles, int n_list, DqMerge dqm) {
+    float* __restrict__ dv, int packed, int BH, int Nr, int max_tiles, int n_list, DqMerge dqm, KeyParts kp) {
   constexpr int NT = 2 * kBwdMfmaThreads, BM = kBwdMfmaBlock;
   constexpr int KS = D / 16, MT = D / 32;
   constexpr int KPT = kBN * D / 8 / NT;
@@ -1004,14 +1046,13 @@ __global__ __launch_bounds__(2 * kBwdMfmaThreads, 1) void k_bwd_dkdv8(
                           perm_token, freq, T);
     return;
   }
-  if (!my_item(items, meta, it) || !bwd_item_ok(it, BH, T, Nr, max_tiles) ||
-      !bwd_key_side_item(it))
-    return;
+  if (!my_item(items, meta, it) || !bwd_item_ok(it, BH, T, Nr, max_tiles)) return;
+  const KeyRange kr = key_range(it);
+  if (kr.slot >= kp.slots) return;
   const int seg0 = it.seg0, n = it.n, tile0 = it.tile0;
-  const int nkb = (n + BM - 1) / BM;
-  const int j0 = (nkb - 1 - it.qb) * BM;
+  const int j0 = kr.j0;
   const int ntiles = (n + kBN - 1) / kBN;
-  const int qt0 = j0 / kBN;
+  const int qt0 = kr.lo, qt1 = kr.hi;   // the item's query tiles
   const int tid = thread_x();
   const int wave = tid / 64, lane = tid % 64;
   const int kgw = wave % 4, qh = wave / 4;   // key group, query half
@@ -1067,11 +1108,11 @@ __global__ __launch_bounds__(2 * kBwdMfmaThreads, 1) void k_bwd_dkdv8(
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) aK[mt][e] = aV[mt][e] = 0.f;
-  for (int qt = qt0; qt < ntiles; ++qt) {
+  for (int qt = qt0; qt < qt1; ++qt) {
     const int st = (qt - qt0) & 1;
     wait_vmcnt<0>();
     __syncthreads();
-    if (qt + 1 < ntiles) issue(qt + 1, st ^ 1);
+    if (qt + 1 < qt1) issue(qt + 1, st ^ 1);
     const int i0 = qt * kBN + 32 * qh_s;   // the wave's first query of the tile
     // its 32 queries against its keys: none visible when they end before
     // the first key
@@ -1134,6 +1175,10 @@ __global__ __launch_bounds__(2 * kBwdMfmaThreads, 1) void k_bwd_dkdv8(
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) mine[mt][e] += take[(mt * 16 + e) * 64 + lane];
+  if (kr.slot >= 0) {   // a part: its sums as they are
+    if (valid) store_row_unrotated<D>(key_part_row(kp, kr.slot, qh, j - j0, D), mine, 1.f, nullptr, 0.0, g);
+    return;
+  }
   if (valid) {
     const int t = min(static_cast<unsigned>(perm_token[seg0 + j]), static_cast<unsigned>(T - 1));
     const size_t o = packed ? static_cast<size_t>(seg0 + j) * D : (static_cast<size_t>(it.s) * T + t) * D;
@@ -1146,6 +1191,62 @@ __global__ __launch_bounds__(2 * kBwdMfmaThreads, 1) void k_bwd_dkdv8(
     } else {
       store_row_unrotated<D>(dv + o, aV, 1.f, nullptr, 0.0, g);   // dv as it is
     }
+  }
+}
+
+// dK and dV rows of the key blocks that ran as query-range parts: the sum of
+// the parts' rows in part order, stored as the key side stores a whole block's
+// (dK times ln 2 and back through the key's rotation).  Units (block, dK or
+// dV, pass of 256 / (D / 8) rows), each thread four pairs (x, x + d/2) of a row.
+constexpr int kKvMergeGroups = 512;
+template <int D>
+__global__ __launch_bounds__(256) void k_bwd_kv_merge(
+    const SplitItem* __restrict__ splits, const int32_t* __restrict__ meta, KeyParts kp,
+    const int32_t* __restrict__ perm_token, const double* __restrict__ freq, int T, int rope_mode,
+    float* __restrict__ dk, float* __restrict__ dv, int packed, int BH, int Nr) {
+  constexpr int BM = kBwdMfmaBlock, TPR = D / 8, RPP = 256 / TPR, NPASS = BM / RPP;
+  const int nsplit = min(max(meta[kMetaSplit], 0), kp.slots / 2);
+  const int tid = thread_x();
+  const int x = 4 * (tid % TPR), rw = tid / TPR;
+  for (int u = block_x(); u < nsplit * 2 * NPASS; u += kKvMergeGroups) {
+    const int i = u / (2 * NPASS), v = u - i * (2 * NPASS), which = v / NPASS;
+    const int ri = (v - which * NPASS) * RPP + rw;
+    const SplitItem si = splits[i];
+    const int j = ((si.n + BM - 1) / BM - 1 - si.qb) * BM + ri;   // the key's rank
+    if (si.qb < 0 || j < 0 || j >= si.n || si.n > T || si.s < 0 || si.s >= BH || si.seg0 < 0 ||
+        si.seg0 > Nr - si.n || si.P < 2 || si.P > kSplitMaxParts || si.base < 0 ||
+        si.base + si.P > kp.slots)
+      continue;
+    float a[4] = {0.f, 0.f, 0.f, 0.f}, b[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int p = 0; p < si.P; ++p) {
+      const float* row = key_part_row(kp, si.base + p, which, ri, D);
+      const float4 u1 = *reinterpret_cast<const float4*>(row + x);
+      const float4 u2 = *reinterpret_cast<const float4*>(row + x + D / 2);
+      a[0] += u1.x; a[1] += u1.y; a[2] += u1.z; a[3] += u1.w;
+      b[0] += u2.x; b[1] += u2.y; b[2] += u2.z; b[3] += u2.w;
+    }
+    const int t = min(static_cast<unsigned>(perm_token[si.seg0 + j]), static_cast<unsigned>(T - 1));
+    if (which == 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        a[e] *= kLn2;
+        b[e] *= kLn2;
+      }
+      if (rope_mode != 2) {
+        const double pos = rope_mode == 0 ? j : t;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float2 w = rope_cs_rev(pos, freq[x + e]);
+          const float d1 = a[e], d2 = b[e];
+          a[e] = d1 * w.x + d2 * w.y;
+          b[e] = d2 * w.x - d1 * w.y;
+        }
+      }
+    }
+    float* dst = (which == 0 ? dk : dv) +
+                 (packed ? static_cast<size_t>(si.seg0 + j) * D : (static_cast<size_t>(si.s) * T + t) * D);
+    *reinterpret_cast<float4*>(dst + x) = make_float4(a[0], a[1], a[2], a[3]);
+    *reinterpret_cast<float4*>(dst + x + D / 2) = make_float4(b[0], b[1], b[2], b[3]);
   }
 }
 
@@ -1181,10 +1282,15 @@ struct BwdMfmaWs {
   float* lse;
   uint16_t *Qs, *dO, *Vp;
   float2* LD;
-  WorkItem* kitems;   // the key side's work list (whole blocks)
+  WorkItem* kitems;   // the key side's work list
   int32_t* kmeta;
+  SplitItem* ksplits; // its blocks that run as parts, and the parts' sums
+  KeyParts kparts;
+  int ksplit_slots;
   size_t rows, bytes;
 };
+
+constexpr int kKeySplitCUs = 256;   // compute units the fair share is taken over
 
 static BwdMfmaWs carve_bwd_mfma(void* ws, int B, int T, int H, int K, int d) {
   const size_t Nr = static_cast<size_t>(B) * T * K;
@@ -1202,6 +1308,10 @@ static BwdMfmaWs carve_bwd_mfma(void* ws, int B, int T, int H, int K, int d) {
   attn_stats_tiles(nullptr, B, T, H, K, d, tl);
   w.kitems = cv.take<WorkItem>(static_cast<size_t>(tl.max_items));
   w.kmeta = cv.take<int32_t>(kMetaCount);
+  w.ksplit_slots = key_split(T) ? kKeySplitCUs * (d == 64 ? BwdMfmaShape<64>::MINB : BwdMfmaShape<128>::MINB) : 0;
+  w.ksplits = cv.take<SplitItem>(static_cast<size_t>(w.ksplit_slots));
+  w.kparts.slots = 2 * w.ksplit_slots;
+  w.kparts.rows = cv.take<float>(static_cast<size_t>(w.kparts.slots) * 2 * kBwdMfmaBlock * d);
   w.bytes = cv.off;
   return w;
 }
@@ -1254,11 +1364,11 @@ static hipError_t run_bwd_mfma(const void* q, const void* k, const void* v, int 
   }
   const double* freq = tl.freq;
   prof_mark("bwd_pack", true, st);
-  // the key side takes whole blocks: its own list, heaviest first, placed for
-  // its own resident workgroups (the query side runs the forward's list with
-  // its key-range parts)
+  // the key side's own list, heaviest first, placed for its own resident
+  // workgroups (the query side runs the forward's list)
   const int cus = bwd_cu_count();
-  const KeyList kl{w.kitems, w.kmeta, tl.max_items, cus, cus * BwdMfmaShape<D>::MINB};
+  const KeyList kl{w.kitems, w.kmeta, tl.max_items, cus, cus * BwdMfmaShape<D>::MINB,
+                   w.ksplit_slots, w.ksplits};
   k_bwd_pack<D><<<static_cast<unsigned>(tl.max_tiles) + 1, kBwdPackThreads, 0, st>>>(
       static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(v), dout, topk_idx, gates,
       seg_offsets, perm_token, freq, tl.h, w.lse, BH, H, T, K, Nr, rope_mode, scale * kLog2e,
@@ -1280,12 +1390,15 @@ static hipError_t run_bwd_mfma(const void* q, const void* k, const void* v, int 
   if constexpr (D == 128)
     k_bwd_dkdv8<D><<<kgrid, 2 * kBwdMfmaThreads, 0, st>>>(
         w.Qs, w.dO, w.LD, tl.Kp, w.Vp, w.kitems, w.kmeta, perm_token, freq, T,
-        rope_mode, dk, dv, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.max_items, dqm);
+        rope_mode, dk, dv, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.max_items, dqm, w.kparts);
   else
     k_bwd_dkdv<D><<<kgrid, kBwdMfmaThreads, 0, st>>>(
         w.Qs, w.dO, w.LD, tl.Kp, w.Vp, w.kitems, w.kmeta, perm_token, freq, T,
-        rope_mode, dk, dv, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.max_items, dqm);
+        rope_mode, dk, dv, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.max_items, dqm, w.kparts);
   prof_mark("bwd_dkdv", false, st);
+  if ((e = hipGetLastError()) != hipSuccess || w.ksplit_slots == 0) return e;
+  k_bwd_kv_merge<D><<<kKvMergeGroups, 256, 0, st>>>(w.ksplits, w.kmeta, w.kparts, perm_token, freq, T,
+                                                    rope_mode, dk, dv, packed ? 1 : 0, BH, Nr);
   return hipGetLastError();
 }
 

@@ -38,7 +38,8 @@ constexpr int kSegLds = 1024;      // segment offsets staged in LDS up to this m
 // gather, first tiles, partial rows) outweighs the balance it buys.  The
 // parts add at most split_slots items, at most 2 split_slots partial slots
 // and at most split_slots split items (sum of w over the split items is at
-// least (number of split items) F, and each adds at most w / F parts).
+// least (number of split items) F, and each adds at most w / F parts); a
+// larger `split_min` only takes items out of that.
 constexpr int kSplitMinTiles = 32;
 constexpr int kSplitMaxParts = 8;
 
@@ -80,8 +81,8 @@ struct SchedLds {
 
 // Parts of an item of w key tiles with fair share F: count P, length L; part
 // p covers [max(0, w - (P - p) L), w - (P - 1 - p) L).
-NAMOH_DEV void split_parts(int w, int F, int& P, int& L) {
-  if (w > F && w >= kSplitMinTiles) {
+NAMOH_DEV void split_parts(int w, int F, int min_tiles, int& P, int& L) {
+  if (w > F && w >= min_tiles) {
     const int P0 = min(kSplitMaxParts, (w + F - 1) / F);
     L = (w + P0 - 1) / P0;
     P = (w + L - 1) / L;
@@ -145,7 +146,8 @@ NAMOH_DEV void attn_schedule(const int32_t* __restrict__ seg_offsets_g, int BH, 
                              int Nr, int max_items, int period, int G,
                              WorkItem* __restrict__ items, int32_t* __restrict__ meta,
                              SchedLds& L, int split_slots = 0,
-                             SplitItem* __restrict__ splits = nullptr, int resident_slots = 0) {
+                             SplitItem* __restrict__ splits = nullptr, int resident_slots = 0,
+                             int split_min = kSplitMinTiles, bool late_pairs = true) {
   static_assert(NT % kWave == 0 && NT / kWave <= 16 && kSortBins % NT == 0, "block size");
   const int tid = thread_x();
   const int lane = tid % kWave, wave = tid / kWave;
@@ -286,7 +288,7 @@ NAMOH_DEV void attn_schedule(const int32_t* __restrict__ seg_offsets_g, int BH, 
       int P = 1, Lp = w;
       if (act) {
         // part 0 holds w - (P - 1) L tiles, parts 1 .. P - 1 L each
-        split_parts(w, F, P, Lp);
+        split_parts(w, F, split_min, P, Lp);
         bin_add(key_of(w - (P - 1) * Lp), G);
         if (P > 1) bin_add(key_of(Lp), (P - 1) * G);
       }
@@ -312,7 +314,7 @@ NAMOH_DEV void attn_schedule(const int32_t* __restrict__ seg_offsets_g, int BH, 
   }
   __syncthreads();
   const int placed = min(total, max_items);
-  const int extra = split_slots > 0 && late_pairs_fit(split_slots, placed - split_slots, period)
+  const int extra = split_slots > 0 && late_pairs && late_pairs_fit(split_slots, placed - split_slots, period)
                         ? placed - split_slots
                         : 0;
   {
@@ -322,7 +324,7 @@ NAMOH_DEV void attn_schedule(const int32_t* __restrict__ seg_offsets_g, int BH, 
       int seg0 = 0, n = 0, w = 0;
       const bool act = c < ncells && cell(c, sg, qb, seg0, n, w);
       int P = 1, Lp = w;
-      if (act) split_parts(w, F, P, Lp);
+      if (act) split_parts(w, F, split_min, P, Lp);
       // a split cell: G split items (one per query head u) with partial slots
       // [base + u P, base + (u + 1) P)
       int base = -1;
