@@ -8,19 +8,17 @@
 // or written.  Eq. namoh-kv-cost: the step reads sum over the selected heads
 // of (n + 1) cached rows, which makes it HBM-bound.
 //
-//   k_decode_route_append  one workgroup per sequence: in every wave lane =
-//                          head, the rank of each head under (logit desc,
-//                          index asc) by H comparisons, gates; then wave w
-//                          handles the selected heads w, w + 4, ...: rotation
-//                          of q and k at rank n (angles in double), the cache
-//                          append and the length update.
 //   k_decode_attn          split over 512-row chunks of every selected head's
-//                          history: 16-byte coalesced loads of K and V rows
-//                          (a row spans d*esize/16 lanes), several rows in
-//                          flight per lane, online softmax in exp2 domain,
+//                          history.  Every workgroup routes its sequence's
+//                          token itself; the one whose chunk the new token
+//                          ends rotates its key (angles in double) and writes
+//                          the cache row.  16-byte coalesced loads of K and V
+//                          rows (a row spans d*esize/16 lanes), several rows
+//                          in flight per lane, online softmax in exp2 domain,
 //                          one (max, sum, acc[d]) partial per chunk.
 //   k_decode_combine       merges the chunk partials of each head by
-//                          log-sum-exp and sums the gated head outputs.
+//                          log-sum-exp, sums the gated head outputs and
+//                          advances the cache lengths.
 //   k_prefill_cache        the prefill -> decode hand-off: every packed
 //                          prompt row (segment b*H + h, rank r, token t)
 //                          writes its rotated key and its value to row r of
@@ -35,8 +33,21 @@
 
 namespace namoh {
 
-constexpr int kDecChunk = 512;   // cached rows per attention workgroup
+constexpr int kDecChunk = 512;   // cached rows per attention workgroup, at most
 constexpr int kDecUnroll = 8;    // rows per lane in flight
+
+// Rows per chunk of a history of L rows with nchunk chunks to spend (512 rows
+// each hold the cache's capacity).  With few workgroups in the launch (`fine`)
+// a short history is spread over all of them, in multiples of 128 rows (a
+// 32-row block per wave of the matrix-core kernel): 8 sequences, 4 of 16
+// groups of 4 heads, 512 rows each, d 128: 16.3 -> 9.7 us.  With the chip full
+// anyway (64 sequences x 8 heads) smaller chunks only add prologues and
+// partials.
+NAMOH_DEV int dec_chunk_rows(int L, int nchunk, int fine) {
+  if (!fine) return kDecChunk;
+  return min(kDecChunk, ((L + nchunk - 1) / nchunk + 127) / 128 * 128);
+}
+constexpr long kDecFineGroups = 1024;   // workgroups of a launch: four per compute unit
 
 template <bool BF16>
 NAMOH_DEV float ld_elem(const void* p, size_t i) {
@@ -50,105 +61,167 @@ NAMOH_DEV void st_elem(void* p, size_t i, float x) {
   else static_cast<float*>(p)[i] = x;
 }
 
-constexpr int kAppendWaves = 4;
+// What a step's attention workgroups need besides the partials.  Routed heads:
+// logits .. topk_idx; shared heads (SHARED): window, every head selected.
+struct DecStep {
+  const float *logits, *bias;
+  const void *q, *k, *v;
+  void *k_cache, *v_cache;
+  const int32_t *cache_len, *seq_pos;
+  int H, K;                // heads, selected heads (shared: Hs, Hs)
+  long cap;
+  double log_base;
+  int rope_mode, gate_mode, window;
+  float qscale;
+  int32_t* topk_idx;
+  float* gates;
+  int32_t* dev_status;
+  int nchunk, fine;        // chunks per head; dec_chunk_rows
+  float *part_acc, *part_ml;
+};
 
-template <int D, bool BF16>
-__global__ __launch_bounds__(64 * kAppendWaves) void k_decode_route_append(
-    const float* __restrict__ logits, const void* __restrict__ q,
-    const void* __restrict__ k, const void* __restrict__ v,
-    void* __restrict__ k_cache, void* __restrict__ v_cache,
-    int32_t* __restrict__ cache_len, const int32_t* __restrict__ seq_pos,
-    int H, int K, long cap, double log_base, int rope_mode, int gate_mode,
-    const float* __restrict__ bias, float qscale, int32_t* __restrict__ topk_idx,
-    float* __restrict__ gates, int32_t* __restrict__ dev_status, float* __restrict__ qrot,
-    int32_t* __restrict__ rows, int G) {
-  const int b = block_x();
+// The head a workgroup (selected head bk, chunk) works on: its history before
+// the new token (rows of it that are read), the first one's ring row, and the
+// new token's row and rotation position.
+struct DecHead {
+  size_t bh;      // b * H + head
+  int hist, ring0, chunk;  // chunk: rows per chunk
+  long slot, pos;
+};
+
+// Every wave finds its workgroup's head by itself (lane = head: one round of
+// loads, then the rank of every head under (logit desc, index asc) by H
+// comparisons), so no launch of its own is needed for the routing.  A step of
+// one sequence with short histories is a chain of latencies: routing and
+// append, attention and combine as three kernels took 5.8 + 5.6 + 3.0 us and
+// two more gaps, now 7.6 + 2.1 us (32 heads, 8 selected, 300 rows, d 64); with
+// 64 sequences 10.3 + 185.3 + 7.4, now 189 + 6.6 us.  The
+// workgroups of chunk 0 write topk_idx, gates and the status.  False: nothing
+// to do (no such head, a full cache, a chunk past the history).
+template <bool SHARED>
+NAMOH_DEV bool dec_head(const DecStep& a, int bk, int chunk, DecHead& o) {
   const int lane = thread_x() % 64;
-  const int wave = thread_x() / 64;
-  const bool real = lane < H;
-  const float l = real ? logits[static_cast<size_t>(b) * H + lane] : 0.f;
-  // selection key: the logit, or with loss-free balancing biases the score
-  // float(a + b) with the affinity a = softmax of the logits in double
-  // (App. "Auxiliary-Loss-Free Balancing", Eq. namoh-biased-routing)
-  float key = l, aff = 0.f;
-  if (bias != nullptr) {
-    float mx = real ? l : -INFINITY;
+  const int b = bk / a.K, kk = bk - (bk / a.K) * a.K;
+  int n;
+  if constexpr (SHARED) {
+    n = a.cache_len[b];
+    const bool over = n < 0 || (a.window == 0 && n >= a.cap);
+    if (over) {
+      if (chunk == 0 && thread_x() == 0 && a.dev_status) a.dev_status[0] = 1;
+      return false;
+    }
+    const int m = a.window > 0 ? min(n + 1, a.window) : n + 1;
+    o.bh = bk;
+    o.hist = m - 1;
+    o.ring0 = static_cast<int>((static_cast<long>(n) + 1 - m) % a.cap);
+    o.slot = n % a.cap;
+    o.pos = n;
+  } else {
+    const bool real = lane < a.H;
+    const size_t bl = static_cast<size_t>(b) * a.H + min(lane, a.H - 1);
+    const float l = real ? a.logits[bl] : 0.f;
+    const int len = a.cache_len[bl];
+    // selection key: the logit, or with loss-free balancing biases the score
+    // float(a + b) with the affinity a = softmax of the logits in double
+    // (App. "Auxiliary-Loss-Free Balancing", Eq. namoh-biased-routing)
+    float key = l, aff = 0.f;
+    if (a.bias != nullptr) {
+      float mx = real ? l : -INFINITY;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    double ex = real ? exp(static_cast<double>(l) - static_cast<double>(mx)) : 0.0;
-    double z = ex;
+      for (int s = 32; s > 0; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s));
+      const double ex = real ? exp(static_cast<double>(l) - static_cast<double>(mx)) : 0.0;
+      double z = ex;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o);
-    const double a = ex / z;
-    aff = static_cast<float>(a);
-    key = real ? static_cast<float>(a + static_cast<double>(bias[lane])) : 0.f;
-  }
-  int rank = 0;
-  for (int j = 0; j < H; ++j) {
-    const float kj = __shfl(key, j);
-    rank += (kj > key) || (kj == key && j < lane);
-  }
-  const bool sel = real && rank < K;
-  const uint64_t first = __ballot(real && rank == 0);
-  const float lmax = __shfl(l, __ffsll(static_cast<long long>(first)) - 1);
-  const float e_sel = sel ? expf(l - lmax) : 0.f;
-  float e_den = gate_mode == 1 ? (real ? expf(l - lmax) : 0.f) : e_sel;
+      for (int s = 32; s > 0; s >>= 1) z += __shfl_xor(z, s);
+      const double af = ex / z;
+      aff = static_cast<float>(af);
+      key = real ? static_cast<float>(af + static_cast<double>(a.bias[min(lane, a.H - 1)])) : 0.f;
+    }
+    int rank = 0;
+    for (int j = 0; j < a.H; ++j) {
+      const float kj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(key), j));
+      rank += (kj > key) || (kj == key && j < lane);
+    }
+    const bool sel = real && rank < a.K;
+    if (kk == 0 && chunk == 0) {
+      const uint64_t first = __ballot(real && rank == 0);
+      const float lmax = __shfl(l, first == 0 ? 0 : __ffsll(static_cast<long long>(first)) - 1);
+      const float e_sel = sel ? expf(l - lmax) : 0.f;
+      float e_den = a.gate_mode == 1 ? (real ? expf(l - lmax) : 0.f) : e_sel;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) e_den += __shfl_xor(e_den, o);
-  if (sel && wave == 0) {
-    topk_idx[static_cast<size_t>(b) * K + rank] = lane;
-    gates[static_cast<size_t>(b) * K + rank] = bias != nullptr ? aff : e_sel / e_den;
-  }
-
-  // every wave routed the token; wave w appends heads w, w + 4, ...
-  for (int kk = wave; kk < K; kk += kAppendWaves) {
-    const uint64_t mk = __ballot(sel && rank == kk);
-    const size_t bk = static_cast<size_t>(b) * K + kk;
-    if (mk == 0) {  // only reachable with NaN logits (outside the contract)
-      if (lane == 0) {
-        rows[bk] = 0;
-        topk_idx[bk] = -1;
-        if (dev_status) dev_status[0] = 2;
+      for (int s = 32; s > 0; s >>= 1) e_den += __shfl_xor(e_den, s);
+      if (sel && thread_x() < 64) {
+        a.topk_idx[static_cast<size_t>(b) * a.K + rank] = lane;
+        a.gates[static_cast<size_t>(b) * a.K + rank] = a.bias != nullptr ? aff : e_sel / e_den;
       }
-      continue;
+    }
+    const uint64_t mk = __ballot(sel && rank == kk);
+    if (mk == 0) {  // only reachable with NaN logits (outside the contract)
+      if (chunk == 0 && thread_x() == 0) {
+        a.topk_idx[bk] = -1;
+        if (a.dev_status) a.dev_status[0] = 2;
+      }
+      return false;
     }
     const int h = __ffsll(static_cast<long long>(mk)) - 1;
-    const size_t bh = static_cast<size_t>(b) * H + h;
-    const int n = cache_len[bh];
-    if (n < 0 || n >= cap) {
-      if (lane == 0) {
-        rows[bk] = 0;
-        if (dev_status) dev_status[0] = 1;
-      }
-      continue;
+    n = __builtin_amdgcn_readlane(len, h);
+    if (n < 0 || n >= a.cap) {
+      if (chunk == 0 && thread_x() == 0 && a.dev_status) a.dev_status[0] = 1;
+      return false;
     }
-    const long pos = rope_mode == 0 ? n : (rope_mode == 1 ? seq_pos[b] : 0);
-    const size_t src = bh * D;
-    const size_t dst = (bh * cap + n) * D;
-    for (int j = lane; j < D / 2; j += 64) {
-      float cs = 1.f, sn = 0.f;
-      if (rope_mode != 2) {
-        const float2 w = rope_cos_sin(static_cast<double>(pos) * exp(-(2.0 * j / D) * log_base));
-        cs = w.x;
-        sn = w.y;
-      }
-      const float k1 = ld_elem<BF16>(k, src + j), k2 = ld_elem<BF16>(k, src + j + D / 2);
-      st_elem<BF16>(k_cache, dst + j, k1 * cs - k2 * sn);
-      st_elem<BF16>(k_cache, dst + j + D / 2, k2 * cs + k1 * sn);
-      st_elem<BF16>(v_cache, dst + j, ld_elem<BF16>(v, src + j));
-      st_elem<BF16>(v_cache, dst + j + D / 2, ld_elem<BF16>(v, src + j + D / 2));
-      // the head's G query heads (G = 1 without key/value groups), rotated at
-      // the same rank
-      for (int u = 0; u < G; ++u) {
-        const size_t qs = (bh * G + u) * D;
-        const float q1 = ld_elem<BF16>(q, qs + j), q2 = ld_elem<BF16>(q, qs + j + D / 2);
-        qrot[(bk * G + u) * D + j] = (q1 * cs - q2 * sn) * qscale;
-        qrot[(bk * G + u) * D + j + D / 2] = (q2 * cs + q1 * sn) * qscale;
-      }
-    }
-    if (lane == 0) {
-      cache_len[bh] = n + 1;
-      rows[bk] = n + 1;
+    o.bh = static_cast<size_t>(b) * a.H + h;
+    o.hist = n;
+    o.ring0 = 0;
+    o.slot = n;
+    o.pos = a.rope_mode == 0 ? n : (a.rope_mode == 1 ? a.seq_pos[b] : 0);
+  }
+  o.chunk = dec_chunk_rows(o.hist + 1, a.nchunk, a.fine);
+  return chunk * o.chunk <= o.hist;
+}
+
+// (cos, sin) of the new token's angles into s_cs, and in the workgroup whose
+// chunk ends with it (`owner`) its rotated key and its value: into the caches
+// and into s_new (key, then value).  Thread j < D / 2 takes pair j.
+template <int D, bool BF16>
+NAMOH_DEV void dec_new_token(const DecStep& a, const DecHead& o, bool owner, float2* s_cs, void* s_new) {
+  const int j = thread_x();
+  if (j >= D / 2) return;
+  const size_t src = o.bh * D;
+  float k1 = 0.f, k2 = 0.f, v1 = 0.f, v2 = 0.f;
+  if (owner) {
+    k1 = ld_elem<BF16>(a.k, src + j);
+    k2 = ld_elem<BF16>(a.k, src + j + D / 2);
+    v1 = ld_elem<BF16>(a.v, src + j);
+    v2 = ld_elem<BF16>(a.v, src + j + D / 2);
+  }
+  float2 w = make_float2(1.f, 0.f);
+  if (a.rope_mode != 2)
+    w = rope_cos_sin(static_cast<double>(o.pos) * exp(-(2.0 * j / D) * a.log_base));
+  s_cs[j] = w;
+  if (owner) {
+    const float r1 = k1 * w.x - k2 * w.y, r2 = k2 * w.x + k1 * w.y;
+    const size_t dst = (o.bh * a.cap + o.slot) * D;
+    st_elem<BF16>(a.k_cache, dst + j, r1);
+    st_elem<BF16>(a.k_cache, dst + j + D / 2, r2);
+    st_elem<BF16>(a.v_cache, dst + j, v1);
+    st_elem<BF16>(a.v_cache, dst + j + D / 2, v2);
+    st_elem<BF16>(s_new, j, r1);
+    st_elem<BF16>(s_new, j + D / 2, r2);
+    st_elem<BF16>(s_new, D + j, v1);
+    st_elem<BF16>(s_new, D + j + D / 2, v2);
+  }
+}
+
+template <bool BF16>
+NAMOH_DEV void dec_unpack(const u32x4 x, float* f) {
+  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (BF16) {
+      f[2 * e] = lo_bf16(w[e]);
+      f[2 * e + 1] = hi_bf16(w[e]);
+    } else {
+      f[e] = __uint_as_float(w[e]);
     }
   }
 }
@@ -157,15 +230,13 @@ __global__ __launch_bounds__(64 * kAppendWaves) void k_decode_route_append(
 // without groups): each row is read once and scored against all of them, with
 // one online softmax per query; the partial of query u of selected head bk is
 // (bk * GQ + u) * nchunk + chunk.
-// RING (shared heads with a window): the caches are rings of cap rows and
-// history row r of bk is physical row (row0[bk] + r) mod cap.
-template <int D, bool BF16, int GQ = 1, bool RING = false>
-__global__ __launch_bounds__(256) void k_decode_attn(
-    const void* __restrict__ k_cache, const void* __restrict__ v_cache,
-    const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ rows,
-    const float* __restrict__ qrot, int H, int K, long cap, int nchunk,
-    float* __restrict__ part_acc, float* __restrict__ part_ml,
-    const int32_t* __restrict__ row0 = nullptr) {
+// SHARED (shared heads): the caches may be rings of cap rows; history row r is
+// physical row (ring0 + r) mod cap.
+// The new token's row is not read from the cache (the workgroup whose chunk it
+// ends writes it): it is scored from LDS after the history.  The first rows of
+// the history are loaded before the new token's angles are formed.
+template <int D, bool BF16, int GQ = 1, bool SHARED = false>
+__global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
   constexpr int EPG = BF16 ? 8 : 4;   // elements per 16-byte granule
   constexpr int G = D / EPG;          // lanes per row
   constexpr int RPW = 64 / G;         // rows per wave per step
@@ -174,28 +245,65 @@ __global__ __launch_bounds__(256) void k_decode_attn(
   constexpr int U = GQ <= 2 ? kDecUnroll : (GQ == 4 ? kDecUnroll / 2 : kDecUnroll / 4);
   __shared__ float s_ml[GQ][RPB][2];
   __shared__ float s_acc[GQ][RPB][D];
+  __shared__ float2 s_cs[D / 2];
+  __shared__ u32x4 s_new[2 * G];
 
-  const int bk = block_x() / nchunk;
-  const int chunk = block_x() - bk * nchunk;
-  const int L = rows[bk];
-  const int r0 = chunk * kDecChunk;
-  if (r0 >= L) return;
-  const int r1 = min(L, r0 + kDecChunk);
-  const int b = bk / K;
-  const int h = topk_idx[bk];
-  const size_t rowbase = (static_cast<size_t>(b) * H + h) * cap;
-  const int ring0 = RING ? row0[bk] : 0;
+  const int bk = block_x() / a.nchunk;
+  const int chunk = block_x() - bk * a.nchunk;
+  DecHead hd;
+  if (!dec_head<SHARED>(a, bk, chunk, hd)) return;
+  const int r0 = chunk * hd.chunk;
+  const int r1 = min(hd.hist, r0 + hd.chunk);   // cached rows [r0, r1)
+  const bool owner = hd.hist < r0 + hd.chunk;   // the new row ends this chunk
+  const size_t rowbase = hd.bh * a.cap;
   const int tid = thread_x();
   const int lane = tid % 64, wave = tid / 64;
   const int sub = lane % G;
   const int grp = wave * RPW + lane / G;
-
+  const u32x4* kc = static_cast<const u32x4*>(a.k_cache);
+  const u32x4* vc = static_cast<const u32x4*>(a.v_cache);
+  u32x4 kx[U], vx[U];
+  auto load_rows = [&](int rb) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = rb + u * RPB + grp;
+      kx[u] = vx[u] = u32x4{0u, 0u, 0u, 0u};
+      if (r < r1) {
+        long pr = r;
+        if constexpr (SHARED) {
+          pr += hd.ring0;
+          if (pr >= a.cap) pr -= a.cap;
+        }
+        const size_t gi = (rowbase + pr) * G + sub;
+        kx[u] = kc[gi];
+        vx[u] = vc[gi];
+      }
+    }
+  };
+  // the lane's granule of each query and its rotation partner's
+  u32x4 qx[GQ], qy[GQ];
+  const int mate = sub < G / 2 ? sub + G / 2 : sub - G / 2;
+#pragma unroll
+  for (int u = 0; u < GQ; ++u) {
+    const u32x4* qrow = static_cast<const u32x4*>(a.q) + (hd.bh * GQ + u) * G;
+    qx[u] = qrow[sub];
+    qy[u] = qrow[mate];
+  }
+  load_rows(r0);
+  dec_new_token<D, BF16>(a, hd, owner, s_cs, s_new);
+  __syncthreads();
   float qv[GQ][EPG];
 #pragma unroll
-  for (int u = 0; u < GQ; ++u)
+  for (int u = 0; u < GQ; ++u) {
+    float x[EPG], y[EPG];
+    dec_unpack<BF16>(qx[u], x);
+    dec_unpack<BF16>(qy[u], y);
 #pragma unroll
-    for (int e = 0; e < EPG; ++e)
-      qv[u][e] = qrot[(static_cast<size_t>(bk) * GQ + u) * D + sub * EPG + e];
+    for (int e = 0; e < EPG; ++e) {
+      const float2 w = s_cs[(sub % (G / 2)) * EPG + e];
+      qv[u][e] = (sub < G / 2 ? x[e] * w.x - y[e] * w.y : x[e] * w.x + y[e] * w.y) * a.qscale;
+    }
+  }
   float m[GQ], lsum[GQ], acc[GQ][EPG];
 #pragma unroll
   for (int u = 0; u < GQ; ++u) {
@@ -205,49 +313,20 @@ __global__ __launch_bounds__(256) void k_decode_attn(
     for (int e = 0; e < EPG; ++e) acc[u][e] = 0.f;
   }
 
-  const u32x4* kc = reinterpret_cast<const u32x4*>(k_cache);
-  const u32x4* vc = reinterpret_cast<const u32x4*>(v_cache);
-  for (int rb = r0; rb < r1; rb += RPB * U) {
-    u32x4 kx[U], vx[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = rb + u * RPB + grp;
-      if (r < r1) {
-        long pr = r;
-        if constexpr (RING) {
-          pr += ring0;
-          if (pr >= cap) pr -= cap;
-        }
-        const size_t gi = (rowbase + pr) * G + sub;
-        kx[u] = kc[gi];
-        vx[u] = vc[gi];
-      } else {
-        kx[u] = u32x4{0u, 0u, 0u, 0u};
-        vx[u] = kx[u];
-      }
-    }
+  // the rows in kx, vx (row u of the lane counts if r + u step < end)
+  auto take_rows = [&](int r, int step, int end) {
     float sc[GQ][U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float f[EPG];
-      if constexpr (BF16) {
-        const uint32_t w[4] = {kx[u].x, kx[u].y, kx[u].z, kx[u].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          f[2 * e] = lo_bf16(w[e]);
-          f[2 * e + 1] = hi_bf16(w[e]);
-        }
-      } else {
-        f[0] = __uint_as_float(kx[u].x); f[1] = __uint_as_float(kx[u].y);
-        f[2] = __uint_as_float(kx[u].z); f[3] = __uint_as_float(kx[u].w);
-      }
+      dec_unpack<BF16>(kx[u], f);
 #pragma unroll
       for (int qq = 0; qq < GQ; ++qq) {
         float dsum = 0.f;
 #pragma unroll
         for (int e = 0; e < EPG; ++e) dsum = fmaf(qv[qq][e], f[e], dsum);
         dsum = group_sum<G>(dsum);
-        sc[qq][u] = (rb + u * RPB + grp < r1) ? dsum : -INFINITY;
+        sc[qq][u] = r + u * step < end ? dsum : -INFINITY;
       }
     }
     float p[GQ][U];
@@ -271,22 +350,23 @@ __global__ __launch_bounds__(256) void k_decode_attn(
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float f[EPG];
-      if constexpr (BF16) {
-        const uint32_t w[4] = {vx[u].x, vx[u].y, vx[u].z, vx[u].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          f[2 * e] = lo_bf16(w[e]);
-          f[2 * e + 1] = hi_bf16(w[e]);
-        }
-      } else {
-        f[0] = __uint_as_float(vx[u].x); f[1] = __uint_as_float(vx[u].y);
-        f[2] = __uint_as_float(vx[u].z); f[3] = __uint_as_float(vx[u].w);
-      }
+      dec_unpack<BF16>(vx[u], f);
 #pragma unroll
       for (int qq = 0; qq < GQ; ++qq)
 #pragma unroll
         for (int e = 0; e < EPG; ++e) acc[qq][e] = fmaf(p[qq][u], f[e], acc[qq][e]);
     }
+  };
+  for (int rb = r0; rb < r1; rb += RPB * U) {
+    if (rb > r0) load_rows(rb);
+    take_rows(rb + grp, RPB, r1);
+  }
+  if (owner && wave == 0) {   // the new token's row, in the first row group
+#pragma unroll
+    for (int u = 0; u < U; ++u) kx[u] = vx[u] = u32x4{0u, 0u, 0u, 0u};
+    kx[0] = s_new[sub];
+    vx[0] = s_new[G + sub];
+    take_rows(grp, 1, 1);
   }
 #pragma unroll
   for (int qq = 0; qq < GQ; ++qq) {
@@ -308,11 +388,11 @@ __global__ __launch_bounds__(256) void k_decode_attn(
       Ls = fmaf(s_ml[qq][gi][1], w, Ls);
       A = fmaf(s_acc[qq][gi][dd], w, A);
     }
-    const size_t pi = (static_cast<size_t>(bk) * GQ + qq) * nchunk + chunk;
-    part_acc[pi * D + dd] = A;
+    const size_t pi = (static_cast<size_t>(bk) * GQ + qq) * a.nchunk + chunk;
+    a.part_acc[pi * D + dd] = A;
     if (dd == 0) {
-      part_ml[2 * pi] = M;
-      part_ml[2 * pi + 1] = Ls;
+      a.part_ml[2 * pi] = M;
+      a.part_ml[2 * pi + 1] = Ls;
     }
   }
 }
@@ -341,17 +421,12 @@ __global__ __launch_bounds__(256) void k_decode_attn(
 // + 3, so a lane's rescale factors apply to its own output accumulators.
 // Partials as in k_decode_attn: (bk * GQ + q) * nchunk + chunk.
 template <int D, int GQ>
-__global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(
-    const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
-    const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ rows,
-    const float* __restrict__ qrot, int H, int K, long cap, int nchunk,
-    float* __restrict__ part_acc, float* __restrict__ part_ml) {
+__global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(const DecStep a) {
   static_assert(GQ == 4 || GQ == 8, "queries per cached row");
   static_assert(D == 64 || D == 128, "head width");
   constexpr int KS = D / 32;           // reduction steps of the score product
   constexpr int NT = D / 16;           // 16-column output tiles
   constexpr int VP = 40;               // padded row length (elements) of the LDS tiles
-  constexpr int RPW = kDecChunk / 4;   // rows per wave
   // the V^T tiles are dead after the loop; the per-wave output rows reuse them
   static_assert(4 * GQ * D * 4 <= 4 * D * VP * 2, "output rows fit the V^T tiles");
   constexpr int KP = D + 8;             // padded key row (elements) of the LDS key tile
@@ -361,44 +436,36 @@ __global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(
   __shared__ __attribute__((aligned(16))) uint16_t s_k[4][32 * KP];
   __shared__ __attribute__((aligned(16))) uint16_t s_p[4][16 * VP];
   __shared__ float s_ml[4][GQ][2];
+  // the new token's factors share the probabilities' tiles (read before the
+  // loop writes those): with 512 bytes more only one workgroup would fit
+  float2* const s_cs = reinterpret_cast<float2*>(&s_p[0][0]);
+  static_assert(sizeof(s_p) >= D / 2 * sizeof(float2), "factors fit");
+  __shared__ u32x4 s_new[2 * GR];
   float (*s_o)[GQ][D] = reinterpret_cast<float (*)[GQ][D]>(&s_vt[0][0]);
 
-  const int bk = block_x() / nchunk;
-  const int chunk = block_x() - bk * nchunk;
-  const int L = rows[bk];
-  const int r0 = chunk * kDecChunk;
-  if (r0 >= L) return;
-  const int r1 = min(L, r0 + kDecChunk);
-  const int b = bk / K;
-  const int h = topk_idx[bk];
-  const size_t rowbase = (static_cast<size_t>(b) * H + h) * cap;
+  const int bk = block_x() / a.nchunk;
+  const int chunk = block_x() - bk * a.nchunk;
+  DecHead hd;
+  if (!dec_head<false>(a, bk, chunk, hd)) return;
+  const int r0 = chunk * hd.chunk;
+  const int n = hd.hist;                       // the new token's row
+  const int r1 = min(n + 1, r0 + hd.chunk);
+  const bool owner = n < r0 + hd.chunk;
+  const size_t rowbase = hd.bh * a.cap;
   const int tid = thread_x();
   const int lane = tid % 64, wave = tid / 64;
   const int j16 = lane & 15, kg = lane >> 4;
-  const int w0 = r0 + wave * RPW;
-  const int w1 = min(r1, w0 + RPW);
+  const int w0 = r0 + wave * (hd.chunk / 4);
+  const int w1 = min(r1, w0 + hd.chunk / 4);
 
-  // A operand rows >= GQ are zero: they read query GQ - 1 and are cleared
-  // after the loads (a load under a branch would be waited for at the join,
-  // one round trip per load)
-  bf16x8 qa[KS];
+  // the lane's queries' granules (A operand rows >= GQ are zero: they read
+  // query GQ - 1 and are cleared after the loads; a load under a branch would
+  // be waited for at the join, one round trip per load)
+  u32x4 qx[KS];
   {
-    const float4* qrow = reinterpret_cast<const float4*>(
-        qrot + (static_cast<size_t>(bk) * GQ + min(j16, GQ - 1)) * D + 8 * kg);
-    float4 f[KS][2];
+    const u32x4* qrow = static_cast<const u32x4*>(a.q) + (hd.bh * GQ + min(j16, GQ - 1)) * GR + kg;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      f[s][0] = qrow[8 * s];
-      f[s][1] = qrow[8 * s + 1];
-    }
-    const bool keep = j16 < GQ;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const float x[8] = {f[s][0].x, f[s][0].y, f[s][0].z, f[s][0].w,
-                          f[s][1].x, f[s][1].y, f[s][1].z, f[s][1].w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) qa[s][e] = static_cast<__bf16>(keep ? x[e] : 0.f);
-    }
+    for (int s = 0; s < KS; ++s) qx[s] = qrow[4 * s];
   }
   float m[4], l[4];
   f32x4 O[NT];
@@ -410,8 +477,8 @@ __global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(
 #pragma unroll
   for (int t = 0; t < NT; ++t) O[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const u32x4* kc = reinterpret_cast<const u32x4*>(k_cache);
-  const u32x4* vc = reinterpret_cast<const u32x4*>(v_cache);
+  const u32x4* kc = static_cast<const u32x4*>(a.k_cache);
+  const u32x4* vc = static_cast<const u32x4*>(a.v_cache);
   uint16_t* vt = s_vt[wave];
   uint16_t* pt = s_p[wave];
   // Coalesced loads: lane (granule lane % GR, row group lane / GR) reads rows
@@ -430,8 +497,35 @@ __global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(
     }
   };
   if (w0 < w1) load_block(w0, kx, vx);
+  dec_new_token<D, true>(a, hd, owner, s_cs, s_new);
+  __syncthreads();
+  // rotated, scaled queries: pair (j, j + D / 2) is granules s and s + KS / 2
+  bf16x8 qa[KS];
+#pragma unroll
+  for (int s = 0; s < KS / 2; ++s) {
+    float x[8], y[8];
+    dec_unpack<true>(qx[s], x);
+    dec_unpack<true>(qx[s + KS / 2], y);
+    const bool keep = j16 < GQ;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float2 w = s_cs[32 * s + 8 * kg + e];
+      qa[s][e] = static_cast<__bf16>(keep ? (x[e] * w.x - y[e] * w.y) * a.qscale : 0.f);
+      qa[s + KS / 2][e] = static_cast<__bf16>(keep ? (y[e] * w.x + x[e] * w.y) * a.qscale : 0.f);
+    }
+  }
+  __syncthreads();
   for (int rb = w0; rb < w1; rb += 32) {
     load_block(min(rb + 32, w1 - 1), kn, vn);
+    if (rb + 32 > n) {   // the new token's row (and rows clamped to it) from LDS
+      const u32x4 nk = s_new[lg], nv = s_new[GR + lg];
+#pragma unroll
+      for (int i = 0; i < RPL; ++i)
+        if (min(rb + RPL * lq + i, w1 - 1) == n) {
+          kx[i] = nk;
+          vx[i] = nv;
+        }
+    }
     // key rows into the wave's LDS tile (row-major, padded rows), values
     // transposed into V^T: lane's RPL consecutive rows of one granule become,
     // per column, one RPL-element run of a V^T row
@@ -525,31 +619,33 @@ __global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(
       Ls = fmaf(s_ml[w][q][1], sc, Ls);
       A = fmaf(s_o[w][q][dd], sc, A);
     }
-    const size_t pi = (static_cast<size_t>(bk) * GQ + q) * nchunk + chunk;
-    part_acc[pi * D + dd] = A;
+    const size_t pi = (static_cast<size_t>(bk) * GQ + q) * a.nchunk + chunk;
+    a.part_acc[pi * D + dd] = A;
     if (dd == 0) {
-      part_ml[2 * pi] = M;
-      part_ml[2 * pi + 1] = Ls;
+      a.part_ml[2 * pi] = M;
+      a.part_ml[2 * pi + 1] = Ls;
     }
   }
 }
 
-// One workgroup per sequence; wave w merges the chunk partials of heads
-// w, w + 4, ... (lane c holds chunk c's max and sum; the accumulators are
-// read column-wise, d = lane + 64 i), then the gated head outputs are summed
-// in head order.
-// With key/value groups (G query heads per selected head) the G heads of a
-// slot share its gate and are summed in head order.
-template <int D, bool OUT_BF16>
-__global__ __launch_bounds__(256) void k_decode_combine(
-    const float* __restrict__ gates, const int32_t* __restrict__ rows,
-    const float* __restrict__ part_acc, const float* __restrict__ part_ml,
-    int K, int nchunk, void* __restrict__ out, int G, int accumulate = 0) {
-  constexpr int NWV = 4;
+// One workgroup per sequence; wave w merges the chunk partials of the heads w,
+// w + NWV, ... (lane c holds chunk c's max and sum; the accumulators are read
+// column-wise, d = lane + 64 i), then the gated head outputs are summed in
+// head order.  With key/value groups (G query heads per selected head) the G
+// heads of a slot share its gate and are summed in head order.  Shared heads
+// (SHARED): every head, gate 1, one length per sequence.  The cache lengths
+// are advanced here, after every wave (and the attention) has read them.
+template <int D, bool OUT_BF16, int NWV, bool SHARED>
+__global__ __launch_bounds__(64 * NWV) void k_decode_combine(
+    const float* __restrict__ gates, const int32_t* __restrict__ topk_idx, int32_t* cache_len,
+    const float* __restrict__ part_acc, const float* __restrict__ part_ml, int H, int K, long cap,
+    int window, int nchunk, int fine, void* __restrict__ out, int G, int accumulate) {
   constexpr int DPL = (D + 63) / 64;  // output columns per lane
   __shared__ float s_o[NWV][D];
   const int b = block_x();
-  const int lane = thread_x() % 64, wave = thread_x() / 64;
+  const int tid = thread_x(), lane = tid % 64, wave = tid / 64;
+  int32_t* len = SHARED ? cache_len + b : cache_len + static_cast<size_t>(b) * H;
+  const int len_l = SHARED ? len[0] : len[min(lane, H - 1)];   // lane = head
   float o[DPL];
 #pragma unroll
   for (int i = 0; i < DPL; ++i) o[i] = 0.f;
@@ -557,29 +653,45 @@ __global__ __launch_bounds__(256) void k_decode_combine(
     const int kk = vk / G;
     const size_t bk = static_cast<size_t>(b) * K + kk;
     const size_t bq = bk * G + (vk - kk * G);   // the head's partials
-    const int L = rows[bk];
+    // the first 64 chunks' (max, sum) and the first chunk's row are loaded
+    // before the history's length is known (past it they are not used)
+    const float2* ml = reinterpret_cast<const float2*>(part_ml) + bq * nchunk;
+    const float* pa = part_acc + bq * nchunk * D;
+    const float2 ml0 = ml[min(lane, nchunk - 1)];
+    float a0[DPL];
+#pragma unroll
+    for (int i = 0; i < DPL; ++i) a0[i] = pa[min(lane + 64 * i, D - 1)];
+    float gate = 1.f;
+    int L;
+    if constexpr (SHARED) {
+      const int p = len_l;
+      L = p < 0 || (window == 0 && p >= cap) ? 0 : (window > 0 ? min(p + 1, window) : p + 1);
+    } else {
+      gate = gates[bk];
+      const int h = __builtin_amdgcn_readfirstlane(topk_idx[bk]);
+      const int n = h >= 0 && h < H ? __builtin_amdgcn_readlane(len_l, h) : -1;
+      L = n >= 0 && n < cap ? n + 1 : 0;
+    }
     if (L == 0) continue;
-    const int nc = (L + kDecChunk - 1) / kDecChunk;
-    const float* ml = part_ml + bq * nchunk * 2;
-    float M = -1e30f;
-    for (int c = lane; c < nc; c += 64) M = fmaxf(M, ml[2 * c]);
+    const int rows = dec_chunk_rows(L, nchunk, fine);
+    const int nc = (L + rows - 1) / rows;
+    float M = lane < nc ? ml0.x : -1e30f;
+    for (int c = lane + 64; c < nc; c += 64) M = fmaxf(M, ml[c].x);
     M = group_max<64>(M);
-    float Ls = 0.f;
-    for (int c = lane; c < nc; c += 64) Ls += ml[2 * c + 1] * __builtin_amdgcn_exp2f(ml[2 * c] - M);
+    float Ls = lane < nc ? ml0.y * __builtin_amdgcn_exp2f(ml0.x - M) : 0.f;
+    for (int c = lane + 64; c < nc; c += 64) Ls += ml[c].y * __builtin_amdgcn_exp2f(ml[c].x - M);
     Ls = group_sum<64>(Ls);
-    const float scale = gates[bk] / Ls;
+    const float scale = gate / Ls;
+    float w = __builtin_amdgcn_exp2f(__shfl(ml0.x, 0) - M);
     float a[DPL];
 #pragma unroll
-    for (int i = 0; i < DPL; ++i) a[i] = 0.f;
-    const float* pa = part_acc + bq * nchunk * D;
-#pragma unroll 4
-    for (int c = 0; c < nc; ++c) {
-      const float w = __builtin_amdgcn_exp2f(ml[2 * c] - M);
+    for (int i = 0; i < DPL; ++i) a[i] = a0[i] * w;
+#pragma unroll 8
+    for (int c = 1; c < nc; ++c) {
+      w = __builtin_amdgcn_exp2f(ml[c].x - M);
 #pragma unroll
-      for (int i = 0; i < DPL; ++i) {
-        const int d = lane + 64 * i;
-        if (d < D) a[i] = fmaf(pa[static_cast<size_t>(c) * D + d], w, a[i]);
-      }
+      for (int i = 0; i < DPL; ++i)
+        a[i] = fmaf(pa[static_cast<size_t>(c) * D + min(lane + 64 * i, D - 1)], w, a[i]);
     }
 #pragma unroll
     for (int i = 0; i < DPL; ++i) o[i] = fmaf(a[i], scale, o[i]);
@@ -589,18 +701,44 @@ __global__ __launch_bounds__(256) void k_decode_combine(
     const int d = lane + 64 * i;
     if (d < D) s_o[wave][d] = o[i];
   }
-  __syncthreads();
-  if (thread_x() < D) {
-    const size_t oi = static_cast<size_t>(b) * D + thread_x();
+  __syncthreads();   // every wave has read the lengths
+  if constexpr (SHARED) {
+    if (tid == 0 && len_l >= 0 && (window > 0 || len_l < cap)) len[0] = len_l + 1;
+  } else if (tid < K) {
+    const int h = topk_idx[static_cast<size_t>(b) * K + tid];
+    if (h >= 0 && h < H) {
+      const int n = len[h];
+      if (n >= 0 && n < cap) len[h] = n + 1;
+    }
+  }
+  if (tid < D) {
+    const size_t oi = static_cast<size_t>(b) * D + tid;
     float r = 0.f;
     if (accumulate) {   // added to what out holds (shared heads after the routed step)
       if constexpr (OUT_BF16) r = bf16_to_f32(static_cast<const uint16_t*>(out)[oi]);
       else r = static_cast<const float*>(out)[oi];
     }
 #pragma unroll
-    for (int w = 0; w < NWV; ++w) r += s_o[w][thread_x()];
+    for (int w = 0; w < NWV; ++w) r += s_o[w][tid];
     if constexpr (OUT_BF16) static_cast<uint16_t*>(out)[oi] = f32_to_bf16(r);
     else static_cast<float*>(out)[oi] = r;
+  }
+}
+
+template <int D, bool SHARED>
+static void launch_dec_combine(const DecStep& a, int32_t* cache_len, int B, int G, void* out,
+                               int out_dtype, int accumulate, hipStream_t st) {
+  auto run = [&](auto kernel, int nwv) {
+    kernel<<<B, 64 * nwv, 0, st>>>(a.gates, a.topk_idx, cache_len, a.part_acc, a.part_ml, a.H, a.K,
+                                   a.cap, a.window, a.nchunk, a.fine, out, G, accumulate);
+  };
+  // a wave per head while there are up to 8; 16 waves for more
+  if (a.K * G <= 8) {
+    if (out_dtype == 1) run(k_decode_combine<D, true, 8, SHARED>, 8);
+    else run(k_decode_combine<D, false, 8, SHARED>, 8);
+  } else {
+    if (out_dtype == 1) run(k_decode_combine<D, true, 16, SHARED>, 16);
+    else run(k_decode_combine<D, false, 16, SHARED>, 16);
   }
 }
 
@@ -829,29 +967,17 @@ static hipError_t run_decode(const float* logits, const float* bias, const void*
   const DecWs w = carve_dec(ws, B, K, D, cap, GQ);
   const int nc = dec_nchunk(cap);
   const double log_base = rope_mode == 2 ? 0.0 : std::log(static_cast<double>(rope_base));
-  k_decode_route_append<D, BF16><<<B, 64 * kAppendWaves, 0, st>>>(
-      logits, q, k, v, k_cache, v_cache, cache_len, seq_pos, H, K, cap, log_base,
-      rope_mode, gate_mode, bias, scale * 1.4426950408889634f, topk_idx, gates,
-      dev_status, w.qrot, w.rows, GQ);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const size_t grid = static_cast<size_t>(B) * K * nc;
+  const DecStep a{logits, bias, q, k, v, k_cache, v_cache, cache_len, seq_pos, H, K, cap, log_base,
+                  rope_mode, gate_mode, 0, scale * 1.4426950408889634f, topk_idx, gates, dev_status,
+                  nc, static_cast<long>(B) * K * nc <= kDecFineGroups, w.part_acc, w.part_ml};
+  const dim3 grid(static_cast<unsigned>(static_cast<size_t>(B) * K * nc));
   if constexpr (BF16 && (GQ == 4 || GQ == 8))
-    launch_k("decode_attn", k_decode_attn_mfma<D, GQ>, dim3(static_cast<unsigned>(grid)),
-             dim3(256), st, static_cast<const uint16_t*>(k_cache),
-             static_cast<const uint16_t*>(v_cache), topk_idx, w.rows, w.qrot, H, K, cap, nc,
-             w.part_acc, w.part_ml);
+    launch_k("decode_attn", k_decode_attn_mfma<D, GQ>, grid, dim3(256), st, a);
   else
-    launch_k("decode_attn", k_decode_attn<D, BF16, GQ>, dim3(static_cast<unsigned>(grid)),
-             dim3(256), st, k_cache, v_cache, topk_idx, w.rows, w.qrot, H, K, cap, nc,
-             w.part_acc, w.part_ml, static_cast<const int32_t*>(nullptr));
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (out_dtype == 1)
-    k_decode_combine<D, true><<<B, 256, 0, st>>>(gates, w.rows, w.part_acc, w.part_ml, K, nc, out,
-                                                GQ);
-  else
-    k_decode_combine<D, false><<<B, 256, 0, st>>>(gates, w.rows, w.part_acc, w.part_ml, K, nc,
-                                                 out, GQ);
+    launch_k("decode_attn", k_decode_attn<D, BF16, GQ>, grid, dim3(256), st, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  launch_dec_combine<D, false>(a, cache_len, B, GQ, out, out_dtype, 0, st);
   return hipGetLastError();
 }
 
@@ -866,64 +992,9 @@ static hipError_t run_decode(const float* logits, const float* bias, const void*
 // tokens; without one row p must exist (p < cap), else the step skips the
 // sequence and reports it.
 //
-//   k_shared_decode_append  one workgroup per sequence: wave w takes heads
-//                           w, w + 4, ...: rotation (angles in double), the
-//                           cache rows, the scaled rotated query, and the
-//                           history each head reads (length, first ring row).
-//   k_decode_attn<…, RING>  the routed step's split-K attention over those
-//                           histories.
-//   k_decode_combine        the routed step's merge, gates 1, added to out.
-template <int D, bool BF16>
-__global__ __launch_bounds__(64 * kAppendWaves) void k_shared_decode_append(
-    const void* __restrict__ q, const void* __restrict__ k, const void* __restrict__ v,
-    void* __restrict__ k_cache, void* __restrict__ v_cache, int32_t* __restrict__ cache_len,
-    int Hs, long cap, int window, double log_base, int rope_mode, float qscale,
-    int32_t* __restrict__ dev_status, float* __restrict__ qrot, int32_t* __restrict__ rows,
-    int32_t* __restrict__ row0, int32_t* __restrict__ heads, float* __restrict__ gates) {
-  const int b = block_x();
-  const int lane = thread_x() % 64, wave = thread_x() / 64;
-  const int p = cache_len[b];
-  const bool over = p < 0 || (window == 0 && p >= cap);
-  const int m = over ? 0 : (window > 0 ? min(p + 1, window) : p + 1);
-  const long slot = over ? 0 : p % cap;
-  for (int s = wave; s < Hs; s += kAppendWaves) {
-    const size_t bs = static_cast<size_t>(b) * Hs + s;
-    if (lane == 0) {
-      rows[bs] = m;
-      row0[bs] = over ? 0 : static_cast<int>((static_cast<long>(p) + 1 - m) % cap);
-      heads[bs] = s;
-      gates[bs] = 1.f;
-    }
-    if (over) continue;
-    const size_t src = bs * D;
-    const size_t dst = (bs * cap + slot) * D;
-    for (int j = lane; j < D / 2; j += 64) {
-      float cs = 1.f, sn = 0.f;
-      if (rope_mode != 2) {
-        const float2 w = rope_cos_sin(static_cast<double>(p) * exp(-(2.0 * j / D) * log_base));
-        cs = w.x;
-        sn = w.y;
-      }
-      const float k1 = ld_elem<BF16>(k, src + j), k2 = ld_elem<BF16>(k, src + j + D / 2);
-      st_elem<BF16>(k_cache, dst + j, k1 * cs - k2 * sn);
-      st_elem<BF16>(k_cache, dst + j + D / 2, k2 * cs + k1 * sn);
-      st_elem<BF16>(v_cache, dst + j, ld_elem<BF16>(v, src + j));
-      st_elem<BF16>(v_cache, dst + j + D / 2, ld_elem<BF16>(v, src + j + D / 2));
-      const float q1 = ld_elem<BF16>(q, src + j), q2 = ld_elem<BF16>(q, src + j + D / 2);
-      qrot[src + j] = (q1 * cs - q2 * sn) * qscale;
-      qrot[src + j + D / 2] = (q2 * cs + q1 * sn) * qscale;
-    }
-  }
-  __syncthreads();   // every wave has read cache_len[b]
-  if (thread_x() == 0) {
-    if (over) {
-      if (dev_status) dev_status[0] = 1;
-    } else {
-      cache_len[b] = p + 1;
-    }
-  }
-}
-
+// The kernels are the routed step's (k_decode_attn and k_decode_combine with
+// SHARED): every head of the sequence, its new row at the ring slot, gates 1,
+// added to out.
 // Prefill -> decode hand-off of the shared heads: token t of the prompt
 // (rotated at t, or not at all) goes to row t mod cap of every shared head's
 // caches, for the last min(T, cap) tokens (with a window the earlier ones are
@@ -996,22 +1067,15 @@ static hipError_t run_shared_decode(const void* q, const void* k, const void* v,
   const SharedDecWs w = carve_shared_dec(ws, B, Hs, D, cap);
   const int nc = dec_nchunk(cap);
   const double log_base = rope_mode == 2 ? 0.0 : std::log(static_cast<double>(rope_base));
-  k_shared_decode_append<D, BF16><<<B, 64 * kAppendWaves, 0, st>>>(
-      q, k, v, k_cache, v_cache, cache_len, Hs, cap, window, log_base, rope_mode,
-      scale * 1.4426950408889634f, dev_status, w.qrot, w.rows, w.row0, w.heads, w.gates);
-  hipError_t e = hipGetLastError();
+  const DecStep a{nullptr, nullptr, q, k, v, k_cache, v_cache, cache_len, nullptr, Hs, Hs, cap,
+                  log_base, rope_mode, 0, window, scale * 1.4426950408889634f, nullptr, nullptr,
+                  dev_status, nc, static_cast<long>(B) * Hs * nc <= kDecFineGroups, w.part_acc,
+                  w.part_ml};
+  const dim3 grid(static_cast<unsigned>(static_cast<size_t>(B) * Hs * nc));
+  launch_k("decode_attn", k_decode_attn<D, BF16, 1, true>, grid, dim3(256), st, a);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const size_t grid = static_cast<size_t>(B) * Hs * nc;
-  launch_k("decode_attn", k_decode_attn<D, BF16, 1, true>, dim3(static_cast<unsigned>(grid)),
-           dim3(256), st, k_cache, v_cache, w.heads, w.rows, w.qrot, Hs, Hs, cap, nc, w.part_acc,
-           w.part_ml, w.row0);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (out_dtype == 1)
-    k_decode_combine<D, true><<<B, 256, 0, st>>>(w.gates, w.rows, w.part_acc, w.part_ml, Hs, nc,
-                                                out, 1, accumulate);
-  else
-    k_decode_combine<D, false><<<B, 256, 0, st>>>(w.gates, w.rows, w.part_acc, w.part_ml, Hs, nc,
-                                                 out, 1, accumulate);
+  launch_dec_combine<D, true>(a, cache_len, B, 1, out, out_dtype, accumulate, st);
   return hipGetLastError();
 }
 
