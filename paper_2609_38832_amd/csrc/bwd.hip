@@ -576,35 +576,44 @@ NAMOH_DEV void store_row_unrotated(float* __restrict__ dst, const f32x16 (&acc)[
 }
 
 // Zero rows of the dense gradients for the (token, head) pairs the routing
-// did not select (the others are written by the MFMA kernels): one float4
-// of a row per thread, rows of D / 4 threads.
+// did not select (the others are written by the MFMA kernels): the share of
+// workgroup `group` of z.groups.  A unit is 256 / (D / 4) tokens of a sequence
+// in every head: the tokens' selections are read once, as a bit mask, and each
+// head's rows go out as one run of 4 KB.
 constexpr int kZeroThreads = 256;
+struct ZeroRows {
+  const int32_t* topk_idx;
+  float *dq, *dk, *dv;
+  int B, H, K, groups;
+};
 template <int D>
-__global__ __launch_bounds__(kZeroThreads) void k_bwd_zero_unrouted(
-    const int32_t* __restrict__ topk_idx, int H, int T, int K, size_t rows,
-    float* __restrict__ dq, float* __restrict__ dk, float* __restrict__ dv) {
+NAMOH_DEV void zero_unrouted(const ZeroRows& z, int T, int group) {
   constexpr int C4 = D / 4, RPB = kZeroThreads / C4;
-  const size_t row = static_cast<size_t>(block_x()) * RPB + thread_x() / C4;
+  const int per_seq = (T + RPB - 1) / RPB;
   const int c4 = thread_x() % C4;
-  if (row >= rows) return;
-  const size_t bh = row / T;
-  const int t = static_cast<int>(row - bh * T);
-  const int b = static_cast<int>(bh / H), h = static_cast<int>(bh - (bh / H) * H);
-  const int32_t* tk = topk_idx + (static_cast<size_t>(b) * T + t) * K;
-  bool routed = false;
-  for (int k0 = 0; k0 < K; k0 += 8) {   // eight independent loads per round
-    int sv[8];
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int u = group; u < z.B * per_seq; u += z.groups) {
+    const int b = u / per_seq;
+    const int t = (u - b * per_seq) * RPB + thread_x() / C4;
+    if (t >= T) continue;
+    const int32_t* tk = z.topk_idx + (static_cast<size_t>(b) * T + t) * z.K;
+    uint64_t routed = 0;
+    for (int k0 = 0; k0 < z.K; k0 += 8) {   // eight independent loads per round
+      int sv[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) sv[u] = tk[min(k0 + u, K - 1)];
+      for (int i = 0; i < 8; ++i) sv[i] = tk[min(k0 + i, z.K - 1)];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) routed |= sv[u] == h;   // clamped repeats change nothing
+      for (int i = 0; i < 8; ++i)   // clamped repeats change nothing
+        if (static_cast<unsigned>(sv[i]) < 64u) routed |= 1ull << sv[i];
+    }
+    for (int h = 0; h < z.H; ++h) {
+      if ((routed >> h) & 1) continue;
+      const size_t o = ((static_cast<size_t>(b) * z.H + h) * T + t) * D + 4 * c4;
+      *reinterpret_cast<float4*>(z.dq + o) = zero;
+      *reinterpret_cast<float4*>(z.dk + o) = zero;
+      *reinterpret_cast<float4*>(z.dv + o) = zero;
+    }
   }
-  if (routed) return;
-  const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-  const size_t o = row * D + 4 * c4;
-  *reinterpret_cast<float4*>(dq + o) = z;
-  *reinterpret_cast<float4*>(dk + o) = z;
-  *reinterpret_cast<float4*>(dv + o) = z;
 }
 
 template <int D> struct BwdMfmaShape {
@@ -661,8 +670,9 @@ __global__ __launch_bounds__(kBwdMfmaThreads, BwdMfmaShape<D>::MINB_Q) void k_bw
     const int32_t* __restrict__ meta,
     const int32_t* __restrict__ perm_token, const double* __restrict__ freq, int T,
     int rope_mode, float scale, float* __restrict__ dq, int packed, int BH, int Nr,
-    int max_tiles, float* __restrict__ part, int part_rows) {
+    int max_tiles, float* __restrict__ part, int part_rows, ZeroRows zero) {
   constexpr int NT = kBwdMfmaThreads, BM = kBwdMfmaBlock;
+  static_assert(NT == kZeroThreads, "one launch for both");
   constexpr int KS = D / 16, MT = D / 32;
   constexpr int KPT = kBN * D / 8 / NT;
   constexpr size_t TS = static_cast<size_t>(kBN) * D;
@@ -671,8 +681,13 @@ __global__ __launch_bounds__(kBwdMfmaThreads, BwdMfmaShape<D>::MINB_Q) void k_bw
   // transposed (64 KB per workgroup at d = 128)
   __shared__ __attribute__((aligned(16))) uint16_t sK[2][kBN * D];
   __shared__ __attribute__((aligned(16))) uint16_t sV[2][kBN * D];
+  if (block_x() < zero.groups) {
+    zero_unrouted<D>(zero, T, block_x());
+    return;
+  }
+  const int block = block_x() - zero.groups;
   WorkItem it;
-  if (!my_item(items, meta, it) || !bwd_item_ok(it, BH, T, Nr, max_tiles)) return;
+  if (!my_item(items, meta, it, block) || !bwd_item_ok(it, BH, T, Nr, max_tiles)) return;
   // a key-range part of a split block adds its keys' share of dQ~ to the
   // block's partial rows (summed by the key-side kernel's merge workgroups)
   const int slot = item_slot(it.qh);
@@ -1355,13 +1370,6 @@ static hipError_t run_bwd_mfma(const void* q, const void* k, const void* v, int 
   if (e != hipSuccess) return e;
   if (tl.BM != kBwdMfmaBlock || static_cast<size_t>(tl.max_tiles) * kBN > w.rows)
     return hipErrorInvalidValue;   // the forward's blocks and tiles must match these kernels
-  if (!packed) {   // dense gradients: rows of tokens not routed to the head are zero
-    const size_t rows = static_cast<size_t>(BH) * T;
-    constexpr int RPB = kZeroThreads / (D / 4);
-    k_bwd_zero_unrouted<D><<<static_cast<unsigned>((rows + RPB - 1) / RPB), kZeroThreads, 0,
-                             st>>>(topk_idx, H, T, K, rows, dq, dk, dv);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
   const double* freq = tl.freq;
   prof_mark("bwd_pack", true, st);
   // the key side's own list, heaviest first, placed for its own resident
@@ -1376,9 +1384,21 @@ static hipError_t run_bwd_mfma(const void* q, const void* k, const void* v, int 
   prof_mark("bwd_pack", false, st);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   prof_mark("bwd_dq", true, st);
-  k_bwd_dq<D><<<static_cast<unsigned>(tl.max_items), kBwdMfmaThreads, 0, st>>>(
+  // Dense gradients: rows of tokens not routed to the head are zero, written
+  // by the query side's first workgroups, one on every other CU, beside the
+  // matrix work.  As a launch of its own the fill ran at the memory's rate with
+  // the matrix cores idle (71 us of a step at T 12289, H 32, K 4, d 128).
+  // Backward, fill launched before -> 128 workgroups first: T 12289 skewed, d 128
+  // 536 -> 492 us; B 4, T 4096, K 8, d 64 201 -> 193; B 2, T 3001, K 8, d 128
+  // 155 -> 147; T 200, d 64 21.7 -> 19.3.  256 first: 508, 193, 145; 64 first
+  // 5 % and 10 % behind 128 on the first two; 256 last: 526, 207, 145.
+  constexpr int RPB = kZeroThreads / (D / 4);
+  const long units = static_cast<long>(B) * ((T + RPB - 1) / RPB);
+  const ZeroRows zero{topk_idx, dq, dk, dv, B, H, K,
+                      packed ? 0 : static_cast<int>(std::min<long>(units, std::max(cus / 2, 1)))};
+  k_bwd_dq<D><<<static_cast<unsigned>(tl.max_items + zero.groups), kBwdMfmaThreads, 0, st>>>(
       w.Qs, w.dO, w.LD, tl.Kp, w.Vp, tl.items, tl.meta, perm_token, freq, T, rope_mode,
-      scale, dq, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.part, tl.part_rows);
+      scale, dq, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.part, tl.part_rows, zero);
   prof_mark("bwd_dq", false, st);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   prof_mark("bwd_dkdv", true, st);

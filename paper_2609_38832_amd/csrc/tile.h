@@ -58,9 +58,9 @@ struct SplitItem {
 // together with the item count (the grid has max_items workgroups, so the
 // read is in bounds either way).
 NAMOH_DEV bool my_item(const WorkItem* __restrict__ items, const int32_t* __restrict__ meta,
-                       WorkItem& it) {
+                       WorkItem& it, int block = block_x()) {
   const int cnt = meta[kMetaItems];
-  const WorkItem v = items[block_x()];
+  const WorkItem v = items[block];
   // the record is the same for the whole workgroup: keep it in scalar registers
   it.s = __builtin_amdgcn_readfirstlane(v.s);
   it.qb = __builtin_amdgcn_readfirstlane(v.qb);
@@ -70,7 +70,7 @@ NAMOH_DEV bool my_item(const WorkItem* __restrict__ items, const int32_t* __rest
   it.qh = __builtin_amdgcn_readfirstlane(v.qh);
   it.kt_lo = __builtin_amdgcn_readfirstlane(v.kt_lo);
   it.kt_hi = __builtin_amdgcn_readfirstlane(v.kt_hi);
-  return block_x() < __builtin_amdgcn_readfirstlane(cnt);
+  return block < __builtin_amdgcn_readfirstlane(cnt);
 }
 
 NAMOH_DEV void unpack8(const uint4 x, float* f) {
