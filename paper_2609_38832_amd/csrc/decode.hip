@@ -8,7 +8,7 @@
 // or written.  Eq. namoh-kv-cost: the step reads sum over the selected heads
 // of (n + 1) cached rows, which makes it HBM-bound.
 //
-//   k_decode_attn          split over 512-row chunks of every selected head's
+//   k_decode_attn          split over chunks (up to 512 rows) of every selected head's
 //                          history.  Every workgroup routes its sequence's
 //                          token itself; the one whose chunk the new token
 //                          ends rotates its key (angles in double) and writes
@@ -38,14 +38,18 @@ constexpr int kDecUnroll = 8;    // rows per lane in flight
 
 // Rows per chunk of a history of L rows with nchunk chunks to spend (512 rows
 // each hold the cache's capacity).  With few workgroups in the launch (`fine`)
-// a short history is spread over all of them, in multiples of 128 rows (a
-// 32-row block per wave of the matrix-core kernel): 8 sequences, 4 of 16
-// groups of 4 heads, 512 rows each, d 128: 16.3 -> 9.7 us.  With the chip full
-// anyway (64 sequences x 8 heads) smaller chunks only add prologues and
-// partials.
+// a short history is spread over all of them, in multiples of 64 KB of keys
+// and values in bf16 (128 rows at d = 128, a 32-row block per wave of the
+// matrix-core kernel): 8 sequences, 4 of 16 groups of 4 heads, 512 rows each,
+// d 128: 16.3 -> 9.7 us.  Smaller chunks only add prologues and partials: 4
+// sequences, 8 heads of 900 rows, d 64, in 256 rows 9.9 us, in 128 rows 10.8;
+// and so do they with the chip full anyway (64 sequences x 8 heads).
+constexpr int dec_min_rows(int d) { return 16384 / d; }
+template <int D>
 NAMOH_DEV int dec_chunk_rows(int L, int nchunk, int fine) {
+  constexpr int R = dec_min_rows(D);
   if (!fine) return kDecChunk;
-  return min(kDecChunk, ((L + nchunk - 1) / nchunk + 127) / 128 * 128);
+  return min(kDecChunk, ((L + nchunk - 1) / nchunk + R - 1) / R * R);
 }
 constexpr long kDecFineGroups = 1024;   // workgroups of a launch: four per compute unit
 
@@ -98,7 +102,7 @@ struct DecHead {
 // 64 sequences 10.3 + 185.3 + 7.4, now 189 + 6.6 us.  The
 // workgroups of chunk 0 write topk_idx, gates and the status.  False: nothing
 // to do (no such head, a full cache, a chunk past the history).
-template <bool SHARED>
+template <int D, bool SHARED>
 NAMOH_DEV bool dec_head(const DecStep& a, int bk, int chunk, DecHead& o) {
   const int lane = thread_x() % 64;
   const int b = bk / a.K, kk = bk - (bk / a.K) * a.K;
@@ -175,7 +179,7 @@ NAMOH_DEV bool dec_head(const DecStep& a, int bk, int chunk, DecHead& o) {
     o.slot = n;
     o.pos = a.rope_mode == 0 ? n : (a.rope_mode == 1 ? a.seq_pos[b] : 0);
   }
-  o.chunk = dec_chunk_rows(o.hist + 1, a.nchunk, a.fine);
+  o.chunk = dec_chunk_rows<D>(o.hist + 1, a.nchunk, a.fine);
   return chunk * o.chunk <= o.hist;
 }
 
@@ -251,7 +255,7 @@ __global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
   const int bk = block_x() / a.nchunk;
   const int chunk = block_x() - bk * a.nchunk;
   DecHead hd;
-  if (!dec_head<SHARED>(a, bk, chunk, hd)) return;
+  if (!dec_head<D, SHARED>(a, bk, chunk, hd)) return;
   const int r0 = chunk * hd.chunk;
   const int r1 = min(hd.hist, r0 + hd.chunk);   // cached rows [r0, r1)
   const bool owner = hd.hist < r0 + hd.chunk;   // the new row ends this chunk
@@ -446,7 +450,7 @@ __global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(const DecStep a) {
   const int bk = block_x() / a.nchunk;
   const int chunk = block_x() - bk * a.nchunk;
   DecHead hd;
-  if (!dec_head<false>(a, bk, chunk, hd)) return;
+  if (!dec_head<D, false>(a, bk, chunk, hd)) return;
   const int r0 = chunk * hd.chunk;
   const int n = hd.hist;                       // the new token's row
   const int r1 = min(n + 1, r0 + hd.chunk);
@@ -673,7 +677,7 @@ __global__ __launch_bounds__(64 * NWV) void k_decode_combine(
       L = n >= 0 && n < cap ? n + 1 : 0;
     }
     if (L == 0) continue;
-    const int rows = dec_chunk_rows(L, nchunk, fine);
+    const int rows = dec_chunk_rows<D>(L, nchunk, fine);
     const int nc = (L + rows - 1) / rows;
     float M = lane < nc ? ml0.x : -1e30f;
     for (int c = lane + 64; c < nc; c += 64) M = fmaxf(M, ml[c].x);
@@ -742,7 +746,21 @@ static void launch_dec_combine(const DecStep& a, int32_t* cache_len, int B, int 
   }
 }
 
-static int dec_nchunk(int cap) { return (cap + kDecChunk - 1) / kDecChunk; }
+// Chunks per head (partials to hold and workgroups to launch) with `heads`
+// active heads in the call: 512-row chunks hold the capacity, and where they
+// leave compute units idle there is one per dec_min_rows rows as long as the
+// launch stays within one workgroup per compute unit.  Steps of attention and
+// combine, 512-row chunks -> these: 2 shared heads over a window of 512, d 128, 8
+// sequences 11.1 -> 8.2 us, 64 sequences 12.7 -> 10.1; one sequence, 8 heads of
+// 4000 rows, d 128, 13.5 -> 11.8; of 300 rows, d 64, 9.8 -> 9.0.  Up to 512
+// workgroups: the same, but 14.6 for 13.1 where the capacity (2051) is far above
+// the histories (520) and the rest of the launch finds no rows.
+constexpr long kDecSpreadGroups = 256;
+static int dec_nchunk(size_t heads, int cap, int d) {
+  const long nc = (static_cast<long>(cap) + kDecChunk - 1) / kDecChunk;
+  const long fit = kDecSpreadGroups / std::max<long>(static_cast<long>(heads), 1);
+  return static_cast<int>(std::max(nc, std::min((static_cast<long>(cap) + dec_min_rows(d) - 1) / dec_min_rows(d), fit)));
+}
 
 struct DecWs {
   float* qrot;
@@ -754,7 +772,7 @@ struct DecWs {
 
 static DecWs carve_dec(void* ws, int B, int K, int d, int cap, int G = 1) {
   const size_t BK = static_cast<size_t>(B) * K;
-  const size_t nc = dec_nchunk(cap);
+  const size_t nc = dec_nchunk(BK, cap, d);
   Carver cv(ws);
   DecWs w;
   w.qrot = cv.take<float>(BK * G * d);
@@ -771,12 +789,11 @@ size_t decode_workspace_bytes(int B, int /*H*/, int K, int d, int cap, int G) {
 
 // ---------------------------------------------------------------------------
 // Scratch of the decode step that allocates nothing (namoh_decode_step_noalloc):
-// the step's workspace (rotated queries, history lengths, per-chunk partials)
-// in a file-scope device array.  Every GPU the library runs on holds its own
-// copy for the life of the process; every call on one GPU uses that GPU's
-// copy, so calls that overlap on one GPU race.  Nothing in it needs to start
-// at zero: the append kernel writes every row length and rotated query the
-// attention reads, and each chunk writes the partial the combine reads.
+// the step's workspace (the per-chunk partials) in a file-scope device array.
+// Every GPU the library runs on holds its own copy for the life of the process;
+// every call on one GPU uses that GPU's copy, so calls that overlap on one GPU
+// race.  Nothing in it needs to start at zero: each chunk writes the partial the
+// combine reads.
 constexpr size_t kDecodeScratchBytes = static_cast<size_t>(32) << 20;
 static __device__ __attribute__((aligned(256))) unsigned char scratch[kDecodeScratchBytes];
 
@@ -965,7 +982,7 @@ static hipError_t run_decode(const float* logits, const float* bias, const void*
                              int out_dtype, int32_t* dev_status, void* ws,
                              hipStream_t st) {
   const DecWs w = carve_dec(ws, B, K, D, cap, GQ);
-  const int nc = dec_nchunk(cap);
+  const int nc = dec_nchunk(static_cast<size_t>(B) * K, cap, D);
   const double log_base = rope_mode == 2 ? 0.0 : std::log(static_cast<double>(rope_base));
   const DecStep a{logits, bias, q, k, v, k_cache, v_cache, cache_len, seq_pos, H, K, cap, log_base,
                   rope_mode, gate_mode, 0, scale * 1.4426950408889634f, topk_idx, gates, dev_status,
@@ -1040,7 +1057,7 @@ struct SharedDecWs {
 
 static SharedDecWs carve_shared_dec(void* ws, int B, int Hs, int d, int cap) {
   const size_t BS = static_cast<size_t>(B) * Hs;
-  const size_t nc = dec_nchunk(cap);
+  const size_t nc = dec_nchunk(BS, cap, d);
   Carver cv(ws);
   SharedDecWs w;
   w.qrot = cv.take<float>(BS * d);
@@ -1065,7 +1082,7 @@ static hipError_t run_shared_decode(const void* q, const void* k, const void* v,
                                     void* out, int out_dtype, int accumulate,
                                     int32_t* dev_status, void* ws, hipStream_t st) {
   const SharedDecWs w = carve_shared_dec(ws, B, Hs, D, cap);
-  const int nc = dec_nchunk(cap);
+  const int nc = dec_nchunk(static_cast<size_t>(B) * Hs, cap, D);
   const double log_base = rope_mode == 2 ? 0.0 : std::log(static_cast<double>(rope_base));
   const DecStep a{nullptr, nullptr, q, k, v, k_cache, v_cache, cache_len, nullptr, Hs, Hs, cap,
                   log_base, rope_mode, 0, window, scale * 1.4426950408889634f, nullptr, nullptr,
