@@ -291,8 +291,9 @@ __global__ __launch_bounds__(256) void k_out_map(
 // ---------------------------------------------------------------------------
 // Tiled GEMM of both projections: a workgroup computes TM data rows x TN
 // output columns with WM x WN waves (8 waves of 64 rows x TN / 2 columns, two
-// per SIMD).  The reduction runs in chunks of 64 through two LDS stages that
-// are filled straight from memory (no staging registers, no LDS stores), one
+// per SIMD; short launches: see kSmallTM).  The reduction runs in chunks of 64
+// through two LDS stages that are filled straight from memory (no staging
+// registers, no LDS stores), one
 // whole 128-byte line per row: chunks of 32 (half lines, four stages) asked
 // the L2 for every line twice and ran at 8 TB/s of L2 traffic, Q/K/V 151 us
 // against 140 us at d_model 2048.  Every unselected head's row lies outside
@@ -316,7 +317,6 @@ __global__ __launch_bounds__(256) void k_out_map(
 constexpr int kXcds = 8;        // XCDs of the device; workgroup i runs on XCD i % 8
 constexpr int kXcdCus = 32;     // compute units of an XCD
 constexpr int kTileKC = 64;     // reduction chunk: 128-byte LDS rows, one memory line each
-constexpr int kTileStages = 2;
 constexpr int kTileMaxB = 256;  // sequences whose row counts are staged (more: per-segment tiles)
 
 template <int TM>
@@ -325,16 +325,16 @@ NAMOH_DEV int seg_btile0(int seg0, int s) { return seg0 / TM + s; }
 // Largest head count whose map tile fits beside the stages of a TN-wide tile.
 constexpr int tile_map_heads(int TN) { return TN == 256 ? 32 : 64; }
 
-template <int TM, int TN, int HM>
+template <int TM, int TN, int HM, int ST>
 struct TileLds {
   // stage: TM data rows, then TN weight rows, of 64 elements each, their
   // 16-byte granules swizzled (swz<8>)
-  uint16_t ring[kTileStages][(TM + TN) * kTileKC];
+  uint16_t ring[ST][(TM + TN) * kTileKC];
   int32_t map[TM * HM];                 // OUT: head map [h][row]
 };
-template <int TM, int TN>
-struct TileLds<TM, TN, 0> {
-  uint16_t ring[kTileStages][(TM + TN) * kTileKC];
+template <int TM, int TN, int ST>
+struct TileLds<TM, TN, 0, ST> {
+  uint16_t ring[ST][(TM + TN) * kTileKC];
 };
 
 // 16 bytes per lane straight into LDS (lane l at lds + 16 l).  Inline
@@ -364,7 +364,7 @@ NAMOH_DEV bool take_half(int half, R& r0, int& nrow) {
   return nrow > 0;
 }
 
-template <int MODE, int TM, int TN, int WM, int WN, int OCC, bool OUT_BF16>
+template <int MODE, int TM, int TN, int WM, int WN, int OCC, bool OUT_BF16, int ST = 2>
 __global__ __launch_bounds__(WM * WN * kWave, OCC) void k_proj_tile(
     const uint16_t* __restrict__ src, const uint16_t* __restrict__ w,
     const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ perm_token,
@@ -378,8 +378,8 @@ __global__ __launch_bounds__(WM * WN * kWave, OCC) void k_proj_tile(
   constexpr int HM = MODE == kProjOut ? tile_map_heads(TN) : 0;
   static_assert(TM == WM * 64 && NW % 2 == 0 && TM / 2 % (8 * NW) == 0 && WI * NW * 8 == TN && CT * WN * 32 == TN,
                 "tile shape");
-  __shared__ __attribute__((aligned(16))) TileLds<TM, TN, HM> L;
-  static_assert(sizeof(TileLds<TM, TN, HM>) <= 160 * 1024, "LDS");
+  __shared__ __attribute__((aligned(16))) TileLds<TM, TN, HM, ST> L;
+  static_assert(sizeof(TileLds<TM, TN, HM, ST>) <= 160 * 1024, "LDS");
   const int tid = thread_x();
   const int lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int c = lane & 31, g = lane >> 5;
@@ -609,43 +609,77 @@ __global__ __launch_bounds__(WM * WN * kWave, OCC) void k_proj_tile(
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
   };
 
-  // One chunk: four 16-wide steps, the fragments of the next one read during
-  // each.  The barrier stands before the last step: it publishes the next
-  // chunk, whose first fragments that step reads, and frees this chunk's
-  // stage for the chunk after the next.  That one's loads go one behind each
-  // product, the data rows (longer latency) in this step and the weight rows
-  // in the first step of the next chunk: issued together they fill the load
-  // queue and the waves stand before it instead of feeding the matrix units.
-  static_assert(XI <= CT * RT && WI <= CT * RT, "a load behind each product");
+  if constexpr (ST > 2) {
+    // Few tiles: what bounds them is the latency of a chunk's loads, so ST - 1
+    // chunks are kept in flight.  Waiting until at most the loads of the ST - 2
+    // chunks behind chunk ch are outstanding leaves it landed; the barrier
+    // publishes it and frees the stage of chunk ch - 1, whose reads have
+    // returned (lgkmcnt), for chunk ch + ST - 1.  Past the last chunk the loads
+    // go on (they wrap around to valid rows, into stages nobody reads any more),
+    // so the count stays the same.
+    constexpr int behind = (ST - 2) * (XI + WI);
+    auto load = [&](int stage) {
 #pragma unroll
-  for (int i = 0; i < XI; ++i) load_x(0, i);
+      for (int i = 0; i < XI; ++i) load_x(stage, i);
 #pragma unroll
-  for (int i = 0; i < WI; ++i) load_w(0, i);
-  next();
-  publish();
-  read_frags(0, 0, 0);
-  if (nchunk > 1)
+      for (int i = 0; i < WI; ++i) load_w(stage, i);
+      next();
+    };
 #pragma unroll
-    for (int i = 0; i < XI; ++i) load_x(1, i);
-  auto chunk = [&](int stage, bool more1, bool more2) {
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(stage, 1, 1);
-    mfmas(0, [&](int k) { if (k < WI && more1) load_w(stage ^ 1, k); });
+    for (int i = 0; i + 1 < ST; ++i) load(i);
+    int st = 0, fill = ST - 1;
+    for (int ch = 0; ch < nchunk; ++ch) {
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(behind) : "memory");
+      load(fill);
+      read_frags(st, 0, 0);
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        if (ks < 3) read_frags(st, ks + 1, (ks + 1) & 1);
+        mfmas(ks & 1, nothing);
+      }
+      fill = st;
+      st = st + 1 == ST ? 0 : st + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else {
+    // One chunk: four 16-wide steps, the fragments of the next one read during
+    // each.  The barrier stands before the last step: it publishes the next
+    // chunk, whose first fragments that step reads, and frees this chunk's
+    // stage for the chunk after the next.  That one's loads go one behind each
+    // product, the data rows (longer latency) in this step and the weight rows
+    // in the first step of the next chunk: issued together they fill the load
+    // queue and the waves stand before it instead of feeding the matrix units.
+    static_assert(XI <= CT * RT && WI <= CT * RT, "a load behind each product");
+  #pragma unroll
+    for (int i = 0; i < XI; ++i) load_x(0, i);
+  #pragma unroll
+    for (int i = 0; i < WI; ++i) load_w(0, i);
     next();
-    read_frags(stage, 2, 0);
-    mfmas(1, nothing);
-    read_frags(stage, 3, 1);
-    mfmas(0, nothing);
     publish();
-    read_frags(stage ^ 1, 0, 0);
-    mfmas(1, [&](int k) { if (k < XI && more2) load_x(stage, k); });
-  };
-  int ch = 0;
-  for (; ch + 1 < nchunk; ch += 2) {
-    chunk(0, true, ch + 2 < nchunk);
-    chunk(1, ch + 2 < nchunk, ch + 3 < nchunk);
+    read_frags(0, 0, 0);
+    if (nchunk > 1)
+  #pragma unroll
+      for (int i = 0; i < XI; ++i) load_x(1, i);
+    auto chunk = [&](int stage, bool more1, bool more2) {
+      __builtin_amdgcn_sched_barrier(0);
+      read_frags(stage, 1, 1);
+      mfmas(0, [&](int k) { if (k < WI && more1) load_w(stage ^ 1, k); });
+      next();
+      read_frags(stage, 2, 0);
+      mfmas(1, nothing);
+      read_frags(stage, 3, 1);
+      mfmas(0, nothing);
+      publish();
+      read_frags(stage ^ 1, 0, 0);
+      mfmas(1, [&](int k) { if (k < XI && more2) load_x(stage, k); });
+    };
+    int ch = 0;
+    for (; ch + 1 < nchunk; ch += 2) {
+      chunk(0, true, ch + 2 < nchunk);
+      chunk(1, ch + 2 < nchunk, ch + 3 < nchunk);
+    }
+    if (ch < nchunk) chunk(0, false, false);
   }
-  if (ch < nchunk) chunk(0, false, false);
 
   // ---- epilogue: lane (c, g) holds data row 64 wr + 32 rt + c, output
   // columns n0 + TN/2 wc + 32 ct + 8 j + 4 g + i in accumulator 4 j + i; the
@@ -729,7 +763,7 @@ static bool out_dense(int B, int T, int H, int K, int d, int d_model) {
          out_dense_bytes(B, T, H, K, d) <= out_pair_bytes(B, T, K, d_model);
 }
 
-template <int TM, int TN, int WM, int WN, int OCC>
+template <int TM, int TN, int WM, int WN, int OCC, int ST = 2>
 static void launch_out_tile(const uint16_t* grows, const uint16_t* w_o, const int32_t* map, long BT,
                             int Nr, int H, int d, int d_model, void* out, bool out_bf16,
                             hipStream_t st) {
@@ -739,10 +773,10 @@ static void launch_out_tile(const uint16_t* grows, const uint16_t* w_o, const in
   const unsigned rem = tiles % units;
   const unsigned grid = tiles + (2 * rem <= units ? rem : 0);   // second halves of a split tail
   if (out_bf16)
-    k_proj_tile<kProjOut, TM, TN, WM, WN, OCC, true><<<grid, WM * WN * kWave, 0, st>>>(
+    k_proj_tile<kProjOut, TM, TN, WM, WN, OCC, true, ST><<<grid, WM * WN * kWave, 0, st>>>(
         grows, w_o, nullptr, nullptr, map, 0, H, 0, BT, Nr, d, d_model, d, nct, 0, out, nullptr, nullptr);
   else
-    k_proj_tile<kProjOut, TM, TN, WM, WN, OCC, false><<<grid, WM * WN * kWave, 0, st>>>(
+    k_proj_tile<kProjOut, TM, TN, WM, WN, OCC, false, ST><<<grid, WM * WN * kWave, 0, st>>>(
         grows, w_o, nullptr, nullptr, map, 0, H, 0, BT, Nr, d, d_model, d, nct, 0, out, nullptr, nullptr);
 }
 
@@ -752,11 +786,11 @@ static unsigned proj_row_tiles(int B, int T, int H, int K) {
   return static_cast<unsigned>(Nr / kProjRows + static_cast<size_t>(B) * H + 1);
 }
 
-template <int TM, int WM, int WN, int OCC>
+template <int TM, int TN, int WM, int WN, int OCC, int ST = 2>
 static void launch_qkv_tile(const uint16_t* x, const uint16_t* w, int B, int T, int H, int K, int d,
                             int d_model, const int32_t* seg_offsets, const int32_t* perm_token,
                             void* q, void* k, void* v, hipStream_t st) {
-  const int N = 3 * d, nct = N / 192;
+  const int N = 3 * d, nct = N / TN;
   // at most Nr / TM full tiles and one partial tile per head, dealt to the
   // XCDs in equal shares; or numbered by segment
   const size_t BT = static_cast<size_t>(B) * T;
@@ -764,9 +798,31 @@ static void launch_qkv_tile(const uint16_t* x, const uint16_t* w, int B, int T, 
   const size_t tiles = BT * K / TM + (by_head ? H : static_cast<size_t>(B) * H + 1);
   // (by head: and the second halves of a split tail)
   const size_t grid = by_head ? ((tiles * nct + kXcds - 1) / kXcds + kXcdCus / 2) * kXcds : tiles * nct;
-  k_proj_tile<kProjQKV, TM, 192, WM, WN, OCC, false><<<static_cast<unsigned>(grid), WM * WN * kWave, 0, st>>>(
+  k_proj_tile<kProjQKV, TM, TN, WM, WN, OCC, false, ST><<<static_cast<unsigned>(grid), WM * WN * kWave, 0, st>>>(
       x, w, seg_offsets, perm_token, nullptr, B, H, T, static_cast<long>(BT), B * T * K, d_model, N,
       d, nct, by_head ? 1 : 0, q, k, v);
+}
+
+// Tiles of 128 x 64 with three stages where a launch is short of 256-row tiles.
+// There a chunk costs the latency of its loads (0.9 us for Q/K/V, 1.2 us for the
+// output, 32 of them in a row at d_model 2048), not its products: smaller tiles
+// put more compute units on it, more stages keep more of it in flight.  The
+// lines lie where the small tiles stop fitting into one round: two workgroups
+// per compute unit for Q/K/V, one for the output (which holds the head map as
+// well).  256-row tiles -> these, H 32, K 8, d 64, d_model 2048: Q/K/V 300 tokens
+// 29 -> 16.5 us, 1000 31 -> 18, 2000 (471 tiles) 33 -> 28, but 4000 (846) 43 -> 45;
+// output 300 tokens 40 -> 25 us, 1000 (256 tiles) 40 -> 30.5, but 1200 (320)
+// 41 -> 44.  d 128, d_model 4096: Q/K/V 300 tokens 50 -> 28, 700 55 -> 41, 1500
+// 57 -> 65.  Four stages instead of three: 29.5 for 22.5 us where two workgroups
+// no longer fit (Q/K/V, 1200 tokens).
+constexpr int kSmallTM = 128, kSmallTN = 64, kSmallStages = 3;
+constexpr size_t kTileUnits = kXcds * kXcdCus;
+static bool qkv_small(int B, int T, int H, int K, int d) {
+  const size_t rows = static_cast<size_t>(B) * T * K / kSmallTM + H;
+  return B <= kTileMaxB && rows * (3 * d / kSmallTN) <= 2 * kTileUnits;
+}
+static bool out_small(long BT, int d_model) {
+  return static_cast<size_t>((BT + kSmallTM - 1) / kSmallTM) * (d_model / kSmallTN) <= kTileUnits;
 }
 
 hipError_t launch_qkv_proj(const void* x, const void* w_qkv, int B, int T, int H, int K, int d,
@@ -774,8 +830,10 @@ hipError_t launch_qkv_proj(const void* x, const void* w_qkv, int B, int T, int H
                            void* q, void* k, void* v, hipStream_t st) {
   if ((3 * d) % 192 != 0 || d_model % kProjKC != 0) return hipErrorInvalidValue;
   prof_mark("qkv_proj", true, st);
-  launch_qkv_tile<256, 4, 2, 2>(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_qkv), B, T,
-                       H, K, d, d_model, seg_offsets, perm_token, q, k, v, st);
+  const auto launch = qkv_small(B, T, H, K, d) ? launch_qkv_tile<kSmallTM, kSmallTN, 2, 2, 1, kSmallStages>
+                                               : launch_qkv_tile<256, 192, 4, 2, 2>;
+  launch(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_qkv), B, T, H, K, d, d_model,
+         seg_offsets, perm_token, q, k, v, st);
   prof_mark("qkv_proj", false, st);
   return hipGetLastError();
 }
@@ -803,7 +861,10 @@ hipError_t launch_out_proj(const void* head_out, int head_out_dtype, const void*
       k_out_map<false><<<mgrid, 256, 0, st>>>(head_out, gates, slot_pos, seg_offsets, BT, H, K, B * H,
                                               B * T * K, d, map, grows);
     const uint16_t* w = static_cast<const uint16_t*>(w_o);
-    if (d_model % 256 == 0 && H <= tile_map_heads(256))
+    if (out_small(BT, d_model))
+      launch_out_tile<kSmallTM, kSmallTN, 2, 2, 1, kSmallStages>(grows, w, map, BT, B * T * K, H, d, d_model,
+                                                                 out, out_dtype == 1, st);
+    else if (d_model % 256 == 0 && H <= tile_map_heads(256))
       launch_out_tile<256, 256, 4, 2, 2>(grows, w, map, BT, B * T * K, H, d, d_model, out, out_dtype == 1, st);
     else
       launch_out_tile<256, 128, 4, 2, 2>(grows, w, map, BT, B * T * K, H, d, d_model, out, out_dtype == 1, st);

@@ -43,7 +43,10 @@ def _sample(B, T, n=40):
 # share (unsplit) and a split tail after full rounds; more than 256 sequences
 QKV = [(1, 1, 1, 1, 64), (1, 127, 2, 2, 64), (1, 129, 1, 1, 128), (1, 255, 3, 3, 64),
        (1, 257, 2, 2, 128), (5, 51, 2, 2, 64), (256, 3, 4, 2, 64), (257, 3, 4, 2, 64),
-       (2, 4400, 8, 4, 64), (3, 2900, 64, 8, 128)]
+       (2, 4400, 8, 4, 64), (3, 2900, 64, 8, 128),
+       # 256-row tiles (more than 512 of the small ones) at the same edges; 510 and 513 of them
+       (1, 129, 64, 64, 128), (1, 255, 64, 64, 128), (1, 257, 48, 48, 128), (1, 500, 64, 16, 128),
+       (1, 20480, 10, 1, 64), (1, 20480, 11, 1, 64)]
 
 
 @pytest.mark.parametrize("B,T,H,K,d", QKV)
@@ -79,7 +82,10 @@ def test_qkv_tiles(B, T, H, K, d, dm=256):
 OUT = [(1, 1, 4, 2, 64, 256), (1, 128, 4, 2, 64, 256), (1, 129, 4, 2, 64, 128),
        (1, 257, 1, 1, 64, 256), (2, 2176, 4, 2, 64, 2048), (1, 9100, 4, 2, 128, 2048),
        (1, 300, 64, 11, 64, 512), (1, 3072, 16, 2, 64, 2048), (1, 2816, 16, 2, 64, 2048),
-       (1, 8192, 16, 2, 128, 2048), (1, 7936, 16, 2, 128, 2048), (1, 25000, 16, 2, 64, 128)]
+       (1, 8192, 16, 2, 128, 2048), (1, 7936, 16, 2, 128, 2048), (1, 25000, 16, 2, 64, 128),
+       # 256 small tiles, and 256-row tiles just past them (1, 128 and 129 rows in the last)
+       (1, 1024, 4, 2, 64, 2048), (1, 1025, 4, 2, 64, 2048), (1, 1152, 4, 2, 64, 2048),
+       (1, 1153, 4, 2, 64, 2048), (1, 4225, 64, 11, 64, 512)]
 
 
 @pytest.mark.parametrize("hdt", [torch.float32, torch.bfloat16])
