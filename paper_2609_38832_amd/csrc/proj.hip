@@ -292,9 +292,9 @@ __global__ __launch_bounds__(256) void k_out_map(
 // Tiled GEMM of both projections: a workgroup computes TM data rows x TN
 // output columns with WM x WN waves (8 waves of 64 rows x TN / 2 columns, two
 // per SIMD; short launches: see kSmallTM).  The reduction runs in chunks of 64
-// through two LDS stages that are filled straight from memory (no staging
-// registers, no LDS stores), one
-// whole 128-byte line per row: chunks of 32 (half lines, four stages) asked
+// through LDS stages (two; small tiles three) that are filled straight from
+// memory (no staging registers, no LDS stores), one whole 128-byte line per
+// row: chunks of 32 (half lines, four stages) asked
 // the L2 for every line twice and ran at 8 TB/s of L2 traffic, Q/K/V 151 us
 // against 140 us at d_model 2048.  Every unselected head's row lies outside
 // the OUT buffer, so three quarters of its data loads (K = H / 4) cost no
