@@ -292,7 +292,7 @@ __global__ __launch_bounds__(256) void k_out_map(
 // Tiled GEMM of both projections: a workgroup computes TM data rows x TN
 // output columns with WM x WN waves (8 waves of 64 rows x TN / 2 columns, two
 // per SIMD; short launches: see kSmallTM).  The reduction runs in chunks of 64
-// through LDS stages (two; small tiles three) that are filled straight from
+// through LDS stages (two; small tiles: rounds of three) that are filled straight from
 // memory (no staging registers, no LDS stores), one whole 128-byte line per
 // row: chunks of 32 (half lines, four stages) asked
 // the L2 for every line twice and ran at 8 TB/s of L2 traffic, Q/K/V 151 us
@@ -610,37 +610,53 @@ __global__ __launch_bounds__(WM * WN * kWave, OCC) void k_proj_tile(
   };
 
   if constexpr (ST > 2) {
-    // Few tiles: what bounds them is the latency of a chunk's loads, so ST - 1
-    // chunks are kept in flight.  Waiting until at most the loads of the ST - 2
-    // chunks behind chunk ch are outstanding leaves it landed; the barrier
-    // publishes it and frees the stage of chunk ch - 1, whose reads have
-    // returned (lgkmcnt), for chunk ch + ST - 1.  Past the last chunk the loads
-    // go on (they wrap around to valid rows, into stages nobody reads any more),
-    // so the count stays the same.
-    constexpr int behind = (ST - 2) * (XI + WI);
-    auto load = [&](int stage) {
+    // Few tiles: what bounds them is the latency of the loads, so a round
+    // loads ST chunks at once.  When all of them have landed (a full wait:
+    // loads into LDS are only ever published that way, see tile_dma), every
+    // wave takes its fragments of the whole round into registers; the second
+    // barrier frees the stages, and the next round's loads run behind this
+    // one's products.  Past the last chunk loads wrap around to valid rows
+    // that no product uses.
+    auto load_round = [&]() {
 #pragma unroll
-      for (int i = 0; i < XI; ++i) load_x(stage, i);
+      for (int s = 0; s < ST; ++s) {
 #pragma unroll
-      for (int i = 0; i < WI; ++i) load_w(stage, i);
-      next();
-    };
+        for (int i = 0; i < XI; ++i) load_x(s, i);
 #pragma unroll
-    for (int i = 0; i + 1 < ST; ++i) load(i);
-    int st = 0, fill = ST - 1;
-    for (int ch = 0; ch < nchunk; ++ch) {
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(behind) : "memory");
-      load(fill);
-      read_frags(st, 0, 0);
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        if (ks < 3) read_frags(st, ks + 1, (ks + 1) & 1);
-        mfmas(ks & 1, nothing);
+        for (int i = 0; i < WI; ++i) load_w(s, i);
+        next();
       }
-      fill = st;
-      st = st + 1 == ST ? 0 : st + 1;
+    };
+    load_round();
+    for (int ch = 0; ch < nchunk; ch += ST) {
+      publish();
+      bf16x8 rx[ST][4][RT], rw[ST][4][CT];
+#pragma unroll
+      for (int s = 0; s < ST; ++s)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          const uint16_t* st = &L.ring[s][0];
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            rx[s][ks][rt] = *reinterpret_cast<const bf16x8*>(st + (fx + 32 * rt) * kTileKC + swz<8>(c, 2 * ks + g) * 8);
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+            rw[s][ks][ct] = *reinterpret_cast<const bf16x8*>(st + (fw + 32 * ct) * kTileKC + swz<8>(c, 2 * ks + g) * 8);
+        }
+      publish();   // (no load is in flight: every wave's reads have returned)
+      if (ch + ST < nchunk) load_round();
+#pragma unroll
+      for (int s = 0; s < ST; ++s) {
+        if (ch + s >= nchunk) break;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+              C[ct][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rw[s][ks][ct], rx[s][ks][rt], C[ct][rt], 0, 0, 0);
+      }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   } else {
     // One chunk: four 16-wide steps, the fragments of the next one read during
     // each.  The barrier stands before the last step: it publishes the next
@@ -803,18 +819,17 @@ static void launch_qkv_tile(const uint16_t* x, const uint16_t* w, int B, int T, 
       d, nct, by_head ? 1 : 0, q, k, v);
 }
 
-// Tiles of 128 x 64 with three stages where a launch is short of 256-row tiles.
-// There a chunk costs the latency of its loads (0.9 us for Q/K/V, 1.2 us for the
-// output, 32 of them in a row at d_model 2048), not its products: smaller tiles
-// put more compute units on it, more stages keep more of it in flight.  The
-// lines lie where the small tiles stop fitting into one round: two workgroups
-// per compute unit for Q/K/V, one for the output (which holds the head map as
-// well).  256-row tiles -> these, H 32, K 8, d 64, d_model 2048: Q/K/V 300 tokens
-// 29 -> 16.5 us, 1000 31 -> 18, 2000 (471 tiles) 33 -> 28, but 4000 (846) 43 -> 45;
-// output 300 tokens 40 -> 25 us, 1000 (256 tiles) 40 -> 30.5, but 1200 (320)
-// 41 -> 44.  d 128, d_model 4096: Q/K/V 300 tokens 50 -> 28, 700 55 -> 41, 1500
-// 57 -> 65.  Four stages instead of three: 29.5 for 22.5 us where two workgroups
-// no longer fit (Q/K/V, 1200 tokens).
+// Tiles of 128 x 64 with rounds of three chunks where a launch is short of
+// 256-row tiles.  There a chunk costs the latency of its loads (0.8 us for
+// Q/K/V, 1.0 us for the output, 32 of them in a row at d_model 2048), not its
+// products: smaller tiles put more compute units on it, and a round pays the
+// latency once for three chunks.  The lines lie where the small tiles stop
+// fitting into one round of workgroups: two per compute unit for Q/K/V, one for
+// the output (which holds the head map as well).  256-row tiles -> these, H 32,
+// K 8, d 64, d_model 2048: Q/K/V 300 tokens 26 -> 14 us, 1000 29 -> 20, 2000
+// (471 tiles) 30 -> 29, but 3000 (660) 32 -> 38; output 300 tokens 33 -> 19 us,
+// 1000 (256 tiles) 35 -> 26.5, but 1200 (320) 35 -> 39.  d 128, d_model 4096:
+// Q/K/V 300 tokens 48 -> 31, 700 52 -> 43, 1500 56 -> 72.
 constexpr int kSmallTM = 128, kSmallTN = 64, kSmallStages = 3;
 constexpr size_t kTileUnits = kXcds * kXcdCus;
 static bool qkv_small(int B, int T, int H, int K, int d) {
@@ -830,7 +845,7 @@ hipError_t launch_qkv_proj(const void* x, const void* w_qkv, int B, int T, int H
                            void* q, void* k, void* v, hipStream_t st) {
   if ((3 * d) % 192 != 0 || d_model % kProjKC != 0) return hipErrorInvalidValue;
   prof_mark("qkv_proj", true, st);
-  const auto launch = qkv_small(B, T, H, K, d) ? launch_qkv_tile<kSmallTM, kSmallTN, 2, 2, 1, kSmallStages>
+  const auto launch = qkv_small(B, T, H, K, d) ? launch_qkv_tile<kSmallTM, kSmallTN, 2, 2, 2, kSmallStages>
                                                : launch_qkv_tile<256, 192, 4, 2, 2>;
   launch(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_qkv), B, T, H, K, d, d_model,
          seg_offsets, perm_token, q, k, v, st);

@@ -125,3 +125,46 @@ def test_out_rows_past_4_gib():
     o = L.out_proj(ho, w, r, B, T, H, K, out_dtype=torch.bfloat16)
     torch.cuda.synchronize()
     _check_out_rows(o, ho, w, r, _sample(B, T, 12))
+
+
+# every row of short inputs (128 x 64 tiles), whose reduction runs in rounds of
+# three chunks: 32 and 64 chunks, and 2, 6 and 10 (a round cut short, whole ones,
+# one chunk over); output: H d / 64 chunks of 1, 2, 3, 4, 32 and 64
+@pytest.mark.parametrize("T,H,K,d,dm", [(300, 32, 8, 64, 2048), (300, 32, 8, 128, 4096),
+                                        (97, 8, 4, 64, 128), (97, 8, 4, 64, 384),
+                                        (97, 8, 4, 64, 640)])
+def test_small_qkv_all_rows(T, H, K, d, dm):
+    say(f"short qkv, all rows: T{T} H{H} K{K} d{d} dm{dm}")
+    g, r = _routing(1, T, H, K, 7)
+    x = torch.randn(1, T, dm, generator=g, device=DEV, dtype=torch.bfloat16)
+    w = torch.randn(H, 3, d, dm, generator=g, device=DEV, dtype=torch.bfloat16) * dm ** -0.5
+    out = {n: torch.full((1, H, T, d), float("nan"), dtype=torch.bfloat16, device=DEV) for n in "qkv"}
+    for rep in range(3):
+        L.qkv_proj(x, w, r, H, K, out=out)
+    top, xd = r["topk_idx"][0].long(), x[0].double()
+    for j, n in enumerate("qkv"):
+        got, ref = [], []
+        for h in range(H):
+            t = (top == h).any(1).nonzero()[:, 0]
+            got.append(out[n][0, h, t].float())
+            ref.append(xd[t] @ w[h, j].double().T)
+        check_out(torch.cat(got).cpu().numpy(), torch.cat(ref).cpu().numpy(), "bf16", what=n)
+
+
+@pytest.mark.parametrize("T,H,K,d,dm", [(300, 32, 8, 64, 2048), (300, 32, 16, 128, 2048),
+                                        (130, 1, 1, 64, 256), (130, 2, 1, 64, 256),
+                                        (130, 3, 1, 64, 256), (130, 2, 1, 128, 256)])
+def test_small_out_all_rows(T, H, K, d, dm):
+    say(f"short output projection, all rows: T{T} H{H} K{K} d{d} dm{dm}")
+    g, r = _routing(1, T, H, K, 8)
+    ho = torch.randn(T * K, d, generator=g, device=DEV)
+    w = torch.randn(H, dm, d, generator=g, device=DEV, dtype=torch.bfloat16) * d ** -0.5
+    for rep in range(3):
+        o = L.out_proj(ho, w, r, 1, T, H, K, out_dtype=torch.float32,
+                       out=torch.full((1, T, dm), float("nan"), device=DEV))
+    ref = torch.zeros(T, dm, dtype=torch.float64, device=DEV)
+    rows = (r["gates"][0].double()[..., None] * ho[r["slot_pos"][0].long()].double())   # [T, K, d]
+    for h in range(H):
+        t, k = (r["topk_idx"][0] == h).nonzero(as_tuple=True)
+        ref[t] += rows[t, k] @ w[h].double().T
+    check_out(o[0].cpu().numpy(), ref.cpu().numpy(), "bf16", what="output rows")
