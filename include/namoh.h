@@ -494,6 +494,9 @@ namoh_status namoh_prefill_cache(const void* k, const void* v, int dtype, int B,
  *      If n == cap the append is skipped, *dev_status (if non-NULL) is set
  *      to 1 and that head contributes nothing to out.  *dev_status is never
  *      cleared by the library.
+ * The decode steps' workspace sizes (this one's, the grouped and the shared
+ * heads') never decrease in B, K, Hs, group_size and cap: a workspace sized
+ * for the largest of each serves every smaller call.
  * ---------------------------------------------------------------------- */
 size_t namoh_decode_workspace_size(int B, int H, int K, int d_head, int cap);
 

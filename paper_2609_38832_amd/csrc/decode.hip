@@ -762,6 +762,17 @@ static int dec_nchunk(size_t heads, int cap, int d) {
   return static_cast<int>(std::max(nc, std::min((static_cast<long>(cap) + dec_min_rows(d) - 1) / dec_min_rows(d), fit)));
 }
 
+// Partials to make room for (per query head): no fewer than heads *
+// dec_nchunk(heads, cap, d), and never fewer for more heads or a larger cap,
+// so a workspace sized for a program's largest batch serves its smaller ones,
+// whose heads are cut into more chunks (the chunks alone: 17 sequences of 8
+// heads, d 128, cap 512, have 136 partials, 16 have 256).
+static size_t dec_partials(size_t heads, int cap, int d) {
+  const size_t whole = heads * ((static_cast<size_t>(cap) + kDecChunk - 1) / kDecChunk);
+  const size_t fine = whole * (kDecChunk / dec_min_rows(d));
+  return std::max(whole, std::min(fine, static_cast<size_t>(kDecSpreadGroups)));
+}
+
 struct DecWs {
   float* qrot;
   int32_t* rows;
@@ -772,13 +783,13 @@ struct DecWs {
 
 static DecWs carve_dec(void* ws, int B, int K, int d, int cap, int G = 1) {
   const size_t BK = static_cast<size_t>(B) * K;
-  const size_t nc = dec_nchunk(BK, cap, d);
+  const size_t np = dec_partials(BK, cap, d);
   Carver cv(ws);
   DecWs w;
   w.qrot = cv.take<float>(BK * G * d);
   w.rows = cv.take<int32_t>(BK);
-  w.part_acc = cv.take<float>(BK * G * nc * d);
-  w.part_ml = cv.take<float>(BK * G * nc * 2);
+  w.part_acc = cv.take<float>(np * G * d);
+  w.part_ml = cv.take<float>(np * G * 2);
   w.bytes = cv.off;
   return w;
 }
@@ -1057,7 +1068,7 @@ struct SharedDecWs {
 
 static SharedDecWs carve_shared_dec(void* ws, int B, int Hs, int d, int cap) {
   const size_t BS = static_cast<size_t>(B) * Hs;
-  const size_t nc = dec_nchunk(BS, cap, d);
+  const size_t np = dec_partials(BS, cap, d);
   Carver cv(ws);
   SharedDecWs w;
   w.qrot = cv.take<float>(BS * d);
@@ -1065,8 +1076,8 @@ static SharedDecWs carve_shared_dec(void* ws, int B, int Hs, int d, int cap) {
   w.row0 = cv.take<int32_t>(BS);
   w.heads = cv.take<int32_t>(BS);
   w.gates = cv.take<float>(BS);
-  w.part_acc = cv.take<float>(BS * nc * d);
-  w.part_ml = cv.take<float>(BS * nc * 2);
+  w.part_acc = cv.take<float>(np * d);
+  w.part_ml = cv.take<float>(np * 2);
   w.bytes = cv.off;
   return w;
 }
