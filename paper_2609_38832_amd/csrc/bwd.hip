@@ -229,11 +229,15 @@ constexpr float kLn2 = 0.6931471805599453f;
 // resident: the key-side kernel's resident workgroups).
 // split_slots / splits: query-range parts of blocks heavier than a fair share
 // of that many workgroups (0: whole blocks only).
+// part_slots: partial slots there are, the query side's parts (counted in
+// fwd_meta, half a slot each) taking the first of them.
 struct KeyList {
   WorkItem* items;
   int32_t* meta;
   int max_items, period, resident, split_slots;
   SplitItem* splits;
+  const int32_t* fwd_meta;
+  int part_slots;
 };
 
 // Query-range parts of the key side.  A key block's work is one serial chain
@@ -274,9 +278,10 @@ __global__ __launch_bounds__(kBwdPackThreads) void k_bwd_pack(
     // the key side's work list: blocks or their parts, heaviest first, placed
     // for the key-side kernel's resident workgroups (it runs alongside the
     // packing)
+    const int used = kl.split_slots > 0 ? (max(kl.fwd_meta[kMetaParts], 0) + 1) / 2 : 0;
     attn_schedule<kBwdPackThreads>(seg_offsets, BH, T, kBwdMfmaBlock, Nr, kl.max_items, kl.period,
                                    1, kl.items, kl.meta, U.sched, kl.split_slots, kl.splits,
-                                   kl.resident, kKeySplitTiles, false);
+                                   kl.resident, kKeySplitTiles, false, used, kl.part_slots);
     return;
   }
   const int gt = block_x() - 1;   // the tile this workgroup packs
@@ -1299,13 +1304,8 @@ struct BwdMfmaWs {
   float2* LD;
   WorkItem* kitems;   // the key side's work list
   int32_t* kmeta;
-  SplitItem* ksplits; // its blocks that run as parts, and the parts' sums
-  KeyParts kparts;
-  int ksplit_slots;
   size_t rows, bytes;
 };
-
-constexpr int kKeySplitCUs = 256;   // compute units the fair share is taken over
 
 static BwdMfmaWs carve_bwd_mfma(void* ws, int B, int T, int H, int K, int d) {
   const size_t Nr = static_cast<size_t>(B) * T * K;
@@ -1323,12 +1323,32 @@ static BwdMfmaWs carve_bwd_mfma(void* ws, int B, int T, int H, int K, int d) {
   attn_stats_tiles(nullptr, B, T, H, K, d, tl);
   w.kitems = cv.take<WorkItem>(static_cast<size_t>(tl.max_items));
   w.kmeta = cv.take<int32_t>(kMetaCount);
-  w.ksplit_slots = key_split(T) ? kKeySplitCUs * (d == 64 ? BwdMfmaShape<64>::MINB : BwdMfmaShape<128>::MINB) : 0;
-  w.ksplits = cv.take<SplitItem>(static_cast<size_t>(w.ksplit_slots));
-  w.kparts.slots = 2 * w.ksplit_slots;
-  w.kparts.rows = cv.take<float>(static_cast<size_t>(w.kparts.slots) * 2 * kBwdMfmaBlock * d);
   w.bytes = cv.off;
   return w;
+}
+
+// The key side's parts (none where key_split says so) take no workspace of
+// their own: their records lie in the forward's transposed values, which the
+// backward does not read, and their sums in the forward's partial rows, behind
+// those that the query side's parts use (the packing's workgroup 0 reads how
+// many; parts that would not fit are made longer).
+struct KeySplit {
+  int slots = 0;              // resident workgroups the fair share assumes
+  SplitItem* splits = nullptr;
+  KeyParts parts{nullptr, 0};
+};
+constexpr int kKeySplitCUs = 256;   // compute units the fair share is taken over
+template <int D>
+static KeySplit key_split_of(const AttnTiles& tl, int T) {
+  KeySplit k;
+  if (!key_split(T)) return k;
+  constexpr int slots = kKeySplitCUs * BwdMfmaShape<D>::MINB;
+  // the values of more than 4096 rows hold the records (at most one a slot)
+  static_assert(slots * sizeof(SplitItem) <= 64ull * kBN * D * sizeof(uint16_t), "records fit");
+  k.slots = slots;
+  k.splits = reinterpret_cast<SplitItem*>(tl.Vt);
+  k.parts = KeyParts{tl.part, tl.part_rows / (2 * kBwdMfmaBlock)};
+  return k;
 }
 
 static bool bwd_uses_mfma(int dtype, int d) { return dtype == 1 && (d == 64 || d == 128); }
@@ -1375,8 +1395,9 @@ static hipError_t run_bwd_mfma(const void* q, const void* k, const void* v, int 
   // the key side's own list, heaviest first, placed for its own resident
   // workgroups (the query side runs the forward's list)
   const int cus = bwd_cu_count();
+  const KeySplit ks = key_split_of<D>(tl, T);
   const KeyList kl{w.kitems, w.kmeta, tl.max_items, cus, cus * BwdMfmaShape<D>::MINB,
-                   w.ksplit_slots, w.ksplits};
+                   ks.slots, ks.splits, tl.meta, ks.parts.slots};
   k_bwd_pack<D><<<static_cast<unsigned>(tl.max_tiles) + 1, kBwdPackThreads, 0, st>>>(
       static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(v), dout, topk_idx, gates,
       seg_offsets, perm_token, freq, tl.h, w.lse, BH, H, T, K, Nr, rope_mode, scale * kLog2e,
@@ -1410,14 +1431,14 @@ static hipError_t run_bwd_mfma(const void* q, const void* k, const void* v, int 
   if constexpr (D == 128)
     k_bwd_dkdv8<D><<<kgrid, 2 * kBwdMfmaThreads, 0, st>>>(
         w.Qs, w.dO, w.LD, tl.Kp, w.Vp, w.kitems, w.kmeta, perm_token, freq, T,
-        rope_mode, dk, dv, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.max_items, dqm, w.kparts);
+        rope_mode, dk, dv, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.max_items, dqm, ks.parts);
   else
     k_bwd_dkdv<D><<<kgrid, kBwdMfmaThreads, 0, st>>>(
         w.Qs, w.dO, w.LD, tl.Kp, w.Vp, w.kitems, w.kmeta, perm_token, freq, T,
-        rope_mode, dk, dv, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.max_items, dqm, w.kparts);
+        rope_mode, dk, dv, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.max_items, dqm, ks.parts);
   prof_mark("bwd_dkdv", false, st);
-  if ((e = hipGetLastError()) != hipSuccess || w.ksplit_slots == 0) return e;
-  k_bwd_kv_merge<D><<<kKvMergeGroups, 256, 0, st>>>(w.ksplits, w.kmeta, w.kparts, perm_token, freq, T,
+  if ((e = hipGetLastError()) != hipSuccess || ks.slots == 0) return e;
+  k_bwd_kv_merge<D><<<kKvMergeGroups, 256, 0, st>>>(ks.splits, w.kmeta, ks.parts, perm_token, freq, T,
                                                     rope_mode, dk, dv, packed ? 1 : 0, BH, Nr);
   return hipGetLastError();
 }

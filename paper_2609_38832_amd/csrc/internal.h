@@ -58,7 +58,8 @@ struct SplitItem;
 // Where launch_attn_stats leaves the forward's pieces inside its workspace.
 struct AttnTiles {
   const uint16_t* Kp;      // rotated keys, bf16, 64-row tiles [max_tiles * 64, d]
-  const uint16_t* Vt;      // values, bf16, per tile transposed [max_tiles, d, 64]
+  uint16_t* Vt;            // values, bf16, per tile transposed [max_tiles, d, 64] (read by the
+                           // forward only: free for the backward)
   const double* freq;      // RoPE theta_j / (2 pi), double [d / 2] (as the forward rotates)
   const WorkItem* items;   // (segment, query block) work list, heaviest first, with
                            // key-range parts for blocks heavier than a fair share

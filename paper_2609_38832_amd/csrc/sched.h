@@ -39,7 +39,9 @@ constexpr int kSegLds = 1024;      // segment offsets staged in LDS up to this m
 // parts add at most split_slots items, at most 2 split_slots partial slots
 // and at most split_slots split items (sum of w over the split items is at
 // least (number of split items) F, and each adds at most w / F parts); a
-// larger `split_min` only takes items out of that.
+// larger `split_min` only takes items out of that.  A caller with less room
+// names its partial slots, [first_slot, slot_end): where the parts need more, F
+// is raised by quarters until they fit.
 constexpr int kSplitMinTiles = 32;
 constexpr int kSplitMaxParts = 8;
 
@@ -147,7 +149,8 @@ NAMOH_DEV void attn_schedule(const int32_t* __restrict__ seg_offsets_g, int BH, 
                              WorkItem* __restrict__ items, int32_t* __restrict__ meta,
                              SchedLds& L, int split_slots = 0,
                              SplitItem* __restrict__ splits = nullptr, int resident_slots = 0,
-                             int split_min = kSplitMinTiles, bool late_pairs = true) {
+                             int split_min = kSplitMinTiles, bool late_pairs = true,
+                             int first_slot = 0, int slot_end = 0x7fffffff) {
   static_assert(NT % kWave == 0 && NT / kWave <= 16 && kSortBins % NT == 0, "block size");
   const int tid = thread_x();
   const int lane = tid % kWave, wave = tid / kWave;
@@ -185,6 +188,7 @@ NAMOH_DEV void attn_schedule(const int32_t* __restrict__ seg_offsets_g, int BH, 
       meta[kMetaItems] = 0;
       meta[kMetaBad] = 1;
       meta[kMetaSplit] = 0;
+      meta[kMetaParts] = 0;
     }
     return;
   }
@@ -279,7 +283,8 @@ NAMOH_DEV void attn_schedule(const int32_t* __restrict__ seg_offsets_g, int BH, 
     F = static_cast<int>(min((wtot + split_slots - 1) / split_slots, 0x7fffffffL));
     F = max(F, 1);
   }
-  {
+  const bool limited = split_slots > 0 && slot_end != 0x7fffffff;
+  for (;;) {
     int sg = s_first, qb = qb_first;
     for (int c0 = 0; c0 < ncells; c0 += NT) {
       const int c = c0 + tid;
@@ -291,11 +296,20 @@ NAMOH_DEV void attn_schedule(const int32_t* __restrict__ seg_offsets_g, int BH, 
         split_parts(w, F, split_min, P, Lp);
         bin_add(key_of(w - (P - 1) * Lp), G);
         if (P > 1) bin_add(key_of(Lp), (P - 1) * G);
+        if (limited && P > 1) atomicAdd(&L.nparts, P * G);
       }
       if (!compact) step(sg, qb);
     }
+    __syncthreads();
+    if (!limited) break;
+    const int np = L.nparts;
+    __syncthreads();
+    if (tid == 0) L.nparts = 0;
+    if (np == 0 || np <= slot_end - first_slot) break;   // (published by the scan's barriers)
+    for (int i = tid; i < kSortBins; i += NT) L.hist[i] = 0;
+    F = F > (1 << 29) ? 0x7fffffff : F + F / 4 + 1;
+    __syncthreads();
   }
-  __syncthreads();
   // exclusive scan of the histogram -> insertion cursors (heaviest first)
   constexpr int PER = kSortBins / NT;
   int h[PER];
@@ -329,7 +343,7 @@ NAMOH_DEV void attn_schedule(const int32_t* __restrict__ seg_offsets_g, int BH, 
       // [base + u P, base + (u + 1) P)
       int base = -1;
       if (act && P > 1) {
-        base = atomicAdd(&L.nparts, P * G);
+        base = first_slot + atomicAdd(&L.nparts, P * G);
         const int j = atomicAdd(&L.nsplit, G);
         for (int u = 0; u < G; ++u) {
           SplitItem si;
@@ -384,6 +398,7 @@ NAMOH_DEV void attn_schedule(const int32_t* __restrict__ seg_offsets_g, int BH, 
     meta[kMetaItems] = placed;
     meta[kMetaBad] = 0;
     meta[kMetaSplit] = L.nsplit;
+    meta[kMetaParts] = L.nparts;
   }
 }
 

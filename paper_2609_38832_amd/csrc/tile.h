@@ -18,7 +18,7 @@ namespace namoh {
 
 constexpr int kBN = 64;            // keys per tile
 
-enum Meta { kMetaItems = 0, kMetaBad = 1, kMetaSplit = 2, kMetaCount = 4 };
+enum Meta { kMetaItems = 0, kMetaBad = 1, kMetaSplit = 2, kMetaParts = 3, kMetaCount = 4 };
 
 // Packed key tiles of segment s (first packed row seg0, length n) are
 // numbered from seg_tile0 = floor(seg0 / 64) + s.  The ranges of successive

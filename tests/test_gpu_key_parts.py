@@ -75,3 +75,57 @@ def test_key_parts(T, first, d):
             err = (got.cpu().double() - x).abs()
             assert float(err.max()) <= 2e-2 * float(x.abs().max()), name
             assert float(err.norm() / x.norm()) <= 1e-2, name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_saved_backward_repeats(d, T=4400):
+    # the parts' records and sums lie in workspace that the saved state does not
+    # need: a second backward from the same state gives the same gradients, and so
+    # does a workspace sized for as many tokens in shorter sequences
+    say(f"saved backward twice, T {T}, d {d}")
+    g = torch.Generator(device=DEV).manual_seed(d)
+    logits = torch.randn(1, T, 8, generator=g, device=DEV)
+    logits[..., 0] += 9.0
+    q, k, v = (torch.randn(1, 8, T, d, generator=g, device=DEV, dtype=torch.bfloat16)
+               for _ in range(3))
+    dout = torch.randn(1, T, d, generator=g, device=DEV)
+    r = L.route(logits, 1)
+    want = L.attn_bwd(q, k, v, r, 1, 1e4, dout, packed=True)
+    ws = L.workspace(L.lib().namoh_attn_bwd_workspace_size(4, 4096, 8, 1, d), DEV)
+    L.attn_fwd_train(q, k, v, r, 1, 1e4, ws)
+    for rep in range(2):
+        got = L.attn_bwd(q, k, v, r, 1, 1e4, dout, ws=ws, packed=True, saved=True)
+        for name in ("dq", "dk", "dv", "dgates"):
+            assert torch.equal(got[name], want[name]), (rep, name)
+
+
+def test_parts_longer_than_a_fair_share(T=16384, d=128):
+    # one head of 16384 tokens: the query side's parts leave too few partial rows
+    # for the key side's at a fair share of 65 tiles (573 + 2 x 286 of 1024)
+    say(f"key-side parts that share the partial rows, T {T}, d {d}")
+    g = torch.Generator(device=DEV).manual_seed(3)
+    q, k, v = (torch.randn(1, 1, T, d, generator=g, device=DEV, dtype=torch.bfloat16)
+               for _ in range(3))
+    dout = torch.randn(1, T, d, generator=g, device=DEV)
+    r = L.route(torch.zeros(1, T, 1, device=DEV), 1)
+    got = L.attn_bwd(q, k, v, r, 1, 1e4, dout, packed=True)
+    qd, kd = (_rope(x[0, 0].cpu().double()).to(DEV) for x in (q, k))
+    vd, do = v[0, 0].double(), dout[0].double()
+    dq, dk, dv = (torch.zeros(T, d, dtype=torch.float64, device=DEV) for _ in range(3))
+    for lo in range(0, T, 2048):
+        hi = lo + 2048
+        s = (qd[lo:hi] @ kd[:hi].T) / math.sqrt(d)
+        i, j = torch.arange(lo, hi, device=DEV)[:, None], torch.arange(hi, device=DEV)[None]
+        p = torch.softmax(s.masked_fill_(j > i, float("-inf")), -1)
+        o = p @ vd[:hi]
+        dv[:hi] += p.T @ do[lo:hi]
+        ds = p * (do[lo:hi] @ vd[:hi].T - (do[lo:hi] * o).sum(-1, keepdim=True)) / math.sqrt(d)
+        dq[lo:hi] = ds @ kd[:hi]
+        dk[:hi] += ds.T @ qd[lo:hi]
+    for name, x in (("dq", dq), ("dk", dk), ("dv", dv)):
+        y = got[name].double()
+        if name != "dv":   # into the rotated frame
+            y = _rope(y.cpu()).to(DEV)
+        err = (y - x).abs()
+        assert float(err.max()) <= 2e-2 * float(x.abs().max()), name
+        assert float(err.norm() / x.norm()) <= 1e-2, name

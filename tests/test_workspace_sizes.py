@@ -74,3 +74,17 @@ def test_decode_workspace_of_a_larger_batch(lib, g, K, B0, batches):
         outs = [L.shared_decode_step(sq, sk, sv, skc.clone(), svc.clone(), plen.clone(), 0, 1e4,
                                      out_dtype=torch.float32, **kw) for kw in ({}, {"ws": sws})]
         assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_backward_size_follows_the_rows(lib, d):
+    # one more token costs its rows, also where key blocks start to run as
+    # parts (past 4096 tokens); long sequences need no more than as many
+    # tokens in short ones, but for their rotation table and block counts
+    for H, K in ((8, 1), (32, 4), (64, 8)):
+        size = [lib.namoh_attn_bwd_workspace_size(1, T, H, K, d) for T in range(4064, 4130)]
+        _never_smaller(size)
+        assert max(b - a for a, b in zip(size, size[1:])) < (1 << 18) * K
+        long = lib.namoh_attn_bwd_workspace_size(1, 16384, H, K, d)
+        short = lib.namoh_attn_bwd_workspace_size(4, 4096, H, K, d)
+        assert long <= short + 16384 * d // 2 * 8
