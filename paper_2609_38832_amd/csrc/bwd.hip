@@ -621,6 +621,33 @@ NAMOH_DEV void zero_unrouted(const ZeroRows& z, int T, int group) {
   }
 }
 
+// The same as a launch of its own, for large fills: a row of a head per D / 4
+// threads, at the rate of memory.
+template <int D>
+__global__ __launch_bounds__(kZeroThreads) void k_bwd_zero_unrouted(const ZeroRows z, int T, size_t rows) {
+  constexpr int C4 = D / 4, RPB = kZeroThreads / C4;
+  const size_t row = static_cast<size_t>(block_x()) * RPB + thread_x() / C4;
+  if (row >= rows) return;
+  const size_t bh = row / T;
+  const int t = static_cast<int>(row - bh * T);
+  const int b = static_cast<int>(bh / z.H), h = static_cast<int>(bh - static_cast<size_t>(b) * z.H);
+  const int32_t* tk = z.topk_idx + (static_cast<size_t>(b) * T + t) * z.K;
+  bool routed = false;
+  for (int k0 = 0; k0 < z.K; k0 += 8) {   // eight independent loads per round
+    int sv[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sv[i] = tk[min(k0 + i, z.K - 1)];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) routed |= sv[i] == h;   // clamped repeats change nothing
+  }
+  if (routed) return;
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  const size_t o = row * D + 4 * (thread_x() % C4);
+  *reinterpret_cast<float4*>(z.dq + o) = zero;
+  *reinterpret_cast<float4*>(z.dk + o) = zero;
+  *reinterpret_cast<float4*>(z.dv + o) = zero;
+}
+
 template <int D> struct BwdMfmaShape {
   static constexpr int MINB = D == 64 ? 2 : 1;   // workgroups per CU (key side)
   static constexpr int MINB_Q = 2;               // (query side; 3 at d = 64 spills)
@@ -666,8 +693,9 @@ NAMOH_DEV float* key_part_row(const KeyParts& kp, int slot, int which, int row, 
   return kp.rows + ((static_cast<size_t>(slot) * 2 + which) * kBwdMfmaBlock + row) * D;
 }
 
-// Query side: dQ~ of one (segment, 128-query block) item.
-template <int D>
+// Query side: dQ~ of one (segment, 128-query block) item.  ZERO: the first
+// workgroups write the dense gradients' zero rows.
+template <int D, bool ZERO>
 __global__ __launch_bounds__(kBwdMfmaThreads, BwdMfmaShape<D>::MINB_Q) void k_bwd_dq(
     const uint16_t* __restrict__ Qs, const uint16_t* __restrict__ dO,
     const float2* __restrict__ LD, const uint16_t* __restrict__ Kp,
@@ -686,11 +714,14 @@ __global__ __launch_bounds__(kBwdMfmaThreads, BwdMfmaShape<D>::MINB_Q) void k_bw
   // transposed (64 KB per workgroup at d = 128)
   __shared__ __attribute__((aligned(16))) uint16_t sK[2][kBN * D];
   __shared__ __attribute__((aligned(16))) uint16_t sV[2][kBN * D];
-  if (block_x() < zero.groups) {
-    zero_unrouted<D>(zero, T, block_x());
-    return;
+  int block = block_x();
+  if constexpr (ZERO) {
+    if (block < zero.groups) {
+      zero_unrouted<D>(zero, T, block);
+      return;
+    }
+    block -= zero.groups;
   }
-  const int block = block_x() - zero.groups;
   WorkItem it;
   if (!my_item(items, meta, it, block) || !bwd_item_ok(it, BH, T, Nr, max_tiles)) return;
   // a key-range part of a split block adds its keys' share of dQ~ to the
@@ -1391,10 +1422,37 @@ static hipError_t run_bwd_mfma(const void* q, const void* k, const void* v, int 
   if (tl.BM != kBwdMfmaBlock || static_cast<size_t>(tl.max_tiles) * kBN > w.rows)
     return hipErrorInvalidValue;   // the forward's blocks and tiles must match these kernels
   const double* freq = tl.freq;
+  // Dense gradients: rows of tokens not routed to the head are zero.  Fills of
+  // up to 512 MB are written by the query side's first workgroups, one on every
+  // other CU, beside the matrix work (as a launch of its own the fill runs at
+  // the memory's rate with the matrix cores idle); larger ones, about twice the
+  // last-level cache, by a launch before the packing: beside the products they
+  // take those the cached tiles, and the workgroups that write them outlast the
+  // rest where few heads are selected.  The backward with a launch / beside, us
+  // (zipf: skewed routing):
+  //   T 200, H 32, K 8, d 64 (4 MB) 21.5 / 17.4; B 4, T 4096 (302 MB) 192 / 184;
+  //   T 4096, H 64, K 1, d 128 (396 MB) 108 / 97; T 12289, H 32, K 4, d 128, zipf
+  //   (529 MB) 495 / 448; T 6000, H 64, K 1, d 128 (581 MB) 137 / 141; B 4, T 4096,
+  //   H 32, K 4, d 128 (705 MB) 262 / 287; T 8192, H 64, K 2, d 128 (780 MB) 189 /
+  //   227; T 16000, H 64, K 8, d 128 (1.4 GB) 608 / 643; B 4, T 4096, H 64, K 1, d 128
+  //   (1.6 GB) 307 / 433; but T 12289, H 64, K 4, d 128, zipf (1.1 GB) 592 / 550.
+  // Workgroups beside: 256 or 64 of them up to 10 % slower on the first four.
+  constexpr int RPB = kZeroThreads / (D / 4);
+  constexpr size_t kFillBeside = static_cast<size_t>(512) << 20;
+  const int cus = bwd_cu_count();
+  const long units = static_cast<long>(B) * ((T + RPB - 1) / RPB);
+  const size_t fill = packed ? 0 : static_cast<size_t>(B) * T * (H - K) * D * 3 * sizeof(float);
+  const ZeroRows zero{topk_idx, dq, dk, dv, B, H, K,
+                      fill == 0 || fill > kFillBeside
+                          ? 0 : static_cast<int>(std::min<long>(units, std::max(cus / 2, 1)))};
+  if (fill > kFillBeside) {
+    const size_t rows = static_cast<size_t>(BH) * T;
+    k_bwd_zero_unrouted<D><<<static_cast<unsigned>((rows + RPB - 1) / RPB), kZeroThreads, 0, st>>>(zero, T, rows);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   prof_mark("bwd_pack", true, st);
   // the key side's own list, heaviest first, placed for its own resident
   // workgroups (the query side runs the forward's list)
-  const int cus = bwd_cu_count();
   const KeySplit ks = key_split_of<D>(tl, T);
   const KeyList kl{w.kitems, w.kmeta, tl.max_items, cus, cus * BwdMfmaShape<D>::MINB,
                    ks.slots, ks.splits, tl.meta, ks.parts.slots};
@@ -1405,19 +1463,8 @@ static hipError_t run_bwd_mfma(const void* q, const void* k, const void* v, int 
   prof_mark("bwd_pack", false, st);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   prof_mark("bwd_dq", true, st);
-  // Dense gradients: rows of tokens not routed to the head are zero, written
-  // by the query side's first workgroups, one on every other CU, beside the
-  // matrix work.  As a launch of its own the fill ran at the memory's rate with
-  // the matrix cores idle (71 us of a step at T 12289, H 32, K 4, d 128).
-  // Backward, fill launched before -> 128 workgroups first: T 12289 skewed, d 128
-  // 536 -> 492 us; B 4, T 4096, K 8, d 64 201 -> 193; B 2, T 3001, K 8, d 128
-  // 155 -> 147; T 200, d 64 21.7 -> 19.3.  256 first: 508, 193, 145; 64 first
-  // 5 % and 10 % behind 128 on the first two; 256 last: 526, 207, 145.
-  constexpr int RPB = kZeroThreads / (D / 4);
-  const long units = static_cast<long>(B) * ((T + RPB - 1) / RPB);
-  const ZeroRows zero{topk_idx, dq, dk, dv, B, H, K,
-                      packed ? 0 : static_cast<int>(std::min<long>(units, std::max(cus / 2, 1)))};
-  k_bwd_dq<D><<<static_cast<unsigned>(tl.max_items + zero.groups), kBwdMfmaThreads, 0, st>>>(
+  const auto dq_kernel = zero.groups > 0 ? k_bwd_dq<D, true> : k_bwd_dq<D, false>;
+  dq_kernel<<<static_cast<unsigned>(tl.max_items + zero.groups), kBwdMfmaThreads, 0, st>>>(
       w.Qs, w.dO, w.LD, tl.Kp, w.Vp, tl.items, tl.meta, perm_token, freq, T, rope_mode,
       scale, dq, packed ? 1 : 0, BH, Nr, tl.max_tiles, tl.part, tl.part_rows, zero);
   prof_mark("bwd_dq", false, st);
