@@ -365,11 +365,15 @@ __global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
     if (rb > r0) load_rows(rb);
     take_rows(rb + grp, RPB, r1);
   }
-  if (owner && wave == 0) {   // the new token's row, in the first row group
+  if (owner && wave == 0) {
+    // the new token's row, in the first row group only: the others' weight for
+    // it is zero, and zero times an infinite value would be NaN
 #pragma unroll
     for (int u = 0; u < U; ++u) kx[u] = vx[u] = u32x4{0u, 0u, 0u, 0u};
-    kx[0] = s_new[sub];
-    vx[0] = s_new[G + sub];
+    if (grp == 0) {
+      kx[0] = s_new[sub];
+      vx[0] = s_new[G + sub];
+    }
     take_rows(grp, 1, 1);
   }
 #pragma unroll

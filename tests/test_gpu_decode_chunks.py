@@ -125,3 +125,33 @@ def test_shared_chunks(B, window, p, d=64, Hs=2):
         got.append(out[b].cpu().numpy())
         ref.append(o.numpy())
     check_out(np.array(got), np.array(ref), "bf16", what="shared decode out")
+
+
+@pytest.mark.parametrize("n", [0, 40, 700])
+@pytest.mark.parametrize("g,dtype", [(1, torch.bfloat16), (2, torch.bfloat16), (1, torch.float32)])
+def test_infinite_value_of_the_new_token(n, g, dtype, d=64, cap=900):
+    # infinite in one column of the new value: that column is infinite (its
+    # weight is positive), the others what they are without it
+    say(f"infinite new value, {n} rows before, group {g}, {dtype}")
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    kw = dict(generator=gen, device=DEV, dtype=dtype)
+    kc, vc = (torch.randn(1, 2, cap, d, **kw) for _ in range(2))
+    q, k, v = torch.randn(1, 2 * g, d, **kw), torch.randn(1, 2, d, **kw), torch.randn(1, 2, d, **kw)
+    logits = torch.randn(1, 2, generator=gen, device=DEV)
+    step = L.decode_step_grouped if g > 1 else L.decode_step
+    outs = []
+    for x in (1.0, float("inf")):
+        v[0, :, 5] = x
+        outs.append(step(logits, q, k, v, kc.clone(), vc.clone(),
+                         torch.full((1, 2), n, dtype=torch.int32, device=DEV), 2, BASE,
+                         out_dtype=torch.float32)["out"][0].cpu())
+    assert torch.isfinite(outs[0]).all() and outs[1][5] == float("inf")
+    keep = torch.arange(d) != 5
+    assert torch.equal(outs[1][keep], outs[0][keep])
+    s = torch.full((1, d), 1.0, device=DEV)   # shared heads, added to out
+    v[0, :, 5] = float("inf")
+    L.shared_decode_step(q[:, :2].contiguous(), k, v, kc, vc,
+                         torch.full((1,), n, dtype=torch.int32, device=DEV), 0, BASE, out=s,
+                         accumulate=True)
+    s = s[0].cpu()
+    assert s[5] == float("inf") and torch.isfinite(s[keep]).all()
