@@ -413,13 +413,15 @@ namoh_status namoh_shared_prefill_cache(const void* k, const void* v, int dtype,
  * cores; q/k/v rounded to bf16.  The output projection takes one of two
  * forms, chosen from the sizes (the dense form when H * d <= 384 * K and
  * H <= 64, and up to 512 * K, with d = 128 up to 1024 * K, where B * T and
- * d_model give enough output tiles; finite weights assumed in both):
+ * d_model give enough output tiles; in both a non-finite weight reaches only
+ * tokens that selected its head):
  *   per-pair: every routed pair's row h W_O^(i) is formed (rounded to bf16)
  *     and the K rows of a token are summed with their gates in k order;
  *   dense:    each token's gated head rows g h (rounded to bf16) enter one
  *     product with the stacked W_O over all H heads (unselected heads
  *     contribute exact zeros) and are summed in head order in fp32: H/K
- *     times the multiply-adds, no per-pair rows.
+ *     times the multiply-adds, no per-pair rows.  Results that are not finite
+ *     are formed again over the selected heads alone.
  * ---------------------------------------------------------------------- */
 
 /* In:  x [B, T, d_model] bf16; w_qkv as above; seg_offsets, perm_token from

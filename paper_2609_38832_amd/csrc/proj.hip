@@ -742,6 +742,49 @@ __global__ __launch_bounds__(WM * WN * kWave, OCC) void k_proj_tile(
         }
       }
     }
+    if constexpr (MODE == kProjOut) {
+      // A non-finite weight of a head that the token did not select met a zero
+      // of its row: where a result is not finite it is formed again over the
+      // selected heads alone (finite ones need no such care, and no time: one
+      // maximum over the bits of each result).
+      uint32_t top = 0;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) top = max(top, __float_as_uint(C[ct][rt][e]) & 0x7FFFFFFFu);
+      if (__builtin_expect(__any(ok && top >= 0x7F800000u), 0)) {
+        static_assert(CT * 16 <= 64, "one bit per result");
+        uint64_t bad = 0;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            bad |= static_cast<uint64_t>((__float_as_uint(C[ct][rt][e]) & 0x7FFFFFFFu) >= 0x7F800000u)
+                   << (16 * ct + e);
+        if (!ok) bad = 0;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (another lane may have stored it)
+        while (bad != 0) {
+          const int i = __ffsll(static_cast<long long>(bad)) - 1;
+          bad &= bad - 1;
+          const int col = n0 + (TN / WN) * wc + 32 * (i >> 4) + 8 * ((i & 15) >> 2) + 4 * g + (i & 3);
+          float sum = 0.f;
+          for (int h = 0; h < H; ++h) {
+            const int m = L.map[h * TM + r];
+            if (m == Nr) continue;
+            const u32x4* a = reinterpret_cast<const u32x4*>(src + static_cast<size_t>(m) * d);
+            const u32x4* b = reinterpret_cast<const u32x4*>(w + (static_cast<size_t>(h) * N + col) * d);
+            for (int x = 0; x < d / 8; ++x) {
+              const u32x4 av = a[x], bv = b[x];
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                sum = fmaf(hi_bf16(av[e]), hi_bf16(bv[e]), fmaf(lo_bf16(av[e]), lo_bf16(bv[e]), sum));
+            }
+          }
+          if constexpr (OUT_BF16) static_cast<uint16_t*>(dst0)[orow + col] = f32_to_bf16(sum);
+          else static_cast<float*>(dst0)[orow + col] = sum;
+        }
+      }
+    }
   }
   };
   if (nrow <= TM / 2)

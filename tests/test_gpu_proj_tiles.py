@@ -168,3 +168,36 @@ def test_small_out_all_rows(T, H, K, d, dm):
         t, k = (r["topk_idx"][0] == h).nonzero(as_tuple=True)
         ref[t] += rows[t, k] @ w[h].double().T
     check_out(o[0].cpu().numpy(), ref.cpu().numpy(), "bf16", what="output rows")
+
+
+# each dense tile form (short inputs; 256 x 256 up to 384 K, at 512 K and at
+# 1024 K; 128 columns for 64 heads; a split tail's half tiles), and the per-pair form
+@pytest.mark.parametrize("T,H,K,d,dm", [(300, 4, 2, 64, 256), (3072, 4, 2, 128, 2048),
+                                        (3072, 16, 2, 64, 2048), (8192, 16, 2, 128, 2048),
+                                        (4225, 64, 11, 64, 512), (2816, 16, 2, 64, 2048)])
+@pytest.mark.parametrize("odt", [torch.float32, torch.bfloat16])
+def test_non_finite_weights_stay_with_their_heads(T, H, K, d, dm, odt):
+    say(f"non-finite weights: T{T} H{H} K{K} d{d} dm{dm} {odt}")
+    g, r = _routing(1, T, H, K, 9)
+    ho = torch.randn(T * K, d, generator=g, device=DEV)
+    w = torch.randn(H, dm, d, generator=g, device=DEV, dtype=torch.bfloat16) * d ** -0.5
+    inf, nan = float("inf"), float("nan")
+    clean = L.out_proj(ho, w, r, 1, T, H, K, out_dtype=odt)
+    w2 = w.clone()
+    w2[1, 5, 3], w2[1, dm - 1, d - 1], w2[H - 1, 37] = inf, nan, -inf
+    o = L.out_proj(ho, w2, r, 1, T, H, K, out_dtype=odt)
+    bad = torch.zeros(1, T, dm, dtype=torch.bool, device=DEV)
+    for h, cols in ((1, [5, dm - 1]), (H - 1, [37])):
+        t = (r["topk_idx"][0] == h).any(1)
+        for col in cols:
+            bad[0, t, col] = True
+    assert torch.equal(~torch.isfinite(o), bad)
+    same = o == clean
+    touched = torch.zeros(dm, dtype=torch.bool, device=DEV)
+    touched[[5, 37, dm - 1]] = True
+    assert same[..., ~touched].all()
+    # the touched columns of the other tokens: float32 sums in another order
+    a, b = o[..., touched].double(), clean[..., touched].double()
+    keep = ~bad[..., touched]
+    lim = 1e-5 if odt == torch.float32 else 2 ** -7
+    assert ((a - b).abs()[keep] <= lim * (1 + b.abs()[keep])).all()
