@@ -706,6 +706,7 @@ __global__ __launch_bounds__(WM * WN * kWave, OCC) void k_proj_tile(
     const int r = (32 * RT) * wr + 32 * rt + c;
     const bool ok = r < nrow;
     size_t orow;
+    float chk = 0.f;
     if constexpr (MODE == kProjQKV) {
       const int bt = ebt[rt], b = bt / T;
       orow = ((static_cast<size_t>(b) * H + hh) * T + (bt - b * T)) * d;
@@ -716,6 +717,10 @@ __global__ __launch_bounds__(WM * WN * kWave, OCC) void k_proj_tile(
     for (int ct = 0; ct < CT; ++ct) {
       const f32x16& A = C[ct][rt];
       const int col0 = n0 + (TN / WN) * wc + 32 * ct;
+      if constexpr (MODE == kProjOut) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) chk = fmaf(A[e], 0.f, chk);   // NaN if one is not finite
+      }
       if constexpr (MODE == kProjOut && !OUT_BF16) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -745,43 +750,31 @@ __global__ __launch_bounds__(WM * WN * kWave, OCC) void k_proj_tile(
     if constexpr (MODE == kProjOut) {
       // A non-finite weight of a head that the token did not select met a zero
       // of its row: where a result is not finite it is formed again over the
-      // selected heads alone (finite ones need no such care, and no time: one
-      // maximum over the bits of each result).
-      uint32_t top = 0;
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) top = max(top, __float_as_uint(C[ct][rt][e]) & 0x7FFFFFFFu);
-      if (__builtin_expect(__any(ok && top >= 0x7F800000u), 0)) {
-        static_assert(CT * 16 <= 64, "one bit per result");
-        uint64_t bad = 0;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-          for (int e = 0; e < 16; ++e)
-            bad |= static_cast<uint64_t>((__float_as_uint(C[ct][rt][e]) & 0x7FFFFFFFu) >= 0x7F800000u)
-                   << (16 * ct + e);
-        if (!ok) bad = 0;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (another lane may have stored it)
-        while (bad != 0) {
-          const int i = __ffsll(static_cast<long long>(bad)) - 1;
-          bad &= bad - 1;
-          const int col = n0 + (TN / WN) * wc + 32 * (i >> 4) + 8 * ((i & 15) >> 2) + 4 * g + (i & 3);
+      // selected heads alone (lane (c, g): its row, half of the wave's columns).
+      if (__builtin_expect(__any(!(chk == 0.f)), 0)) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the wave's stores are done
+        constexpr int PER = OUT_BF16 ? 2 : 1;              // results per word
+        const int col0 = n0 + (TN / WN) * wc + 16 * CT * g;
+        const uint32_t* row = reinterpret_cast<const uint32_t*>(dst0) + (orow + col0) / PER;
+        for (int x = 0; ok && x < 16 * CT; ++x) {
+          uint32_t v = __hip_atomic_load(row + x / PER, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if constexpr (OUT_BF16) v = (x & 1) ? v & 0xFFFF0000u : v << 16;
+          if ((v & 0x7F800000u) != 0x7F800000u) continue;
           float sum = 0.f;
           for (int h = 0; h < H; ++h) {
             const int m = L.map[h * TM + r];
             if (m == Nr) continue;
             const u32x4* a = reinterpret_cast<const u32x4*>(src + static_cast<size_t>(m) * d);
-            const u32x4* b = reinterpret_cast<const u32x4*>(w + (static_cast<size_t>(h) * N + col) * d);
-            for (int x = 0; x < d / 8; ++x) {
-              const u32x4 av = a[x], bv = b[x];
+            const u32x4* b = reinterpret_cast<const u32x4*>(w + (static_cast<size_t>(h) * N + col0 + x) * d);
+            for (int i = 0; i < d / 8; ++i) {
+              const u32x4 av = a[i], bv = b[i];
 #pragma unroll
               for (int e = 0; e < 4; ++e)
                 sum = fmaf(hi_bf16(av[e]), hi_bf16(bv[e]), fmaf(lo_bf16(av[e]), lo_bf16(bv[e]), sum));
             }
           }
-          if constexpr (OUT_BF16) static_cast<uint16_t*>(dst0)[orow + col] = f32_to_bf16(sum);
-          else static_cast<float*>(dst0)[orow + col] = sum;
+          if constexpr (OUT_BF16) static_cast<uint16_t*>(dst0)[orow + col0 + x] = f32_to_bf16(sum);
+          else static_cast<float*>(dst0)[orow + col0 + x] = sum;
         }
       }
     }
