@@ -372,7 +372,7 @@ namoh_status namoh_shared_attn(const void* q, const void* k, const void* v, int 
  *      gets no shared-head term and *dev_status (if non-NULL) is set to 1.
  *      cache_len int32 [B].
  * Out: out [B, d] of out_dtype.  Workspace: namoh_shared_decode_workspace_size
- *      bytes (rotated queries, history extents, per-chunk partials).
+ *      bytes (per-chunk partials).
  * Limits: Hs <= 1024, B*Hs*ceil(cap/512) < 2^31.
  * ---------------------------------------------------------------------- */
 size_t namoh_shared_decode_workspace_size(int B, int Hs, int d_head, int cap);

@@ -57,7 +57,6 @@ template <> struct MfmaShape<128> {
 // 2^kLazyLog2 and the final normalisation is exact), so the output
 // accumulator is rarely rescaled.
 constexpr float kLazyLog2 = 8.f;
-constexpr int kGenericBM = 64;   // (the float32 path's share of the workspace)
 
 constexpr int kPackThreads = 256;
 
@@ -1091,8 +1090,7 @@ static int device_cu_count() {
   return n;
 }
 
-static int block_queries(int d, int dtype) {
-  if (!use_mfma(d, dtype)) return kGenericBM;
+static int block_queries(int d) {
   return d == 64 ? 32 * MfmaShape<64>::NQT * MfmaShape<64>::NW
                  : 32 * MfmaShape<128>::NQT * MfmaShape<128>::NW;
 }
@@ -1124,27 +1122,25 @@ constexpr int kSplitCUs = 256;
 static AttnWs carve_attn(void* ws, int B, int T, int H, int K, int d, int dtype, int G = 1) {
   const size_t BH = static_cast<size_t>(B) * H;
   const size_t Nr = static_cast<size_t>(B) * T * K;
-  const int BM = block_queries(d, dtype);
-  AttnWs w;
-  w.split_slots = !use_mfma(d, dtype)
-                      ? 0
-                      : kSplitCUs * (d == 64 ? MfmaShape<64>::MINB : MfmaShape<128>::MINB);
+  const int BM = block_queries(d);
+  AttnWs w{};
+  Carver cv(ws);
+  if (!use_mfma(d, dtype)) {   // the float32 path: the rotation table and the head outputs
+    w.table = cv.take<float2>(static_cast<size_t>(T) * (d / 2));
+    w.hpack = cv.take<float>(Nr * G * d);
+    w.bytes = cv.off;
+    return w;
+  }
+  w.split_slots = kSplitCUs * (d == 64 ? MfmaShape<64>::MINB : MfmaShape<128>::MINB);
   w.max_items = (Nr / BM + BH + 1) * G + static_cast<size_t>(w.split_slots);
   w.max_tiles = Nr / kBN + BH + 1;
-  Carver cv(ws);
   w.meta = cv.take<int32_t>(kMetaCount);
   w.items = cv.take<WorkItem>(w.max_items);
   w.table = cv.take<float2>(static_cast<size_t>(T) * (d / 2));
-  if (use_mfma(d, dtype)) {
-    w.Kp = cv.take<uint16_t>(w.max_tiles * kBN * d);
-    w.Vt = cv.take<uint16_t>(w.max_tiles * kBN * d);
-    w.knorm = cv.take<float>(w.max_tiles);
-    w.freq = cv.take<double>(64);
-  } else {
-    w.Kp = w.Vt = nullptr;
-    w.knorm = nullptr;
-    w.freq = nullptr;
-  }
+  w.Kp = cv.take<uint16_t>(w.max_tiles * kBN * d);
+  w.Vt = cv.take<uint16_t>(w.max_tiles * kBN * d);
+  w.knorm = cv.take<float>(w.max_tiles);
+  w.freq = cv.take<double>(64);
   w.hpack = cv.take<float>(Nr * G * d);
   const size_t ps = 2 * static_cast<size_t>(w.split_slots);
   w.splits = cv.take<SplitItem>(static_cast<size_t>(w.split_slots));
@@ -1222,7 +1218,6 @@ hipError_t launch_attn(const void* q, const void* k, const void* v, int dtype,
   // combine); the combine accumulates in fp32 either way.
   const bool hb = head_out == nullptr && use_mfma(d, dtype);
   void* hout = head_out ? static_cast<void*>(head_out) : static_cast<void*>(w.hpack);
-  const int BM = block_queries(d, dtype);
   const int Nr = B * T * K;
   const double log_base = rope_mode == 2 ? 0.0 : std::log(static_cast<double>(rope_base));
   // the MFMA path forms its rotation factors in the kernels; the fp32 path
@@ -1260,8 +1255,8 @@ hipError_t launch_attn(const void* q, const void* k, const void* v, int dtype,
   if (hb) {
     pr.part_o = w.part_o;
     pr.part_ml = w.part_ml;
-    pr.BM = BM;
-    pr.rows = 2 * w.split_slots * BM;
+    pr.BM = block_queries(d);
+    pr.rows = 2 * w.split_slots * pr.BM;
   }
   if (hb && out_dtype == 1)
     launch_k("combine", G == 1 ? k_combine<true, true, 1, true> : k_combine<true, true, 0, true>,
@@ -1448,7 +1443,7 @@ void attn_stats_tiles(void* ws, int B, int T, int H, int K, int d, AttnTiles& ti
   tiles.h = w.hpack;
   tiles.max_items = static_cast<int>(w.max_items);
   tiles.max_tiles = static_cast<int>(w.max_tiles);
-  tiles.BM = block_queries(d, 1);
+  tiles.BM = block_queries(d);
   tiles.part_rows = 2 * w.split_slots * tiles.BM;
 }
 

@@ -913,7 +913,7 @@ __global__ __launch_bounds__(kBwdMfmaThreads, BwdMfmaShape<D>::MINB) void k_bwd_
     const int32_t* __restrict__ meta, const int32_t* __restrict__ perm_token,
     const double* __restrict__ freq, int T, int rope_mode, float* __restrict__ dk,
     float* __restrict__ dv, int packed, int BH, int Nr, int max_tiles, int n_list, DqMerge dqm, KeyParts kp) {
-  constexpr int NT = kBwdMfmaThreads, BM = kBwdMfmaBlock;
+  constexpr int NT = kBwdMfmaThreads;
   constexpr int KS = D / 16, MT = D / 32;
   constexpr int KPT = kBN * D / 8 / NT;
   constexpr size_t TS = static_cast<size_t>(kBN) * D;
@@ -1074,7 +1074,7 @@ __global__ __launch_bounds__(2 * kBwdMfmaThreads, 1) void k_bwd_dkdv8(
     const int32_t* __restrict__ meta, const int32_t* __restrict__ perm_token,
     const double* __restrict__ freq, int T, int rope_mode, float* __restrict__ dk,
     float* __restrict__ dv, int packed, int BH, int Nr, int max_tiles, int n_list, DqMerge dqm, KeyParts kp) {
-  constexpr int NT = 2 * kBwdMfmaThreads, BM = kBwdMfmaBlock;
+  constexpr int NT = 2 * kBwdMfmaThreads;
   constexpr int KS = D / 16, MT = D / 32;
   constexpr int KPT = kBN * D / 8 / NT;
   constexpr size_t TS = static_cast<size_t>(kBN) * D;

@@ -778,8 +778,6 @@ static size_t dec_partials(size_t heads, int cap, int d) {
 }
 
 struct DecWs {
-  float* qrot;
-  int32_t* rows;
   float* part_acc;
   float* part_ml;
   size_t bytes;
@@ -790,8 +788,6 @@ static DecWs carve_dec(void* ws, int B, int K, int d, int cap, int G = 1) {
   const size_t np = dec_partials(BK, cap, d);
   Carver cv(ws);
   DecWs w;
-  w.qrot = cv.take<float>(BK * G * d);
-  w.rows = cv.take<int32_t>(BK);
   w.part_acc = cv.take<float>(np * G * d);
   w.part_ml = cv.take<float>(np * G * 2);
   w.bytes = cv.off;
@@ -1060,11 +1056,6 @@ __global__ __launch_bounds__(256) void k_shared_prefill_cache(
 }
 
 struct SharedDecWs {
-  float* qrot;
-  int32_t* rows;
-  int32_t* row0;
-  int32_t* heads;
-  float* gates;
   float* part_acc;
   float* part_ml;
   size_t bytes;
@@ -1075,11 +1066,6 @@ static SharedDecWs carve_shared_dec(void* ws, int B, int Hs, int d, int cap) {
   const size_t np = dec_partials(BS, cap, d);
   Carver cv(ws);
   SharedDecWs w;
-  w.qrot = cv.take<float>(BS * d);
-  w.rows = cv.take<int32_t>(BS);
-  w.row0 = cv.take<int32_t>(BS);
-  w.heads = cv.take<int32_t>(BS);
-  w.gates = cv.take<float>(BS);
   w.part_acc = cv.take<float>(np * d);
   w.part_ml = cv.take<float>(np * 2);
   w.bytes = cv.off;

@@ -92,13 +92,12 @@ NAMOH_DEV void proj_load(u32x4 (&xr)[XG], u32x4 (&wr)[WG], const void* __restric
 // into registers while the current one is multiplied from LDS.  src = packed
 // head outputs [Nr, d] (f32 if SRC_F32, else bf16; rounded to bf16 as they
 // are staged), w = W_O [H, d_model, d] bf16, kdim = d, N = d_model; output Y
-// [Nr, d_model] bf16 (dst0).
-template <int MODE, int NT, bool SRC_F32>
+// [Nr, d_model] bf16 (dst).
+template <int NT, bool SRC_F32>
 __global__ __launch_bounds__(kProjThreads, 2) void k_proj_gemm(
     const void* __restrict__ src, const uint16_t* __restrict__ w,
-    const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ perm_token, int BH,
-    int H, int T, int Nr, int kdim, int N, int d, uint16_t* __restrict__ dst0,
-    uint16_t* __restrict__ dst1, uint16_t* __restrict__ dst2) {
+    const int32_t* __restrict__ seg_offsets, int BH, int H, int T, int Nr, int kdim, int N,
+    uint16_t* __restrict__ dst) {
   static_assert(NT % 32 == 0 && (NT * kProjKC / 8) % kProjThreads == 0, "column tile");
   constexpr int CT = NT / 32;                                  // 32-column MFMA tiles
   constexpr int XG = kProjRows * kProjKC / 8 / kProjThreads;   // data granules per thread
@@ -199,7 +198,7 @@ __global__ __launch_bounds__(kProjThreads, 2) void k_proj_gemm(
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int col = n0 + 32 * t2 + 8 * j + 4 * g;
-        *reinterpret_cast<uint2*>(dst0 + orow + col) =
+        *reinterpret_cast<uint2*>(dst + orow + col) =
             make_uint2(pack_bf16x2(C[t2][4 * j], C[t2][4 * j + 1]),
                        pack_bf16x2(C[t2][4 * j + 2], C[t2][4 * j + 3]));
       }
@@ -926,13 +925,13 @@ hipError_t launch_out_proj(const void* head_out, int head_out_dtype, const void*
   const dim3 grid(proj_row_tiles(B, T, H, K), static_cast<unsigned>(d_model / 128));
   prof_mark("out_proj", true, st);
   if (head_out_dtype == 0)
-    k_proj_gemm<kProjOut, 128, true><<<grid, kProjThreads, 0, st>>>(
-        head_out, static_cast<const uint16_t*>(w_o), seg_offsets, nullptr, B * H, H, T,
-        B * T * K, d, d_model, d, Y, nullptr, nullptr);
+    k_proj_gemm<128, true><<<grid, kProjThreads, 0, st>>>(
+        head_out, static_cast<const uint16_t*>(w_o), seg_offsets, B * H, H, T, B * T * K, d, d_model,
+        Y);
   else
-    k_proj_gemm<kProjOut, 128, false><<<grid, kProjThreads, 0, st>>>(
-        head_out, static_cast<const uint16_t*>(w_o), seg_offsets, nullptr, B * H, H, T,
-        B * T * K, d, d_model, d, Y, nullptr, nullptr);
+    k_proj_gemm<128, false><<<grid, kProjThreads, 0, st>>>(
+        head_out, static_cast<const uint16_t*>(w_o), seg_offsets, B * H, H, T, B * T * K, d, d_model,
+        Y);
   prof_mark("out_proj", false, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
