@@ -1457,7 +1457,7 @@ hipError_t launch_attn_stats(const void* q, const void* k, const void* v, int B,
   const double log_base = rope_mode == 2 ? 0.0 : std::log(static_cast<double>(rope_base));
   const float sl2 = scale * 1.4426950408889634f;
   // key-range parts as in the inference forward (the backward's query side
-  // runs the same parts; the key side takes each split block once)
+  // runs the same parts; the key side cuts blocks of its own list)
   if (d == 64)
     launch_mfma<64>(w, q, k, v, B, T, H, 1, Nr, rope_mode, log_base, sl2, seg_offsets,
                     perm_token, w.hpack, false, lse, st, 0, true);

@@ -247,8 +247,17 @@ struct KeyList {
 // idle at the end).  Blocks with more than a fair share are cut as the forward
 // cuts its query blocks; a part writes its dK, dV sums to the block's partial
 // rows, which k_bwd_kv_merge adds in part order.  Only blocks of at least
-// kKeySplitTiles query tiles: then no block is cut at T <= 4096, and the
-// merge launch (about 4 us, also when nothing was cut) is left out there.
+// kKeySplitTiles query tiles, so none at T <= 4096, where the merge launch is
+// left out: it costs 1.5 to 2.5 us also when nothing was cut, as the host does not
+// know the lengths.  Backward in us, whole blocks -> parts, H 32 (zipf: skewed
+// routing; one sequence unless B is given):
+//   past the line   T 5000, K 4, d 64 45.5 -> 47.3, zipf 138 -> 129; T 8192, K 4,
+//                   d 128 105 -> 107; T 8192, d 64, zipf 195 -> 140; T 12289, d 128,
+//                   zipf 545 -> 412;
+//   before it (blocks from 33 tiles on cut)   T 3000, K 4, d 64 33.5 -> 36.1, d 128
+//                   55.6 -> 57.1; B 4, T 4096, K 4, d 128, zipf 252 -> 257; but T 4096,
+//                   K 4, d 128, zipf 202 -> 150, one head of 3000 tokens 164 -> 140.
+// Short balanced calls, which pay 2 to 8 %, are the more common ones there.
 constexpr int kKeySplitTiles = 65;
 static bool key_split(int T) { return T > (kKeySplitTiles - 1) * kBN; }
 
@@ -655,9 +664,9 @@ template <int D> struct BwdMfmaShape {
 
 // A work record checked before it addresses anything (the saved backward
 // takes the list from the caller's workspace): its segment, rows and tiles
-// inside the packed arrays, a whole item (the backward's list holds no
-// key-range parts) and a block inside its segment.  A record that fails is
-// skipped.
+// inside the packed arrays, a block inside its segment, and the block's tiles
+// or a part of them (the partial slot of a part is checked where it is used).
+// A record that fails is skipped.
 NAMOH_DEV bool bwd_item_ok(const WorkItem& it, int BH, int T, int Nr, int max_tiles) {
   if (it.s < 0 || it.s >= BH || it.n <= 0 || it.n > T || it.seg0 < 0 || it.seg0 > Nr - it.n)
     return false;

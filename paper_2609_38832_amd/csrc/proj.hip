@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256) void k_out_map(
 //     sequences of the batch one after another (only each head's last tile is
 //     padded, not each segment's); gathered x rows; columns of W_QKV[h].
 //   kProjOut: the data rows are consecutive tokens; the reduction runs over
-//     H * d (chunk c belongs to head c / (d / 32)); the rows are the tokens'
+//     H * d (chunk c belongs to head c / (d / 64)); the rows are the tokens'
 //     gated head rows G found through the head map (the zero row for
 //     unselected heads).
 constexpr int kXcds = 8;        // XCDs of the device; workgroup i runs on XCD i % 8
