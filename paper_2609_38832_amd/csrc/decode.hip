@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "internal.h"
@@ -141,10 +142,30 @@ NAMOH_DEV bool dec_head(const DecStep& a, int bk, int chunk, DecHead& o) {
       aff = static_cast<float>(af);
       key = real ? static_cast<float>(af + static_cast<double>(a.bias[min(lane, a.H - 1)])) : 0.f;
     }
-    int rank = 0;
-    for (int j = 0; j < a.H; ++j) {
-      const float kj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(key), j));
-      rank += (kj > key) || (kj == key && j < lane);
+    // ranks below `need` (the workgroup that writes the selection: all K): the
+    // maximum of what is left, lowest index first, `need` times over, or H
+    // comparisons where those are fewer instructions (or a key is NaN).  With
+    // many workgroups the VALU is the limit, with few this chain (32 heads, 8
+    // selected, d 64, comparisons -> maxima: 945 sequences of 24 rows 61 -> 56 us a
+    // step, one of 300 rows 10.6 -> 9.7)
+    const int need = kk == 0 && chunk == 0 ? a.K : kk + 1;
+    int rank = a.H;
+    if (5 * need <= 2 * a.H && __ballot(real && key != key) == 0) {
+      const uint32_t u = __float_as_uint(key + 0.f);   // (-0 and 0 are equal)
+      int left = real ? static_cast<int>(u ^ (static_cast<int>(u) < 0 ? 0x7FFFFFFFu : 0u)) : INT32_MIN;
+      for (int r = 0; r < need; ++r) {
+        const uint64_t at = __ballot(left == wave_max_i(left));
+        if (lane == __ffsll(static_cast<long long>(at)) - 1) {
+          rank = r;
+          left = INT32_MIN;
+        }
+      }
+    } else {
+      rank = 0;
+      for (int j = 0; j < a.H; ++j) {
+        const float kj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(key), j));
+        rank += (kj > key) || (kj == key && j < lane);
+      }
     }
     const bool sel = real && rank < a.K;
     if (kk == 0 && chunk == 0) {
@@ -317,11 +338,12 @@ __global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
     for (int e = 0; e < EPG; ++e) acc[u][e] = 0.f;
   }
 
-  // the rows in kx, vx (row u of the lane counts if r + u step < end)
-  auto take_rows = [&](int r, int step, int end) {
-    float sc[GQ][U];
+  // the first UU rows in kx, vx (row u of the lane counts if r + u step < end)
+  auto take_rows = [&](auto uu, int r, int step, int end) {
+    constexpr int UU = decltype(uu)::value;
+    float sc[GQ][UU];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < UU; ++u) {
       float f[EPG];
       dec_unpack<BF16>(kx[u], f);
 #pragma unroll
@@ -333,26 +355,26 @@ __global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
         sc[qq][u] = r + u * step < end ? dsum : -INFINITY;
       }
     }
-    float p[GQ][U];
+    float p[GQ][UU];
 #pragma unroll
     for (int qq = 0; qq < GQ; ++qq) {
       float mx = sc[qq][0];
 #pragma unroll
-      for (int u = 1; u < U; ++u) mx = fmaxf(mx, sc[qq][u]);
+      for (int u = 1; u < UU; ++u) mx = fmaxf(mx, sc[qq][u]);
       const float mnew = fmaxf(m[qq], mx);
       const float corr = __builtin_amdgcn_exp2f(m[qq] - mnew);
       lsum[qq] *= corr;
 #pragma unroll
       for (int e = 0; e < EPG; ++e) acc[qq][e] *= corr;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
+      for (int u = 0; u < UU; ++u) {
         p[qq][u] = __builtin_amdgcn_exp2f(sc[qq][u] - mnew);
         lsum[qq] += p[qq][u];
       }
       m[qq] = mnew;
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < UU; ++u) {
       float f[EPG];
       dec_unpack<BF16>(vx[u], f);
 #pragma unroll
@@ -363,18 +385,22 @@ __global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
   };
   for (int rb = r0; rb < r1; rb += RPB * U) {
     if (rb > r0) load_rows(rb);
-    take_rows(rb + grp, RPB, r1);
+    // as few of the row slots as hold the rows that are left (the others would
+    // change nothing): 945 sequences x 8 heads of 24 rows, d 64, 56 -> 47 us
+    const int left = r1 - rb;
+    if (left > RPB * U / 2) take_rows(std::integral_constant<int, U>{}, rb + grp, RPB, r1);
+    else if (left > RPB * U / 4) take_rows(std::integral_constant<int, U / 2>{}, rb + grp, RPB, r1);
+    else take_rows(std::integral_constant<int, U / 4 ? U / 4 : 1>{}, rb + grp, RPB, r1);
   }
   if (owner && wave == 0) {
     // the new token's row, in the first row group only: the others' weight for
     // it is zero, and zero times an infinite value would be NaN
-#pragma unroll
-    for (int u = 0; u < U; ++u) kx[u] = vx[u] = u32x4{0u, 0u, 0u, 0u};
+    kx[0] = vx[0] = u32x4{0u, 0u, 0u, 0u};
     if (grp == 0) {
       kx[0] = s_new[sub];
       vx[0] = s_new[G + sub];
     }
-    take_rows(grp, 1, 1);
+    take_rows(std::integral_constant<int, 1>{}, grp, 1, 1);
   }
 #pragma unroll
   for (int qq = 0; qq < GQ; ++qq) {
