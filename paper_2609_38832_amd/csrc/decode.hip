@@ -16,6 +16,9 @@
 //                          rows (a row spans d*esize/16 lanes), several rows
 //                          in flight per lane, online softmax in exp2 domain,
 //                          one (max, sum, acc[d]) partial per chunk.
+//   k_decode_route         the routing, the append and the queries' rotation as
+//                          a launch before it, where many sequences have short
+//                          histories.
 //   k_decode_combine       merges the chunk partials of each head by
 //                          log-sum-exp, sums the gated head outputs and
 //                          advances the cache lengths.
@@ -83,6 +86,8 @@ struct DecStep {
   int32_t* dev_status;
   int nchunk, fine;        // chunks per head; dec_chunk_rows
   float *part_acc, *part_ml;
+  int32_t* ahead;          // k_decode_route's: history (or -1) of every selected
+  float* qrot;             // head, its rotated, scaled queries [G, D]
 };
 
 // The head a workgroup (selected head bk, chunk) works on: its history before
@@ -251,6 +256,42 @@ NAMOH_DEV void dec_unpack(const u32x4 x, float* f) {
   }
 }
 
+// The routing, the append and the queries' rotation as a launch of their own
+// (one wave per selected head, G query heads each), for launches of many short
+// chunks: see dec_route_ahead.
+template <int D, bool BF16>
+__global__ __launch_bounds__(64) void k_decode_route(const DecStep a, int G) {
+  __shared__ float2 s_cs[D / 2];
+  __shared__ u32x4 s_new[2 * D * (BF16 ? 2 : 4) / 16];
+  const int bk = block_x(), j = thread_x();
+  DecHead hd;
+  const bool ok = dec_head<D, false>(a, bk, 0, hd);
+  if (j == 0) a.ahead[bk] = ok ? hd.hist : -1;
+  if (!ok) return;
+  dec_new_token<D, BF16>(a, hd, true, s_cs, s_new);
+  if (j >= D / 2) return;
+  const float2 w = s_cs[j];   // (written by this thread)
+  for (int u = 0; u < G; ++u) {
+    const size_t src = (hd.bh * G + u) * D + j, dst = (static_cast<size_t>(bk) * G + u) * D + j;
+    const float q1 = ld_elem<BF16>(a.q, src), q2 = ld_elem<BF16>(a.q, src + D / 2);
+    a.qrot[dst] = (q1 * w.x - q2 * w.y) * a.qscale;
+    a.qrot[dst + D / 2] = (q2 * w.x + q1 * w.y) * a.qscale;
+  }
+}
+
+// dec_head after k_decode_route: the new token's row is one of the history's.
+template <int D>
+NAMOH_DEV bool dec_head_ahead(const DecStep& a, int bk, int chunk, DecHead& o) {
+  const int n = __builtin_amdgcn_readfirstlane(a.ahead[bk]);
+  const int h = __builtin_amdgcn_readfirstlane(a.topk_idx[bk]);
+  if (n < 0) return false;
+  o.bh = static_cast<size_t>(bk / a.K) * a.H + h;
+  o.hist = n + 1;
+  o.ring0 = 0;
+  o.chunk = dec_chunk_rows<D>(n + 1, a.nchunk, a.fine);
+  return chunk * o.chunk <= n;
+}
+
 // GQ queries per history row (the query heads of a key/value group; 1
 // without groups): each row is read once and scored against all of them, with
 // one online softmax per query; the partial of query u of selected head bk is
@@ -260,7 +301,8 @@ NAMOH_DEV void dec_unpack(const u32x4 x, float* f) {
 // The new token's row is not read from the cache (the workgroup whose chunk it
 // ends writes it): it is scored from LDS after the history.  The first rows of
 // the history are loaded before the new token's angles are formed.
-template <int D, bool BF16, int GQ = 1, bool SHARED = false>
+// AHEAD: k_decode_route ran before.
+template <int D, bool BF16, int GQ = 1, bool SHARED = false, bool AHEAD = false>
 __global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
   constexpr int EPG = BF16 ? 8 : 4;   // elements per 16-byte granule
   constexpr int G = D / EPG;          // lanes per row
@@ -276,10 +318,14 @@ __global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
   const int bk = block_x() / a.nchunk;
   const int chunk = block_x() - bk * a.nchunk;
   DecHead hd;
-  if (!dec_head<D, SHARED>(a, bk, chunk, hd)) return;
+  if constexpr (AHEAD) {
+    if (!dec_head_ahead<D>(a, bk, chunk, hd)) return;
+  } else {
+    if (!dec_head<D, SHARED>(a, bk, chunk, hd)) return;
+  }
   const int r0 = chunk * hd.chunk;
   const int r1 = min(hd.hist, r0 + hd.chunk);   // cached rows [r0, r1)
-  const bool owner = hd.hist < r0 + hd.chunk;   // the new row ends this chunk
+  const bool owner = !AHEAD && hd.hist < r0 + hd.chunk;   // the new row ends this chunk
   const size_t rowbase = hd.bh * a.cap;
   const int tid = thread_x();
   const int lane = tid % 64, wave = tid / 64;
@@ -305,28 +351,37 @@ __global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
       }
     }
   };
-  // the lane's granule of each query and its rotation partner's
-  u32x4 qx[GQ], qy[GQ];
-  const int mate = sub < G / 2 ? sub + G / 2 : sub - G / 2;
-#pragma unroll
-  for (int u = 0; u < GQ; ++u) {
-    const u32x4* qrow = static_cast<const u32x4*>(a.q) + (hd.bh * GQ + u) * G;
-    qx[u] = qrow[sub];
-    qy[u] = qrow[mate];
-  }
-  load_rows(r0);
-  dec_new_token<D, BF16>(a, hd, owner, s_cs, s_new);
-  __syncthreads();
   float qv[GQ][EPG];
+  if constexpr (AHEAD) {
 #pragma unroll
-  for (int u = 0; u < GQ; ++u) {
-    float x[EPG], y[EPG];
-    dec_unpack<BF16>(qx[u], x);
-    dec_unpack<BF16>(qy[u], y);
+    for (int u = 0; u < GQ; ++u)
 #pragma unroll
-    for (int e = 0; e < EPG; ++e) {
-      const float2 w = s_cs[(sub % (G / 2)) * EPG + e];
-      qv[u][e] = (sub < G / 2 ? x[e] * w.x - y[e] * w.y : x[e] * w.x + y[e] * w.y) * a.qscale;
+      for (int e = 0; e < EPG; ++e)
+        qv[u][e] = a.qrot[(static_cast<size_t>(bk) * GQ + u) * D + sub * EPG + e];
+    load_rows(r0);
+  } else {
+    // the lane's granule of each query and its rotation partner's
+    u32x4 qx[GQ], qy[GQ];
+    const int mate = sub < G / 2 ? sub + G / 2 : sub - G / 2;
+#pragma unroll
+    for (int u = 0; u < GQ; ++u) {
+      const u32x4* qrow = static_cast<const u32x4*>(a.q) + (hd.bh * GQ + u) * G;
+      qx[u] = qrow[sub];
+      qy[u] = qrow[mate];
+    }
+    load_rows(r0);
+    dec_new_token<D, BF16>(a, hd, owner, s_cs, s_new);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < GQ; ++u) {
+      float x[EPG], y[EPG];
+      dec_unpack<BF16>(qx[u], x);
+      dec_unpack<BF16>(qy[u], y);
+#pragma unroll
+      for (int e = 0; e < EPG; ++e) {
+        const float2 w = s_cs[(sub % (G / 2)) * EPG + e];
+        qv[u][e] = (sub < G / 2 ? x[e] * w.x - y[e] * w.y : x[e] * w.x + y[e] * w.y) * a.qscale;
+      }
     }
   }
   float m[GQ], lsum[GQ], acc[GQ][EPG];
@@ -454,7 +509,7 @@ __global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
 // The reduction group kg = l / 16 of every layout holds queries 4 kg .. 4 kg
 // + 3, so a lane's rescale factors apply to its own output accumulators.
 // Partials as in k_decode_attn: (bk * GQ + q) * nchunk + chunk.
-template <int D, int GQ>
+template <int D, int GQ, bool AHEAD>
 __global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(const DecStep a) {
   static_assert(GQ == 4 || GQ == 8, "queries per cached row");
   static_assert(D == 64 || D == 128, "head width");
@@ -480,23 +535,38 @@ __global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(const DecStep a) {
   const int bk = block_x() / a.nchunk;
   const int chunk = block_x() - bk * a.nchunk;
   DecHead hd;
-  if (!dec_head<D, false>(a, bk, chunk, hd)) return;
+  if constexpr (AHEAD) {
+    if (!dec_head_ahead<D>(a, bk, chunk, hd)) return;
+  } else {
+    if (!dec_head<D, false>(a, bk, chunk, hd)) return;
+  }
   const int r0 = chunk * hd.chunk;
-  const int n = hd.hist;                       // the new token's row
+  const int n = AHEAD ? hd.hist - 1 : hd.hist;   // the new token's row
   const int r1 = min(n + 1, r0 + hd.chunk);
   const bool owner = n < r0 + hd.chunk;
   const size_t rowbase = hd.bh * a.cap;
   const int tid = thread_x();
   const int lane = tid % 64, wave = tid / 64;
   const int j16 = lane & 15, kg = lane >> 4;
-  const int w0 = r0 + wave * (hd.chunk / 4);
-  const int w1 = min(r1, w0 + hd.chunk / 4);
+  // (after k_decode_route: many workgroups, and the waves share short chunks)
+  const int rpw = AHEAD ? ((r1 - r0 + 3) / 4 + 31) / 32 * 32 : hd.chunk / 4;
+  const int w0 = r0 + wave * rpw;
+  const int w1 = min(r1, w0 + rpw);
 
   // the lane's queries' granules (A operand rows >= GQ are zero: they read
   // query GQ - 1 and are cleared after the loads; a load under a branch would
   // be waited for at the join, one round trip per load)
   u32x4 qx[KS];
-  {
+  float4 qf[KS][2];
+  if constexpr (AHEAD) {
+    const float4* qrow = reinterpret_cast<const float4*>(
+        a.qrot + (static_cast<size_t>(bk) * GQ + min(j16, GQ - 1)) * D + 8 * kg);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      qf[s][0] = qrow[8 * s];
+      qf[s][1] = qrow[8 * s + 1];
+    }
+  } else {
     const u32x4* qrow = static_cast<const u32x4*>(a.q) + (hd.bh * GQ + min(j16, GQ - 1)) * GR + kg;
 #pragma unroll
     for (int s = 0; s < KS; ++s) qx[s] = qrow[4 * s];
@@ -531,27 +601,37 @@ __global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(const DecStep a) {
     }
   };
   if (w0 < w1) load_block(w0, kx, vx);
-  dec_new_token<D, true>(a, hd, owner, s_cs, s_new);
-  __syncthreads();
-  // rotated, scaled queries: pair (j, j + D / 2) is granules s and s + KS / 2
   bf16x8 qa[KS];
+  const bool keep = j16 < GQ;
+  if constexpr (AHEAD) {
 #pragma unroll
-  for (int s = 0; s < KS / 2; ++s) {
-    float x[8], y[8];
-    dec_unpack<true>(qx[s], x);
-    dec_unpack<true>(qx[s + KS / 2], y);
-    const bool keep = j16 < GQ;
+    for (int s = 0; s < KS; ++s) {
+      const float x[8] = {qf[s][0].x, qf[s][0].y, qf[s][0].z, qf[s][0].w,
+                          qf[s][1].x, qf[s][1].y, qf[s][1].z, qf[s][1].w};
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float2 w = s_cs[32 * s + 8 * kg + e];
-      qa[s][e] = static_cast<__bf16>(keep ? (x[e] * w.x - y[e] * w.y) * a.qscale : 0.f);
-      qa[s + KS / 2][e] = static_cast<__bf16>(keep ? (y[e] * w.x + x[e] * w.y) * a.qscale : 0.f);
+      for (int e = 0; e < 8; ++e) qa[s][e] = static_cast<__bf16>(keep ? x[e] : 0.f);
     }
+  } else {
+    dec_new_token<D, true>(a, hd, owner, s_cs, s_new);
+    __syncthreads();
+    // rotated, scaled queries: pair (j, j + D / 2) is granules s and s + KS / 2
+#pragma unroll
+    for (int s = 0; s < KS / 2; ++s) {
+      float x[8], y[8];
+      dec_unpack<true>(qx[s], x);
+      dec_unpack<true>(qx[s + KS / 2], y);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float2 w = s_cs[32 * s + 8 * kg + e];
+        qa[s][e] = static_cast<__bf16>(keep ? (x[e] * w.x - y[e] * w.y) * a.qscale : 0.f);
+        qa[s + KS / 2][e] = static_cast<__bf16>(keep ? (y[e] * w.x + x[e] * w.y) * a.qscale : 0.f);
+      }
+    }
+    __syncthreads();
   }
-  __syncthreads();
   for (int rb = w0; rb < w1; rb += 32) {
     load_block(min(rb + 32, w1 - 1), kn, vn);
-    if (rb + 32 > n) {   // the new token's row (and rows clamped to it) from LDS
+    if (!AHEAD && rb + 32 > n) {   // the new token's row (and rows clamped to it) from LDS
       const u32x4 nk = s_new[lg], nv = s_new[GR + lg];
 #pragma unroll
       for (int i = 0; i < RPL; ++i)
@@ -803,7 +883,32 @@ static size_t dec_partials(size_t heads, int cap, int d) {
   return std::max(whole, std::min(fine, static_cast<size_t>(kDecSpreadGroups)));
 }
 
+// Routing ahead (k_decode_route): where a launch has many workgroups of few
+// rows each, finding the head, forming the angles and rotating the queries in
+// every one of them costs more than a launch (the VALU is the limit; on the
+// matrix cores two or three workgroups per compute unit, each a chain of
+// latencies).  A step in us, routed in every workgroup -> ahead:
+//   g 1, d 64   945 sequences x 8 heads of 24 rows 46 -> 32, 512 x 8 of 100 34 -> 30,
+//               256 x 8 of 30 16.8 -> 15.8; but 128 x 8 of 100 12.5 -> 14.2, 1024 x 4
+//               of 1000 193 -> 198;
+//   g 1, d 128  600 x 16 of 20 55 -> 32; but 512 x 8 of 400 161 -> 165;
+//   g 1, d 32   1009 x 4 of 355 78 -> 57, 400 x 8 of 1000 91 -> 85;
+//   g 4, d 64   489 x 8 of 162 100 -> 66; d 128, 723 x 4 of 80 67 -> 48, 306 x 1 of
+//               1277 56 -> 52; but g 8, d 64, 665 x 1 of 1546 59 -> 65.
+// The lengths are on the device, so the rule goes by the capacity; the
+// workspace has room for it at any capacity (sizes never decrease in it).
+static bool dec_ahead_room(size_t heads, int cap, int d, int G) {
+  return heads * dec_nchunk(heads, cap, d) > (G >= 4 || d == 32 ? 1024 : 2000);
+}
+static bool dec_route_ahead(size_t heads, int cap, int d, int G) {
+  if (!dec_ahead_room(heads, cap, d, G)) return false;
+  if (G >= 4) return cap <= 1792;
+  return d == 32 ? cap <= 2048 : static_cast<long>(cap) * d <= 25600;
+}
+
 struct DecWs {
+  int32_t* ahead;
+  float* qrot;
   float* part_acc;
   float* part_ml;
   size_t bytes;
@@ -813,7 +918,11 @@ static DecWs carve_dec(void* ws, int B, int K, int d, int cap, int G = 1) {
   const size_t BK = static_cast<size_t>(B) * K;
   const size_t np = dec_partials(BK, cap, d);
   Carver cv(ws);
-  DecWs w;
+  DecWs w{};
+  if (dec_ahead_room(BK, cap, d, G)) {
+    w.ahead = cv.take<int32_t>(BK);
+    w.qrot = cv.take<float>(BK * G * d);
+  }
   w.part_acc = cv.take<float>(np * G * d);
   w.part_ml = cv.take<float>(np * G * 2);
   w.bytes = cv.off;
@@ -1023,12 +1132,20 @@ static hipError_t run_decode(const float* logits, const float* bias, const void*
   const double log_base = rope_mode == 2 ? 0.0 : std::log(static_cast<double>(rope_base));
   const DecStep a{logits, bias, q, k, v, k_cache, v_cache, cache_len, seq_pos, H, K, cap, log_base,
                   rope_mode, gate_mode, 0, scale * 1.4426950408889634f, topk_idx, gates, dev_status,
-                  nc, static_cast<long>(B) * K * nc <= kDecFineGroups, w.part_acc, w.part_ml};
+                  nc, static_cast<long>(B) * K * nc <= kDecFineGroups, w.part_acc, w.part_ml, w.ahead,
+                  w.qrot};
   const dim3 grid(static_cast<unsigned>(static_cast<size_t>(B) * K * nc));
-  if constexpr (BF16 && (GQ == 4 || GQ == 8))
-    launch_k("decode_attn", k_decode_attn_mfma<D, GQ>, grid, dim3(256), st, a);
-  else
-    launch_k("decode_attn", k_decode_attn<D, BF16, GQ>, grid, dim3(256), st, a);
+  const bool route_ahead = dec_route_ahead(static_cast<size_t>(B) * K, cap, D, GQ);
+  if (route_ahead)
+    launch_k("decode_route", k_decode_route<D, BF16>, dim3(static_cast<unsigned>(B * K)), dim3(64), st, a, GQ);
+  auto attn = [&](auto ahead) {
+    if constexpr (BF16 && (GQ == 4 || GQ == 8))
+      launch_k("decode_attn", k_decode_attn_mfma<D, GQ, decltype(ahead)::value>, grid, dim3(256), st, a);
+    else
+      launch_k("decode_attn", k_decode_attn<D, BF16, GQ, false, decltype(ahead)::value>, grid, dim3(256), st, a);
+  };
+  if (route_ahead) attn(std::true_type{});
+  else attn(std::false_type{});
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   launch_dec_combine<D, false>(a, cache_len, B, GQ, out, out_dtype, 0, st);
@@ -1114,7 +1231,7 @@ static hipError_t run_shared_decode(const void* q, const void* k, const void* v,
   const DecStep a{nullptr, nullptr, q, k, v, k_cache, v_cache, cache_len, nullptr, Hs, Hs, cap,
                   log_base, rope_mode, 0, window, scale * 1.4426950408889634f, nullptr, nullptr,
                   dev_status, nc, static_cast<long>(B) * Hs * nc <= kDecFineGroups, w.part_acc,
-                  w.part_ml};
+                  w.part_ml, nullptr, nullptr};
   const dim3 grid(static_cast<unsigned>(static_cast<size_t>(B) * Hs * nc));
   launch_k("decode_attn", k_decode_attn<D, BF16, 1, true>, grid, dim3(256), st, a);
   const hipError_t e = hipGetLastError();

@@ -155,3 +155,57 @@ def test_infinite_value_of_the_new_token(n, g, dtype, d=64, cap=900):
                          accumulate=True)
     s = s[0].cpu()
     assert s[5] == float("inf") and torch.isfinite(s[keep]).all()
+
+
+# Many sequences with short caches are routed in a launch before the attention;
+# the same sequences in small batches are routed in its workgroups.  The appends
+# and the routing are the same arithmetic; the outputs differ by the order of
+# float32 sums (one or two heads a row) or by the maximum that bf16 probabilities
+# are rounded against (four and eight).
+@pytest.mark.parametrize("d,g,dtype,cap,rope,biased", [
+    (64, 1, torch.bfloat16, 300, 0, False), (128, 1, torch.bfloat16, 200, 1, False),
+    (64, 2, torch.bfloat16, 400, 0, False), (128, 2, torch.bfloat16, 150, 2, False),
+    (64, 4, torch.bfloat16, 1100, 0, False), (128, 8, torch.bfloat16, 300, 1, False),
+    (64, 8, torch.bfloat16, 40, 2, False), (128, 4, torch.bfloat16, 1792, 0, False),
+    (32, 1, torch.bfloat16, 600, 0, True), (32, 1, torch.float32, 300, 1, False),
+    (64, 1, torch.float32, 257, 2, True), (128, 1, torch.float32, 200, 0, False)])
+def test_routed_ahead(d, g, dtype, cap, rope, biased, B=336, K=6, H=9):
+    say(f"decode routed ahead: d{d} g{g} {dtype} cap{cap} rope{rope} biased{biased}")
+    gen = torch.Generator(device=DEV).manual_seed(d + g + cap)
+    kw = dict(generator=gen, device=DEV, dtype=dtype)
+    lens = [n for n in LENS + [cap - 1, cap - 2, cap] if n <= cap]
+    n0 = torch.tensor([[lens[(b * H + h) % len(lens)] for h in range(H)] for b in range(B)],
+                      dtype=torch.int32, device=DEV)
+    kc, vc = (torch.randn(B, H, cap, d, **kw) for _ in range(2))
+    past = torch.arange(cap, device=DEV)[None, None] >= n0[..., None]
+    kc[past], vc[past] = float("nan"), float("nan")
+    logits = torch.randn(B, H, generator=gen, device=DEV)
+    logits[::7] = torch.round(logits[::7])   # ties
+    logits[::7][logits[::7] == 0] *= -1      # zeros of both signs
+    q, k, v = torch.randn(B, H * g, d, **kw), torch.randn(B, H, d, **kw), torch.randn(B, H, d, **kw)
+    pos = torch.randint(0, 5000, (B,), generator=gen, device=DEV, dtype=torch.int32)
+    extra = {"bias": torch.randn(H, generator=gen, device=DEV) * 0.1} if biased else {}
+
+    def run(lo, hi):
+        c = [x[lo:hi].clone() for x in (kc, vc, n0)]
+        st = torch.zeros(1, dtype=torch.int32, device=DEV)
+        step = L.decode_step_grouped if g > 1 else L.decode_step
+        r = step(logits[lo:hi], q[lo:hi], k[lo:hi], v[lo:hi], *c, K, BASE, rope,
+                 seq_pos=pos[lo:hi] if rope == 1 else None, out_dtype=torch.float32, dev_status=st,
+                 **extra)
+        return [r["topk_idx"], r["gates"], *c, r["out"]], int(st.item())
+
+    whole, status = run(0, B)
+    parts = [run(lo, lo + 42) for lo in range(0, B, 42)]
+    assert status == max(p[1] for p in parts) == 1    # (some selected head's cache is full)
+    same = [torch.cat([p[0][i] for p in parts]) for i in range(6)]
+    for a, b in zip(whole[:2] + whole[4:5], same[:2] + same[4:5]):
+        assert torch.equal(a, b)
+    for a, b in zip(whole[2:4], same[2:4]):            # caches, their unused rows NaN
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    assert torch.isfinite(whole[5]).all()
+    if g >= 4:
+        check_out(whole[5].cpu().numpy(), same[5].cpu().double().numpy(), "bf16", what="outputs")
+    else:
+        err = (whole[5] - same[5]).abs().max()
+        assert float(err) <= 1e-5 * float(same[5].abs().max())
