@@ -120,12 +120,18 @@ NAMOH_DEV bool dec_head(const DecStep& a, int bk, int chunk, DecHead& o) {
       if (chunk == 0 && thread_x() == 0 && a.dev_status) a.dev_status[0] = 1;
       return false;
     }
-    const int m = a.window > 0 ? min(n + 1, a.window) : n + 1;
+    const int hist = a.window > 0 ? min(n, a.window - 1) : n;
+    o.chunk = dec_chunk_rows<D>(hist + 1, a.nchunk, a.fine);
+    // most workgroups of a cache far larger than its histories end here, before
+    // the divisions
+    if (chunk * o.chunk > hist) return false;
     o.bh = bk;
-    o.hist = m - 1;
-    o.ring0 = static_cast<int>((static_cast<long>(n) + 1 - m) % a.cap);
-    o.slot = n % a.cap;
+    o.hist = hist;
+    const uint32_t cap = static_cast<uint32_t>(a.cap);
+    o.ring0 = static_cast<int>(static_cast<uint32_t>(n - hist) % cap);
+    o.slot = static_cast<uint32_t>(n) % cap;
     o.pos = n;
+    return true;
   } else {
     const bool real = lane < a.H;
     const size_t bl = static_cast<size_t>(b) * a.H + min(lane, a.H - 1);
