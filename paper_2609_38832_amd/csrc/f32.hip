@@ -14,8 +14,8 @@
 //               it is, and a lane reads one value of column c per step.
 // The four waves of a workgroup share one 32-row block and take every fourth
 // tile each (QW = 1), or share a 64-row block in two pairs that take every
-// second tile (QW = 2: see f32_qw); the waves' partial results are merged in
-// order through LDS.
+// second tile (QW = 2: see f32_qw), or hold a 32-row block each (QW = 4: see
+// f32_short); the waves' partial results are merged in order through LDS.
 //
 // Masked (query, key) pairs get weight zero; where a tile that has such pairs
 // also holds a non-finite value (zero times it would be NaN), its weighted
@@ -53,8 +53,9 @@ template <int D, int QW> struct FShape {
   static constexpr int BM = 32 * QW;           // block rows of a workgroup
   // keys and values (queries and output gradients) of a staging; later the
   // parts' rows of one gradient or two (KS BM = 128 rows each)
-  static constexpr int BUF = 2 * 128 * LD;
-  static constexpr int MINB = D == 128 ? 1 : 2;
+  // (QW = 4, forward only: one part)
+  static constexpr int BUF = (QW == 4 ? 1 : 2) * 128 * LD;
+  static constexpr int MINB = D == 128 ? 1 : QW == 4 ? 3 : 2;
 };
 
 struct FBlock { int s, a, n, r0; };   // segment, first packed row, length, first row of the block
@@ -675,14 +676,23 @@ __global__ __launch_bounds__(kFThreads, (FShape<D, QW>::MINB)) void k_f32_bwd_kv
 // H 8, K 4, skewed: 93 -> 137, 323 -> 478 us); 128-row blocks lose more.
 constexpr int f32_qw(int D) { return D == 128 ? 2 : 1; }
 
+// Many short segments (d = 64, forward): a workgroup per 128 rows whose waves
+// take a query block each of one tile after the other, instead of one query
+// block with the tiles split over the waves: with a few rows a segment three
+// of four staged tiles were empty.  Forward in us, split tiles -> query blocks,
+// 64 heads, 4 selected (zipf: skewed routing): 40 sequences of 79 tokens 64 -> 45,
+// 200 of 60 (2 selected) 240 -> 157, 16 of 200 46 -> 31, zipf, 32 heads 40 -> 38; 16
+// of 300 48 -> 34, but zipf 55 -> 72, 16 of 600, zipf 99 -> 118: long segments want
+// the split.  16 heads x 16 sequences, 1 selected, 100 tokens, zipf 21 -> 22.5.
+static bool f32_short(int d, int BH, int T) { return d == 64 && BH >= 512 && T <= 256; }
+
 template <int BM>
 static dim3 f32_grid(int Nr, int BH) { return dim3(static_cast<unsigned>(Nr / BM + BH + 1)); }
 
-template <int D, bool BF16>
+template <int D, bool BF16, int QW = f32_qw(D)>
 static void run_f32_attn(const void* q, const void* k, const void* v, const float2* table,
                          const int32_t* seg_offsets, const int32_t* perm_token, int BH, int T,
                          int Nr, int rope_mode, float scale_log2, float* hout, hipStream_t st) {
-  constexpr int QW = f32_qw(D);
   launch_k("attn", k_f32_attn<D, BF16, QW>, f32_grid<32 * QW>(Nr, BH), dim3(kFThreads), st, q, k, v,
            table, seg_offsets, perm_token, BH, T, Nr, rope_mode, scale_log2, hout);
 }
@@ -699,6 +709,8 @@ hipError_t launch_f32_attn(const void* q, const void* k, const void* v, int dtyp
     NAMOH_F32(32, true);
   } else if (d == 32) {
     NAMOH_F32(32, false);
+  } else if (f32_short(d, BH, T)) {
+    run_f32_attn<64, false, 4>(q, k, v, table, seg_offsets, perm_token, BH, T, Nr, rope_mode, sl2, hout, st);
   } else if (d == 64) {
     NAMOH_F32(64, false);
   } else {

@@ -141,3 +141,42 @@ def test_non_finite_rows_stay_where_they_are_seen(bad, d):
     assert _rel(res["dk"][0, :, t + 1:], gk[:, t + 1:]) <= REL
     assert _rel(res["dv"][0, :, t + 1:], gv[:, t + 1:]) <= REL
     assert _rel(res["dq"][0, :, t + 1:], gq[:, t + 1:]) <= REL
+
+
+# 512 segments and more of at most 256 rows, d 64: a wave per query block; the same
+# sequences in small batches (and any of 257 rows) run the general form
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 64, 65, 127, 128, 129, 160, 255, 256, 257])
+def test_many_short_segments(n, d=64, B=512):
+    say(f"float32 forward, {B} segments of {n} rows")
+    q, k, v, _, r = _one_head(B, n, d, torch.float32)
+    if n > 40:   # a value and a key that later rows see: not a matter of masking alone
+        v[3, 0, 40, 1], v[4, 0, n - 1], k[5, 0, n - 1] = float("inf"), float("nan"), float("nan")
+    out = L.attn_fwd(q, k, v, r, 1, BASE)
+    for b in (0, 255, 511):
+        ref, _ = _reference(q[b:b + 1, 0], k[b:b + 1, 0], v[b:b + 1, 0],
+                            torch.zeros(1, n, d, device=DEV))
+        assert _rel(out[b:b + 1], ref) <= REL
+    few = 8
+    _, _, _, _, rf = _one_head(few, n, d, torch.float32)
+    part = L.attn_fwd(q[:few].contiguous(), k[:few].contiguous(), v[:few].contiguous(), rf, 1, BASE)
+    got = out[:few]
+    assert torch.equal(torch.isnan(got), torch.isnan(part))
+    assert torch.equal(torch.isinf(got), torch.isinf(part))
+    ok = torch.isfinite(part)
+    assert ok.float().mean() > 0.5
+    assert float((got[ok] - part[ok]).norm() / part[ok].norm()) <= REL
+
+
+def test_many_ragged_segments(B=40, T=200, H=16, K=4, d=64):
+    say("float32 forward, ragged short segments")
+    g = torch.Generator(device=DEV).manual_seed(2)
+    logits = torch.randn(B, T, H, generator=g, device=DEV)
+    logits -= 0.4 * torch.arange(H, device=DEV)          # some heads get few tokens or none
+    q, k, v = (torch.randn(B, H, T, d, generator=g, device=DEV) for _ in range(3))
+    for rope in (0, 1, 2):
+        out = L.attn_fwd(q, k, v, L.route(logits, K), K, BASE, rope)
+        part = torch.cat([L.attn_fwd(q[b:b + 8].contiguous(), k[b:b + 8].contiguous(),
+                                     v[b:b + 8].contiguous(),
+                                     L.route(logits[b:b + 8].contiguous(), K), K, BASE, rope)
+                          for b in range(0, B, 8)])
+        assert float((out - part).norm() / part.norm()) <= REL
