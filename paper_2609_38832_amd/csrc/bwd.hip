@@ -23,6 +23,7 @@
 //                  rows; dgates at the (t, k) slots.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 #include "internal.h"
@@ -1582,47 +1583,50 @@ hipError_t launch_train_fwd(const void* q, const void* k, const void* v, int dty
 // Router gradient through the gates (selection fixed).
 // SOFTMAX_SELECTED: dl_j = g_j (dg_j - sum_k g_k dg_k) on the selected heads;
 // SOFTMAX_ALL (and the loss-free balancing gates): dl = a (da - <a, da>).
-// What bounds it is latency: a few floats per token, behind one another.  Eight
-// lanes per token, each owning the heads congruent to its index, and 32 tokens
-// per workgroup (512 workgroups at 16384 tokens; one thread per token in 128
-// workgroups walked the K entries and the H exponentials of a token from
-// memory, one after the other).  The entries are staged in LDS by consecutive
-// loads and read there by all eight lanes; a lane adds the entries of its own
-// heads in entry order.  T 12289, H 32, K 4, SOFTMAX_ALL: 12.9 -> 4.4 us; B 4,
-// T 4096, H 32, K 8, SOFTMAX_SELECTED: 4.8 -> 3.5 us; T 32768, H 64, K 64: 24.6 ->
-// 17.2 and 58.9 -> 18.8 us (in captured runs).
-constexpr int kRouteBwdLanes = 8;
+// What bounds it is latency: a few floats per token, behind one another, and
+// with hundreds of thousands of tokens the instructions.  A token has 1, 4 or 8
+// lanes, each owning the heads congruent to its index (at most 8), and the
+// entries are staged in LDS by consecutive loads and read there by all lanes of
+// the token; a lane adds the entries of its own heads in entry order; the rows
+// go out in one run.  One thread per token that walked the K entries and the H
+// exponentials from memory, in 128-token workgroups -> now: T 12289, H 32, K 4,
+// SOFTMAX_ALL 12.9 -> 4.4 us; B 4, T 4096, H 32, K 8, SOFTMAX_SELECTED 4.8 -> 3.6; T
+// 32768, H 64, K 64 24.6 -> 17.2 and 58.9 -> 18.8.  Lanes, 8 -> 1 at 300000 tokens of 8
+// heads, 8 selected 22 -> 7.8 (20 before); 8 -> 4 at 50000 tokens, H 32, K 8
+// 6.5 -> 5.5, H 16, K 2 4.4 -> 3.4, but at 300 tokens, H 32, K 8 3.3 -> 3.5.  With one
+// or two of many heads selected and 100000 tokens and more a thread per token
+// was up to a sixth faster (H 64, K 2, 300000: 17.3, now 20.6).
 constexpr int kRouteBwdThreads = 256;
-constexpr int kRouteBwdTokens = kRouteBwdThreads / kRouteBwdLanes;
-constexpr int kRouteBwdHeads = 64;
-template <bool SOFTMAX_ALL>
+constexpr int kRouteBwdLaneHeads = 8;
+constexpr long kRouteBwdMany = 32768;   // tokens from which fewer lanes each pay
+template <bool SOFTMAX_ALL, int LANES>
 __global__ __launch_bounds__(kRouteBwdThreads) void k_route_bwd(
     const float* __restrict__ logits, const int32_t* __restrict__ topk_idx,
     const float* __restrict__ gates, const float* __restrict__ dgates, long BT, int H, int K,
     float* __restrict__ dlogits) {
-  constexpr int HL = kRouteBwdHeads / kRouteBwdLanes;
-  constexpr int LDS = kRouteBwdTokens * (kRouteBwdHeads + 1);   // rows of odd lengths: no conflicts
+  constexpr int HL = kRouteBwdLaneHeads, TOK = kRouteBwdThreads / LANES;
+  constexpr int LDS = TOK * (HL * LANES + 1);   // rows of odd lengths: no conflicts
   __shared__ int32_t s_tk[LDS];
   __shared__ float s_dg[LDS];
   __shared__ float s_a[LDS];   // gates [K], or affinities [H]
   __shared__ float s_dl[LDS];
   const int KS = K | 1, HS = H | 1;
   const int tid = thread_x();
-  const int sub = tid % kRouteBwdLanes, tok = tid / kRouteBwdLanes;
-  const long tok0 = static_cast<long>(block_x()) * kRouteBwdTokens;
-  const int ntok = static_cast<int>(min(static_cast<long>(kRouteBwdTokens), BT - tok0));
+  const int sub = tid % LANES, tok = tid / LANES;
+  const long tok0 = static_cast<long>(block_x()) * TOK;
+  const int ntok = static_cast<int>(min(static_cast<long>(TOK), BT - tok0));
   const bool live = tok < ntok;
   float p[HL];   // SOFTMAX_ALL: logits, then affinities of heads sub + 8 e
   if constexpr (SOFTMAX_ALL) {
     const float* l = logits + (tok0 + (live ? tok : 0)) * H;
 #pragma unroll
     for (int e = 0; e < HL; ++e) {
-      const int h = sub + kRouteBwdLanes * e;
+      const int h = sub + LANES * e;
       p[e] = h < H ? l[h] : -INFINITY;
     }
   }
   if (live)
-    for (int kk = sub; kk < K; kk += kRouteBwdLanes) {
+    for (int kk = sub; kk < K; kk += LANES) {
       const long i = (tok0 + tok) * K + kk;
       s_tk[tok * KS + kk] = topk_idx[i];
       s_dg[tok * KS + kk] = dgates[i];
@@ -1633,53 +1637,56 @@ __global__ __launch_bounds__(kRouteBwdThreads) void k_route_bwd(
 #pragma unroll
     for (int e = 1; e < HL; ++e) mx = fmaxf(mx, p[e]);
 #pragma unroll
-    for (int o = 1; o < kRouteBwdLanes; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, kRouteBwdLanes));
+    for (int o = 1; o < LANES; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, LANES));
     float z = 0.f;
 #pragma unroll
     for (int e = 0; e < HL; ++e) {
-      p[e] = sub + kRouteBwdLanes * e < H ? expf(p[e] - mx) : 0.f;
+      p[e] = sub + LANES * e < H ? expf(p[e] - mx) : 0.f;
       z += p[e];
     }
 #pragma unroll
-    for (int o = 1; o < kRouteBwdLanes; o <<= 1) z += __shfl_xor(z, o, kRouteBwdLanes);
+    for (int o = 1; o < LANES; o <<= 1) z += __shfl_xor(z, o, LANES);
     const float iz = 1.f / z;
 #pragma unroll
     for (int e = 0; e < HL; ++e) {
-      const int h = sub + kRouteBwdLanes * e;
+      const int h = sub + LANES * e;
       p[e] *= iz;
       if (h < H) s_a[tok * HS + h] = p[e];
     }
   }
   __syncthreads();
-  if (!live) return;
   const int32_t* tk = s_tk + tok * KS;
   const float* dg = s_dg + tok * KS;
   const float* a = s_a + tok * (SOFTMAX_ALL ? HS : KS);
-  float* dl = s_dl + tok * HS;   // each lane its own heads
-  bool valid = true;   // entries out of range: not a selection, no gradient
+  float* dl = s_dl + tok * H;    // each lane its own heads
+  bool valid = live;   // entries out of range: not a selection, no gradient
   float sum = 0.f;     // <a, da>
+  if (live) {
 #pragma unroll 8
-  for (int kk = 0; kk < K; ++kk) {
-    const int h = tk[kk];
-    const bool in = h >= 0 && h < H;
-    valid &= in;
-    sum = fmaf(a[SOFTMAX_ALL ? (in ? h : 0) : kk], dg[kk], sum);
+    for (int kk = 0; kk < K; ++kk) {
+      const int h = tk[kk];
+      const bool in = h >= 0 && h < H;
+      valid &= in;
+      sum = fmaf(a[SOFTMAX_ALL ? (in ? h : 0) : kk], dg[kk], sum);
+    }
   }
 #pragma unroll
   for (int e = 0; e < HL; ++e) {
-    const int h = sub + kRouteBwdLanes * e;
+    const int h = sub + LANES * e;
     if (h < H) dl[h] = SOFTMAX_ALL && valid ? -p[e] * sum : 0.f;
   }
   if (valid) {
 #pragma unroll 8
     for (int kk = 0; kk < K; ++kk) {
       const int h = tk[kk];
-      if (h % kRouteBwdLanes == sub)
+      if (h % LANES == sub)
         dl[h] = SOFTMAX_ALL ? fmaf(a[h], dg[kk], dl[h]) : a[kk] * (dg[kk] - sum);
     }
   }
-  float* out = dlogits + (tok0 + tok) * H;
-  for (int h = sub; h < H; h += kRouteBwdLanes) out[h] = dl[h];
+  // the rows in one run, consecutive threads on consecutive floats
+  __syncthreads();
+  float* out = dlogits + tok0 * H;
+  for (int i = tid; i < ntok * H; i += kRouteBwdThreads) out[i] = s_dl[i];
 }
 
 hipError_t launch_route_bwd(const float* logits, const int32_t* topk_idx, const float* gates,
@@ -1687,9 +1694,15 @@ hipError_t launch_route_bwd(const float* logits, const int32_t* topk_idx, const 
                             float* dlogits, hipStream_t st) {
   const long BT = static_cast<long>(B) * T;
   if (H > 64) return hipErrorInvalidValue;   // the API allows H <= 64
-  const auto kern = gate_mode == 0 ? k_route_bwd<false> : k_route_bwd<true>;
-  kern<<<static_cast<unsigned>((BT + kRouteBwdTokens - 1) / kRouteBwdTokens), kRouteBwdThreads, 0,
-         st>>>(logits, topk_idx, gates, dgates, BT, H, K, dlogits);
+  auto run = [&](auto lanes) {
+    constexpr int LANES = decltype(lanes)::value, TOK = kRouteBwdThreads / LANES;
+    const auto kern = gate_mode == 0 ? k_route_bwd<false, LANES> : k_route_bwd<true, LANES>;
+    kern<<<static_cast<unsigned>((BT + TOK - 1) / TOK), kRouteBwdThreads, 0, st>>>(
+        logits, topk_idx, gates, dgates, BT, H, K, dlogits);
+  };
+  if (H <= 8) run(std::integral_constant<int, 1>{});
+  else if (H <= 32 && BT > kRouteBwdMany) run(std::integral_constant<int, 4>{});
+  else run(std::integral_constant<int, 8>{});
   return hipGetLastError();
 }
 

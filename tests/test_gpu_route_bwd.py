@@ -1,5 +1,6 @@
-"""Router gradient at the edges of its token groups (32 tokens, eight lanes each) and of the
-head and selection counts, against the formula in float64.
+"""Router gradient at the edges of its token groups (32 tokens with eight lanes each, 64 with
+four from 32769 tokens and up to 32 heads, 256 with one up to 8 heads) and of the head and
+selection counts, against the formula in float64.
 
 Bounds: each float32 operation adds at most 2^-24 relative; an affinity carries the
 rounding of its exponent argument (the logit range R), two units of expf, the sum of at
@@ -18,7 +19,10 @@ if torch.cuda.is_available():
 
 
 @pytest.mark.parametrize("BT,H,K", [((1, 1), 1, 1), ((1, 31), 7, 3), ((1, 33), 33, 5),
-                                    ((3, 43), 64, 64), ((2, 1000), 32, 8)])
+                                    ((3, 43), 64, 64), ((2, 1000), 32, 8),
+                                    ((1, 255), 8, 8), ((1, 257), 5, 2), ((2, 128), 8, 1),
+                                    ((1, 513), 9, 9), ((1, 32768), 32, 4), ((1, 32769), 9, 2),
+                                    ((3, 10950), 32, 4), ((1, 33000), 33, 3), ((1, 33000), 8, 3)])
 @pytest.mark.parametrize("gate_mode", [O.GATE_SOFTMAX_SELECTED, O.GATE_SOFTMAX_ALL])
 def test_route_bwd_edges(BT, H, K, gate_mode):
     say(f"route backward {BT} H {H} K {K} gate_mode {gate_mode}")
