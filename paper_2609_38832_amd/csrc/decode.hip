@@ -86,9 +86,15 @@ struct DecStep {
   int32_t* dev_status;
   int nchunk, fine;        // chunks per head; dec_chunk_rows
   float *part_acc, *part_ml;
-  int32_t* ahead;          // k_decode_route's: history (or -1) of every selected
-  float* qrot;             // head, its rotated, scaled queries [G, D]
 };
+// And what k_decode_route leaves for them (a kernel without it has the smaller
+// arguments: the 16 bytes cost 0.4 us of host time a call).
+struct DecAhead : DecStep {
+  int32_t* ahead;          // history (or -1) of every selected head
+  float* qrot;             // its rotated, scaled queries [G, D]
+};
+template <bool AHEAD>
+using DecArgs = std::conditional_t<AHEAD, DecAhead, DecStep>;
 
 // The head a workgroup (selected head bk, chunk) works on: its history before
 // the new token (rows of it that are read), the first one's ring row, and the
@@ -266,7 +272,7 @@ NAMOH_DEV void dec_unpack(const u32x4 x, float* f) {
 // (one wave per selected head, G query heads each), for launches of many short
 // chunks: see dec_route_ahead.
 template <int D, bool BF16>
-__global__ __launch_bounds__(64) void k_decode_route(const DecStep a, int G) {
+__global__ __launch_bounds__(64) void k_decode_route(const DecAhead a, int G) {
   __shared__ float2 s_cs[D / 2];
   __shared__ u32x4 s_new[2 * D * (BF16 ? 2 : 4) / 16];
   const int bk = block_x(), j = thread_x();
@@ -287,7 +293,7 @@ __global__ __launch_bounds__(64) void k_decode_route(const DecStep a, int G) {
 
 // dec_head after k_decode_route: the new token's row is one of the history's.
 template <int D>
-NAMOH_DEV bool dec_head_ahead(const DecStep& a, int bk, int chunk, DecHead& o) {
+NAMOH_DEV bool dec_head_ahead(const DecAhead& a, int bk, int chunk, DecHead& o) {
   const int n = __builtin_amdgcn_readfirstlane(a.ahead[bk]);
   const int h = __builtin_amdgcn_readfirstlane(a.topk_idx[bk]);
   if (n < 0) return false;
@@ -309,7 +315,7 @@ NAMOH_DEV bool dec_head_ahead(const DecStep& a, int bk, int chunk, DecHead& o) {
 // the history are loaded before the new token's angles are formed.
 // AHEAD: k_decode_route ran before.
 template <int D, bool BF16, int GQ = 1, bool SHARED = false, bool AHEAD = false>
-__global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
+__global__ __launch_bounds__(256) void k_decode_attn(const DecArgs<AHEAD> a) {
   constexpr int EPG = BF16 ? 8 : 4;   // elements per 16-byte granule
   constexpr int G = D / EPG;          // lanes per row
   constexpr int RPW = 64 / G;         // rows per wave per step
@@ -516,7 +522,7 @@ __global__ __launch_bounds__(256) void k_decode_attn(const DecStep a) {
 // + 3, so a lane's rescale factors apply to its own output accumulators.
 // Partials as in k_decode_attn: (bk * GQ + q) * nchunk + chunk.
 template <int D, int GQ, bool AHEAD>
-__global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(const DecStep a) {
+__global__ __launch_bounds__(256, 2) void k_decode_attn_mfma(const DecArgs<AHEAD> a) {
   static_assert(GQ == 4 || GQ == 8, "queries per cached row");
   static_assert(D == 64 || D == 128, "head width");
   constexpr int KS = D / 32;           // reduction steps of the score product
@@ -1138,20 +1144,22 @@ static hipError_t run_decode(const float* logits, const float* bias, const void*
   const double log_base = rope_mode == 2 ? 0.0 : std::log(static_cast<double>(rope_base));
   const DecStep a{logits, bias, q, k, v, k_cache, v_cache, cache_len, seq_pos, H, K, cap, log_base,
                   rope_mode, gate_mode, 0, scale * 1.4426950408889634f, topk_idx, gates, dev_status,
-                  nc, static_cast<long>(B) * K * nc <= kDecFineGroups, w.part_acc, w.part_ml, w.ahead,
-                  w.qrot};
+                  nc, static_cast<long>(B) * K * nc <= kDecFineGroups, w.part_acc, w.part_ml};
   const dim3 grid(static_cast<unsigned>(static_cast<size_t>(B) * K * nc));
-  const bool route_ahead = dec_route_ahead(static_cast<size_t>(B) * K, cap, D, GQ);
-  if (route_ahead)
-    launch_k("decode_route", k_decode_route<D, BF16>, dim3(static_cast<unsigned>(B * K)), dim3(64), st, a, GQ);
-  auto attn = [&](auto ahead) {
+  auto attn = [&](auto ahead, const auto& args) {
+    constexpr bool AHEAD = decltype(ahead)::value;
     if constexpr (BF16 && (GQ == 4 || GQ == 8))
-      launch_k("decode_attn", k_decode_attn_mfma<D, GQ, decltype(ahead)::value>, grid, dim3(256), st, a);
+      launch_k("decode_attn", k_decode_attn_mfma<D, GQ, AHEAD>, grid, dim3(256), st, args);
     else
-      launch_k("decode_attn", k_decode_attn<D, BF16, GQ, false, decltype(ahead)::value>, grid, dim3(256), st, a);
+      launch_k("decode_attn", k_decode_attn<D, BF16, GQ, false, AHEAD>, grid, dim3(256), st, args);
   };
-  if (route_ahead) attn(std::true_type{});
-  else attn(std::false_type{});
+  if (dec_route_ahead(static_cast<size_t>(B) * K, cap, D, GQ)) {
+    const DecAhead aa{a, w.ahead, w.qrot};
+    launch_k("decode_route", k_decode_route<D, BF16>, dim3(static_cast<unsigned>(B * K)), dim3(64), st, aa, GQ);
+    attn(std::true_type{}, aa);
+  } else {
+    attn(std::false_type{}, a);
+  }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   launch_dec_combine<D, false>(a, cache_len, B, GQ, out, out_dtype, 0, st);
@@ -1237,7 +1245,7 @@ static hipError_t run_shared_decode(const void* q, const void* k, const void* v,
   const DecStep a{nullptr, nullptr, q, k, v, k_cache, v_cache, cache_len, nullptr, Hs, Hs, cap,
                   log_base, rope_mode, 0, window, scale * 1.4426950408889634f, nullptr, nullptr,
                   dev_status, nc, static_cast<long>(B) * Hs * nc <= kDecFineGroups, w.part_acc,
-                  w.part_ml, nullptr, nullptr};
+                  w.part_ml};
   const dim3 grid(static_cast<unsigned>(static_cast<size_t>(B) * Hs * nc));
   launch_k("decode_attn", k_decode_attn<D, BF16, 1, true>, grid, dim3(256), st, a);
   const hipError_t e = hipGetLastError();
