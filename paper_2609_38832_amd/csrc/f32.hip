@@ -230,14 +230,16 @@ struct F32Stage {
 // Causal attention of the wave's query (row r of the segment, half row qf in
 // log2 units) over the key tiles up to its own one: unnormalised output acc,
 // running maximum m, and l, the sum over the lane's own keys (the two lanes of
-// a query hold the two halves).
+// a query hold the two halves).  m starts at the lowest finite value: a tile
+// whose scores are all -inf (a part's first one, say) weighs nothing and is not
+// -inf - -inf = NaN.
 template <int D, int QW, typename Stage>
 NAMOH_DEV void f32_attend(f32x16 (&acc)[D / 32], float& m, float& l, const float (&qf)[D / 2], int r,
                           int qt, int part, bool active, int ntile, float* sk, float* sv, int c,
                           int g, Stage& stage) {
   using S = FShape<D, QW>;
   f32_clear<D>(acc);
-  m = -INFINITY;
+  m = -FLT_MAX;
   l = 0.f;
   for (int t0 = 0; t0 < ntile; t0 += S::KS) {
     stage.load(32 * t0);

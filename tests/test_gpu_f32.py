@@ -142,6 +142,27 @@ def test_non_finite_rows_stay_where_they_are_seen(bad, d):
     assert _rel(res["dv"][0, :, t + 1:], gv[:, t + 1:]) <= REL
     assert _rel(res["dq"][0, :, t + 1:], gq[:, t + 1:]) <= REL
 
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("n,lo", [(70, 32), (200, 64)])
+def test_a_tile_of_minus_infinite_scores_weighs_nothing(n, lo, d):
+    # 32 keys that score -inf against every query (their products overflow) in
+    # the first tile that a wave takes
+    say(f"float32 path, keys {lo} to {lo + 31} of {n} at -inf, d {d}")
+    q, k, v, dout, r = _one_head(1, n, d, torch.float32, 4)
+    q = q.abs() + 0.5
+    k[:, :, lo:lo + 32] = -3e38
+    out = L.attn_fwd(q, k, v, r, 1, BASE, L.ROPE_NONE)
+    res = L.attn_bwd(q, k, v, r, 1, BASE, dout, L.ROPE_NONE)
+    x = [y[0, 0].cpu().double().requires_grad_(True) for y in (q, k, v)]
+    s = x[0] @ x[1].T / math.sqrt(d)
+    hidden = torch.ones(n, n).triu(1).bool()
+    hidden[:, lo:lo + 32] = True
+    ref = torch.softmax(s.masked_fill(hidden, float("-inf")), -1) @ x[2]
+    assert _rel(out[0], ref.detach()) <= REL
+    grads = torch.autograd.grad((ref * dout[0].cpu().double()).sum(), x)
+    for name, g in zip(("dq", "dk", "dv"), grads):
+        assert _rel(res[name][0, 0], g) <= REL, name
+
 
 # 512 segments and more of at most 256 rows, d 64: a wave per query block; the same
 # sequences in small batches (and any of 257 rows) run the general form
