@@ -1432,30 +1432,35 @@ static hipError_t run_bwd_mfma(const void* q, const void* k, const void* v, int 
   if (tl.BM != kBwdMfmaBlock || static_cast<size_t>(tl.max_tiles) * kBN > w.rows)
     return hipErrorInvalidValue;   // the forward's blocks and tiles must match these kernels
   const double* freq = tl.freq;
-  // Dense gradients: rows of tokens not routed to the head are zero.  Fills of
-  // up to 512 MB are written by the query side's first workgroups, one on every
-  // other CU, beside the matrix work (as a launch of its own the fill runs at
-  // the memory's rate with the matrix cores idle); larger ones, about twice the
-  // last-level cache, by a launch before the packing: beside the products they
-  // take those the cached tiles, and the workgroups that write them outlast the
-  // rest where few heads are selected.  The backward with a launch / beside, us
-  // (zipf: skewed routing):
-  //   T 200, H 32, K 8, d 64 (4 MB) 21.5 / 17.4; B 4, T 4096 (302 MB) 192 / 184;
-  //   T 4096, H 64, K 1, d 128 (396 MB) 108 / 97; T 12289, H 32, K 4, d 128, zipf
-  //   (529 MB) 495 / 448; T 6000, H 64, K 1, d 128 (581 MB) 137 / 141; B 4, T 4096,
-  //   H 32, K 4, d 128 (705 MB) 262 / 287; T 8192, H 64, K 2, d 128 (780 MB) 189 /
-  //   227; T 16000, H 64, K 8, d 128 (1.4 GB) 608 / 643; B 4, T 4096, H 64, K 1, d 128
-  //   (1.6 GB) 307 / 433; but T 12289, H 64, K 4, d 128, zipf (1.1 GB) 592 / 550.
-  // Workgroups beside: 256 or 64 of them up to 10 % slower on the first four.
+  // Dense gradients: rows of tokens not routed to the head are zero.  They are
+  // written by the query side's first workgroups, one on every other CU, beside
+  // the matrix work (as a launch of its own the fill runs at the memory's rate
+  // with the matrix cores idle), or by a launch before the packing where the
+  // fill is past 512 MB, about twice the last-level cache, and the products are
+  // few for it: beside them it takes those the cached tiles, and the workgroups
+  // that write outlast the rest.  A routed row has about K T / H products and
+  // (H - K) / K rows to fill; the line lies at 400 of the one for the other.
+  // Backward with a launch / beside, us (zipf: skewed routing), d 128 unless given:
+  //   up to 512 MB  T 200, H 32, K 8, d 64 (4 MB) 21.5 / 17.4; B 4, T 4096 (302 MB)
+  //                 192 / 184; T 4096, H 64, K 1 (396 MB) 108 / 97
+  //   fewer than 400  T 6000, H 64, K 1 137 / 141; B 4, T 4096, H 32, K 4 262 / 287; T
+  //                 8192, H 64, K 2 189 / 227; T 16000, H 64, K 8 608 / 643; B 4, T
+  //                 4096, H 64, K 1 307 / 433; 20000, H 64, K 8 (357) even; but zipf
+  //                 T 12289, H 64, K 4 592 / 550
+  //   from 400 on (whole steps)  T 24000, H 64, K 8 (429) 1304 / 1285; T 32768 2053 /
+  //                 1961; T 30000, H 32, K 4 926 / 921; B 4, T 8192, H 16, K 4 653 / 634;
+  //                 B 8, T 8192, H 32, K 8, d 64 1198 / 1170; zipf T 32768, H 64, K 8,
+  //                 d 64 3272 / 3285.
+  // Workgroups beside: 256 or 64 of them up to 10 % slower on small fills.
   constexpr int RPB = kZeroThreads / (D / 4);
   constexpr size_t kFillBeside = static_cast<size_t>(512) << 20;
   const int cus = bwd_cu_count();
   const long units = static_cast<long>(B) * ((T + RPB - 1) / RPB);
   const size_t fill = packed ? 0 : static_cast<size_t>(B) * T * (H - K) * D * 3 * sizeof(float);
+  const bool ahead = fill > kFillBeside && static_cast<double>(K) * K * T < 400.0 * H * (H - K);
   const ZeroRows zero{topk_idx, dq, dk, dv, B, H, K,
-                      fill == 0 || fill > kFillBeside
-                          ? 0 : static_cast<int>(std::min<long>(units, std::max(cus / 2, 1)))};
-  if (fill > kFillBeside) {
+                      fill == 0 || ahead ? 0 : static_cast<int>(std::min<long>(units, std::max(cus / 2, 1)))};
+  if (ahead) {
     const size_t rows = static_cast<size_t>(BH) * T;
     k_bwd_zero_unrouted<D><<<static_cast<unsigned>((rows + RPB - 1) / RPB), kZeroThreads, 0, st>>>(zero, T, rows);
     if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -2,8 +2,9 @@
 exactly zero and the others equal the packed gradients, in outputs that hold NaN.
 
 Token counts around the fill's units (16 tokens at d = 64, 8 at d = 128), more units than
-fill workgroups, every head selected, 64 heads, and fills on both sides of 512 MB (written
-beside the query side's products, or by a launch of their own)."""
+fill workgroups, every head selected, 64 heads, fills on both sides of 512 MB (written beside
+the query side's products, or by a launch of their own), and past it on both sides of 400
+products a filled row (beside again from there on)."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -27,7 +28,8 @@ from gpu_util import DEV, say  # noqa: E402
                                        (2, 33, 4, 4, 64), (3, 700, 8, 2, 128), (1, 2307, 6, 1, 64),
                                        (1, 5548, 64, 1, 128),
                                        (1, 5549, 64, 1, 128), (2, 5548, 64, 1, 64),
-                                       (3, 3699, 64, 1, 64)])
+                                       (3, 3699, 64, 1, 64),
+                                       (110, 799, 8, 4, 128), (110, 800, 8, 4, 128)])
 def test_dense_rows(B, T, H, K, d):
     say(f"dense gradients B {B} T {T} H {H} K {K} d {d}")
     g = torch.Generator(device=DEV).manual_seed(T)
